@@ -87,6 +87,43 @@ def test_quantize_fp8_nonfinite_flag():
     assert np.isnan(scales.cpu().numpy()[1]) and np.all(codes.cpu().numpy()[1] == 0)
 
 
+# every row-length range of the FP8 kernels at its edges, one cell past each, and the two-pass rows
+@pytest.mark.parametrize("k", [16, 512, 1024, 1040, 2048, 2064, 3584, 3600, 4096, 4112, 8192, 8208, 16384, 16400,
+                               32768, 32784])
+def test_quantize_fp8_row_lengths(k):
+    w = special_rows(synth.normal_f16((7, k), 0.02, synth.stream_seed(2, k)))
+    codes, scales = sq.sq_quantize_fp8_e4m3(w.to(DEV))
+    c_ref, s_ref = oracle.quantize_fp8_e4m3(bits16(w))
+    assert np.array_equal(codes.cpu().numpy(), c_ref)
+    assert np.array_equal(scales.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
+
+
+def test_quantize_fp8_every_half():
+    """All 63488 finite halves, by magnitude, in rows of 992: every rounding and tie under many row scales."""
+    mags = np.arange(0x7C00, dtype=np.uint16)
+    h = np.stack([mags, mags | 0x8000], -1).reshape(64, 992)
+    w = torch.from_numpy(h.view(np.float16).copy())
+    codes, scales = sq.sq_quantize_fp8_e4m3(w.to(DEV))
+    c_ref, s_ref = oracle.quantize_fp8_e4m3(h)
+    assert np.array_equal(codes.cpu().numpy(), c_ref)
+    assert np.array_equal(scales.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("unit", [1.0, 2.0 ** -14, 2.0 ** -24, 0.0371, 777.0])
+def test_quantize_int4_ties(unit):
+    """Groups of multiples of half a step (exact ties where the step is a half itself), ranges on either side of zero."""
+    g = torch.Generator().manual_seed(3)
+    steps = torch.randint(-30, 31, (61, 3 * 128), generator=g).double()
+    steps[::3] = steps[::3].abs()
+    steps[1::3] = -steps[1::3].abs()
+    w = (steps * (0.5 * unit)).half() if unit != 2.0 ** -24 else (steps * unit).half()
+    codes, scales, zeros = sq.sq_quantize_int4_g128(w.to(DEV))
+    c_ref, s_ref, z_ref = oracle.quantize_int4_g128(bits16(w))
+    assert np.array_equal(codes.cpu().numpy(), c_ref)
+    assert np.array_equal(bits16(scales), s_ref)
+    assert np.array_equal(bits16(zeros), z_ref)
+
+
 # ----------------------------------------------------------------- GEMV ----
 # (3, 8192) and (2, 16384): a few rows with long rows, so tasks span several
 # wavefronts of one workgroup with idle wavefronts between them
