@@ -6,24 +6,35 @@
 // b * (2kd + 1) rows spread over the whole chip:
 //   1. stats:    per (row, chunk) the max of z = l / T and sum exp(z - max),
 //                fp64 (online-softmax partials, merged later in chunk order);
-//   2. decide:   per (sequence, chunk) merge the row partials, take the kd
+//   2. accept:   per (sequence, chunk) merge the row partials, take the kd
 //                accept decisions u * q(x) < p(x) (one thread each), find the
 //                first rejection n, and sum the chunk's share of the draw
 //                weights R = rint(r * 2^60) in int64 (exact, so the total
-//                does not depend on the summation order);
-//   3. draw:     per sequence, locate the chunk holding t = floor(u Z / 2^24)
-//                with a block scan of the chunk totals, then block-scan that
-//                chunk.
+//                does not depend on the summation order); the workgroup that
+//                finishes a sequence's last chunk draws: it locates the chunk
+//                holding t = floor(u Z / 2^24) with a block scan of the chunk
+//                totals, then block-scans that chunk.
+// A call is a chain of latencies (launch, load, reduce), not of bytes: the
+// draw as a kernel of its own cost a third launch per call, and reductions
+// through LDS permutes instead of DPP moves most of the time inside a kernel
+// (one sequence, 151936 logits, T = 1: a call 15.3 -> 12.1 us).
 // Probabilities are computed in fp64 and held in fp32 (prob32), the values
 // q_out / p_out hand back; the decisions and the draw weights are formed in
 // fp64 from those fp32 values, so that they can be reproduced exactly from
 // q_out / p_out.  A -inf logit is a masked token (probability 0).  A row
 // holding a NaN or +inf logit, or no finite logit, has no distribution: its
 // sequence gets n_accepted = next_token = -1 (and NaN rows in q_out / p_out).
-// Greedy uses per-chunk (max, first index) pairs and one decision pass.
+// Greedy reduces every row to its argmax in one kernel, whose last workgroup
+// per sequence takes the decisions.
+//
+// Last workgroups are found by counting arrivals.  A workgroup publishes its
+// part with an agent-scope store, waits for that store and then adds to the
+// counter, so the one that completes the count sees every part; nobody waits
+// for another workgroup.  The counters are zero between launches: that workgroup resets its.
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "sq_device.hpp"
 #include "sq_internal.hpp"
@@ -37,56 +48,200 @@ constexpr int kThreads = 256;
 constexpr int kChunk = kAcceptChunk;  // 1024: a 152k-token row spreads over 149 workgroups
 constexpr int kPer = kChunk / kThreads;  // logits per thread and chunk
 
-struct SeqInfo {
-  int n;
-  int pad;
-  double lp, sp, lq, sq;  // merged (max, sum) of the draw rows p_n and q_n
-};
-
-struct ArgMax {
-  float v;
-  int i;
-};
-
-__device__ __forceinline__ double zval(float l, float t) { return t == 1.0f ? (double)l : (double)l / (double)t; }
-
-__device__ __forceinline__ int64_t grid_weight(double r) { return llrint(ldexp(r, 60)); }
-
-// A probability exp(z - L) / S in fp64, held in fp32: the one expression
-// behind q_out / p_out, the decisions and the draw weights.
-__device__ __forceinline__ float prob32(float l, float t, double L, double S) {
-  return (float)(exp(zval(l, t) - L) / S);
+__device__ __forceinline__ double quotient(double a, double b, double rb) {
+  const double q = a * rb;
+  return __builtin_fma(__builtin_fma(-q, b, a), rb, q);
 }
 
-// Deterministic block reductions over 256 threads (4 wavefronts).
-__device__ double block_max(double v, double* sh) {
+// What the softmax arithmetic of a thread holds in registers.  These kernels
+// are bound by fp64 instructions (one per four cycles) where there are many
+// rows, so the two expensive operations have forms of their own:
+//   z = l / T and p = exp / S: an estimate by the reciprocal plus one
+//     exact-remainder correction, the correctly rounded quotient for three
+//     operations instead of a dozen; kOne: T == 1, z = l;
+//   exp of x <= 0: n = rint(x / ln 2) (Cody and Waite's two-part reduction),
+//     then the minimax polynomial of degree 11 on |r| <= ln(2) / 2 (Remez
+//     exchange, relative error 3.1e-18, below the rounding of its evaluation)
+//     and the scaling by 2^n: 17 operations, without the library's range
+//     selections.  Below -1100 (a masked logit's -inf too) it gives 0.
+// The coefficients sit in vector registers, so that every step is one
+// three-operand fma (72 rows of 151936 logits, statistics: 21.6 -> 13.3 us).
+template <bool kOne>
+struct Soft {
+  static constexpr bool one = kOne;
+  double t, rt;
+  double c[10], l2e, magic, hi, lo;
+
+  __device__ __forceinline__ explicit Soft(float temp)
+      : t((double)temp), rt(kOne ? 1.0 : 1.0 / (double)temp),
+        c{0x1.ad66168f6ec16p-26, 0x1.28b31c3ff65e9p-22, 0x1.71df45378dcabp-19, 0x1.a01992c5bfed9p-16,
+          0x1.a01a0110431a9p-13, 0x1.6c16c187853cdp-10, 0x1.1111111130e38p-7, 0x1.555555554f35cp-5,
+          0x1.55555555554a2p-3, 0x1.0000000000010p-1},
+        l2e(0x1.71547652b82fep+0), magic(0x1.8p52), hi(-0x1.62e42fefa2000p-1), lo(-0x1.9ef35793c7673p-41) {
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  v = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-  __syncthreads();
+    for (int i = 0; i < 10; ++i) asm("" : "+v"(c[i]));
+    asm("" : "+v"(l2e), "+v"(magic), "+v"(hi), "+v"(lo));
+  }
+
+  __device__ __forceinline__ double exp(double x) const {
+    x = fmax(x, -1100.0);
+    const double k = __builtin_fma(x, l2e, magic);  // rint(x / ln 2) in the low mantissa bits
+    const double n = k - magic;
+    const double r = __builtin_fma(n, lo, __builtin_fma(n, hi, x));
+    double p = __builtin_fma(c[0], r, c[1]);
+#pragma unroll
+    for (int i = 2; i < 10; ++i) p = __builtin_fma(p, r, c[i]);
+    p = __builtin_fma(p, r, 1.0);
+    p = __builtin_fma(p, r, 1.0);
+    return ldexp(p, (int)(uint32_t)__builtin_bit_cast(uint64_t, k));
+  }
+
+  // A masked logit (-inf) becomes a finite value far below every logit's
+  // quotient (a remainder of infinities would be NaN).
+  __device__ __forceinline__ double z(float l) const {
+    if constexpr (kOne) return (double)l;
+    return quotient(fmax((double)l, -1e250), t, rt);
+  }
+};
+
+__device__ __forceinline__ int64_t grid_weight(double r) { return llrint(r * 0x1p60); }
+
+// A probability exp(z - L) / S in fp64, held in fp32 (rS = 1 / S): the one
+// expression behind q_out / p_out, the decisions and the draw weights.  Of a
+// row without a distribution (S NaN) it is NaN.
+template <class T>
+__device__ __forceinline__ float prob32(float l, const T& sf, double L, double S, double rS) {
+  return (float)quotient(sf.exp(sf.z(l) - L), S, rS);
+}
+
+// ---- wavefront reductions and scans on DPP moves (a permute through LDS costs several times the latency)
+template <int Ctrl, int RowMask = 0xF>
+__device__ __forceinline__ uint32_t dpp32(uint32_t v) {  // lanes without a source, or outside RowMask: 0
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, Ctrl, RowMask, 0xF, false);
+}
+
+template <int Ctrl, int RowMask = 0xF, class T>
+__device__ __forceinline__ T dpp_move(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, dpp32<Ctrl, RowMask>(__builtin_bit_cast(uint32_t, v)));
+  } else {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = dpp32<Ctrl, RowMask>((uint32_t)u), hi = dpp32<Ctrl, RowMask>((uint32_t)(u >> 32));
+    return __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
+  }
+}
+
+// op over the 64 lanes, a fixed tree; every lane receives the result.
+template <class T, class Op>
+__device__ __forceinline__ T wave_all(T v, Op op) {
+  v = op(v, dpp_move<0xB1>(v));   // quad_perm [1,0,3,2]
+  v = op(v, dpp_move<0x4E>(v));   // quad_perm [2,3,0,1]
+  v = op(v, dpp_move<0x141>(v));  // row_half_mirror
+  v = op(v, dpp_move<0x140>(v));  // row_mirror: every lane holds its row of 16's result
+  constexpr int N = sizeof(T) / 4;
+  struct W {
+    uint32_t w[N];
+  };
+  W x = __builtin_bit_cast(W, v), y;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const auto p = __builtin_amdgcn_permlane16_swap(x.w[i], x.w[i], false, false);
+    const uint32_t p0 = p[0], p1 = p[1];  // scalar copies: vector element lvalues are misread
+    x.w[i] = p0;
+    y.w[i] = p1;
+  }
+  v = op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+  x = __builtin_bit_cast(W, v);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const auto p = __builtin_amdgcn_permlane32_swap(x.w[i], x.w[i], false, false);
+    const uint32_t p0 = p[0], p1 = p[1];
+    x.w[i] = p0;
+    y.w[i] = p1;
+  }
+  return op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+}
+
+__device__ __forceinline__ float wave_max_f32(float v) {
+  return wave_all(v, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ double wave_max_f64(double v) {
+  return wave_all(v, [](double a, double b) { return fmax(a, b); });
+}
+__device__ __forceinline__ double wave_sum_f64(double v) {
+  return wave_all(v, [](double a, double b) { return a + b; });
+}
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
+  return wave_all(v, [](int64_t a, int64_t b) { return a + b; });
+}
+
+// Inclusive prefix sum over the 64 lanes.
+__device__ __forceinline__ int64_t wave_scan_i64(int64_t v) {
+  v += dpp_move<0x111>(v);       // row_shr:1
+  v += dpp_move<0x112>(v);       // row_shr:2
+  v += dpp_move<0x114>(v);       // row_shr:4
+  v += dpp_move<0x118>(v);       // row_shr:8
+  v += dpp_move<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_move<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
 
-__device__ double block_sum(double v, double* sh) {
+// Exclusive prefix sum of v over the workgroup in thread order; `total`
+// receives the workgroup's sum.  Integer, so exact.  sh: one cell per wavefront.
+template <int kWaves>
+__device__ int64_t block_exclusive_scan_i64(int64_t v, int64_t* sh, int64_t& total) {
+  const int w = threadIdx.x >> 6;
+  const int64_t x = wave_scan_i64(v);
+  if ((threadIdx.x & 63) == 63) sh[w] = x;
+  __syncthreads();
+  int64_t base = 0, t = 0;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  for (int i = 0; i < kWaves; ++i) {
+    base += i < w ? sh[i] : 0;
+    t += sh[i];
+  }
+  total = t;
   __syncthreads();
-  v = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-  __syncthreads();
-  return v;
+  return base + x - v;
 }
 
+template <int kWaves>
 __device__ int64_t block_sum_i64(int64_t v, int64_t* sh) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  v = wave_sum_i64(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  v = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  int64_t t = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) t += sh[i];
   __syncthreads();
-  return v;
+  return t;
+}
+
+// ---- parts published to a last workgroup
+__device__ __forceinline__ void publish(int64_t* p, int64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int64_t published(const int64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Arrival counters, zero between launches: set 0 for the calls on the
+// library's workspace, set 1 for the allocation-free call (the two may run on
+// different streams).  A launch covers at most kSlots rows or sequences.
+constexpr int kSlots = 65536;
+static __device__ int32_t arrivals[2][2][kSlots];
+
+// One thread's arrival, after its parts are published: true for the last of n
+// (every part is visible to it; the counter is reset).  The parts are written
+// through to the level all XCDs share, so the wait for their stores is all
+// the release needs (a release fence would also write back the whole L2,
+// measured at about 2 us), and they are read from there.
+__device__ __forceinline__ bool arrive(int32_t* counter, int n) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (n == 1) return true;
+  if (__hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n - 1) return false;
+  __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
 }
 
 // Row r of the combined row space: target rows first ([b][kd+1] order), then
@@ -96,28 +251,9 @@ __device__ __forceinline__ const float* row_ptr(const float* draft, const float*
   return r < rows_t ? target + r * v : draft + (r - rows_t) * v;
 }
 
-// Exclusive prefix sum of v over the 256 threads in thread order; `total`
-// receives the block's sum.  Integer, so exact.
-__device__ int64_t block_exclusive_scan_i64(int64_t v, int64_t* sh, int64_t& total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int64_t x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int64_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
-  if (lane == 63) sh[w] = x;
-  __syncthreads();
-  int64_t base = 0;
-  for (int i = 0; i < w; ++i) base += sh[i];
-  total = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-  __syncthreads();
-  return base + x - v;
-}
-
 // One wavefront merges a row's chunk partials: L = max over chunks, S = the
 // sum of S_c exp(L_c - L), each lane taking every 64th chunk in increasing
-// order and the lanes combined in a fixed shuffle tree.  A fully masked chunk
+// order and the lanes combined in a fixed tree.  A fully masked chunk
 // (S_c = 0) adds nothing; a chunk marked invalid (S_c NaN), or a row without
 // any mass, gives L = S = NaN.  Every lane returns the values.
 //
@@ -135,8 +271,9 @@ __device__ __forceinline__ void load_cells(const double2* st, int nchunk, double
   for (int i = 0; i < kCells; ++i) e[i] = st[min(lane + 64 * i, nchunk - 1)];
 }
 
-template <bool kWide>
-__device__ void merge_cells(const double2* st, int nchunk, const double2 (&e)[kCells], double& L, double& S) {
+template <bool kWide, class T>
+__device__ void merge_cells(const T& sf, const double2* st, int nchunk, const double2 (&e)[kCells], double& L,
+                            double& S) {
   const int lane = threadIdx.x & 63;
   double mx = -INFINITY;
   int bad = 0;
@@ -153,24 +290,20 @@ __device__ void merge_cells(const double2* st, int nchunk, const double2 (&e)[kC
       if (f.y > 0.0) mx = fmax(mx, f.x);
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    mx = fmax(mx, __shfl_xor(mx, off, 64));
-    bad |= __shfl_xor(bad, off, 64);
-  }
+  mx = wave_max_f64(mx);
+  const bool any_bad = __any(bad);
   double s = 0.0;
 #pragma unroll
   for (int i = 0; i < kCells; ++i)
-    if (lane + 64 * i < nchunk && e[i].y > 0.0) s += e[i].y * exp(e[i].x - mx);
+    if (lane + 64 * i < nchunk && e[i].y > 0.0) s += e[i].y * sf.exp(e[i].x - mx);
   if constexpr (kWide) {
     for (int c = lane + 64 * kCells; c < nchunk; c += 64) {
       const double2 f = st[c];
-      if (f.y > 0.0) s += f.y * exp(f.x - mx);
+      if (f.y > 0.0) s += f.y * sf.exp(f.x - mx);
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (bad || !(s > 0.0)) {
+  s = wave_sum_f64(s);
+  if (any_bad || !(s > 0.0)) {
     mx = NAN;
     s = NAN;
   }
@@ -178,96 +311,105 @@ __device__ void merge_cells(const double2* st, int nchunk, const double2 (&e)[kC
   S = s;
 }
 
-__device__ void wave_merge(const double2* st, int nchunk, double& L, double& S) {
+template <class T>
+__device__ void wave_merge(const T& sf, const double2* st, int nchunk, double& L, double& S) {
   double2 e[kCells];
   load_cells(st, nchunk, e);
-  merge_cells<true>(st, nchunk, e, L, S);
+  merge_cells<true>(sf, st, nchunk, e, L, S);
 }
 
 // 1. per (row, chunk): (max z, sum exp(z - max z)).  blockIdx.x = row * nchunk + chunk.
-__global__ __launch_bounds__(kThreads) void stats_kernel(const float* __restrict__ draft,
-                                                         const float* __restrict__ target, int64_t rows_t, int v,
-                                                         float temp, int nchunk, double2* __restrict__ stats) {
-  __shared__ double sh[4];
+// One wavefront holds a whole chunk: with four, each with four logits a lane,
+// the reductions and barriers were most of the instructions issued.
+constexpr int kCPer = kChunk / 64;  // logits per lane where a wavefront holds a chunk
+
+__device__ __forceinline__ void load_row_chunk(const float* __restrict__ l, int c, int v, float (&x)[kCPer]) {
+#pragma unroll
+  for (int e = 0; e < kCPer; ++e) x[e] = l[min(c * kChunk + e * 64 + (int)(threadIdx.x & 63), v - 1)];
+}
+
+template <bool kOne>
+__global__ __launch_bounds__(64) void stats_kernel(const float* __restrict__ draft, const float* __restrict__ target,
+                                                   int64_t rows_t, int v, float temp, int nchunk,
+                                                   double2* __restrict__ stats) {
   const int64_t row = blockIdx.x / nchunk;
   const int c = blockIdx.x % nchunk;
-  const float* l = row_ptr(draft, target, rows_t, row, v);
-  const int beg = c * kChunk;
-  double z[kPer];
-  double mx = -INFINITY;
+  float x[kCPer];
+  load_row_chunk(row_ptr(draft, target, rows_t, row, v), c, v, x);
+  const Soft<kOne> sf(temp);
+  float m32 = -INFINITY;
   int bad = 0;
 #pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    const int j = beg + e * kThreads + threadIdx.x;
-    const float lj = j < v ? l[j] : -INFINITY;
-    bad |= (isnan(lj) || lj == INFINITY) ? 1 : 0;
-    z[e] = zval(lj, temp);
-    if (!isnan(z[e])) mx = fmax(mx, z[e]);
+  for (int e = 0; e < kCPer; ++e) {
+    if (c * kChunk + e * 64 + (int)threadIdx.x >= v) x[e] = -INFINITY;
+    bad |= (isnan(x[e]) || x[e] == INFINITY) ? 1 : 0;
+    m32 = fmaxf(m32, x[e]);
   }
-  bad = __syncthreads_or(bad);
-  mx = block_max(mx, sh);
+  m32 = wave_max_f32(m32);
+  const bool mass = m32 > -INFINITY;  // uniform
+  const double mx = mass ? sf.z(m32) : -INFINITY;  // l / T grows with l
+  bad = __any(bad);
   double s = 0.0;
-  if (mx > -INFINITY && !bad) {  // uniform across the block
+  if (mass && !bad) {
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) s += exp(z[e] - mx);  // masked and padded cells add exp(-inf) = 0
+    for (int e = 0; e < kCPer; ++e) s += sf.exp(sf.z(x[e]) - mx);  // masked and padded cells add exp(-inf) = 0
   }
-  s = block_sum(s, sh);
+  s = wave_sum_f64(s);
   // (max, sum); a fully masked chunk is (-inf, 0); an invalid one (NaN, NaN)
   if (threadIdx.x == 0) stats[row * nchunk + c] = bad ? make_double2(NAN, NAN) : make_double2(mx, s);
 }
 
 // Optional copies of the distributions: p or q = exp(z - L) / S as fp32.
-__global__ __launch_bounds__(kThreads) void probs_kernel(const float* __restrict__ draft,
-                                                         const float* __restrict__ target, int64_t rows_t, int v,
-                                                         float temp, int nchunk, const double2* __restrict__ stats,
-                                                         float* __restrict__ q_out, float* __restrict__ p_out) {
-  __shared__ double sL, sS;
+template <bool kOne>
+__global__ __launch_bounds__(64) void probs_kernel(const float* __restrict__ draft, const float* __restrict__ target,
+                                                   int64_t rows_t, int v, float temp, int nchunk,
+                                                   const double2* __restrict__ stats, float* __restrict__ q_out,
+                                                   float* __restrict__ p_out) {
   const int64_t row = blockIdx.x / nchunk;
   const int c = blockIdx.x % nchunk;
   float* out = row < rows_t ? (p_out ? p_out + row * v : nullptr) : (q_out ? q_out + (row - rows_t) * v : nullptr);
-  if (!out) return;  // uniform across the block
-  if (threadIdx.x < 64) {
-    double L, S;
-    wave_merge(stats + row * nchunk, nchunk, L, S);
-    if (threadIdx.x == 0) {
-      sL = L;
-      sS = S;
-    }
-  }
-  __syncthreads();
-  const double L = sL, S = sS;  // NaN for a row without a distribution: NaN out
-  const float* l = row_ptr(draft, target, rows_t, row, v);
-  for (int e = 0; e < kPer; ++e) {
-    const int j = c * kChunk + e * kThreads + threadIdx.x;
-    if (j < v) out[j] = prob32(l[j], temp, L, S);
+  if (!out) return;  // uniform
+  float x[kCPer];
+  load_row_chunk(row_ptr(draft, target, rows_t, row, v), c, v, x);
+  double L, S;  // NaN for a row without a distribution: NaN out
+  const Soft<kOne> sf(temp);
+  wave_merge(sf, stats + row * nchunk, nchunk, L, S);
+  const double rS = 1.0 / S;
+#pragma unroll
+  for (int e = 0; e < kCPer; ++e) {
+    const int j = c * kChunk + e * 64 + (int)threadIdx.x;
+    if (j < v) out[j] = prob32(x[e], sf, L, S, rS);
   }
 }
 
 // 2. per (sequence, chunk): decisions, first rejection, chunk share of the draw weights.
 // zs[(s * nchunk + c) * 2 + 0] = sum of R over the chunk for the draw row
 // (residual max(0, p_n - q_n) when n < kd, else p_kd); [.. + 1] = sum of R for
-// p_n (the fallback when the residual mass is zero).  A sequence with a row
-// without a distribution gets n = -1 and zero weights.
-// blockIdx.x = s * nchunk + c.
+// p_n (the fallback when the residual mass is zero).  The last workgroup of a
+// sequence draws.  A sequence with a row without a distribution gets -1.
+// blockIdx.x = (s - s0) * nchunk + c.
 // Loads that wait for nothing computed here go out together, so that their
 // round trips overlap: the draft tokens and their uniforms, the first rows of
 // chunk partials, the logits at the tokens, and this chunk of p_0 and q_0
 // (the draw rows when the first draft token is rejected, or when kd = 0).
 // Every one of them is unconditional (indices clamped, the value ignored
 // where it does not apply).
-template <bool kWide>
-__global__ __launch_bounds__(kThreads) void decide_kernel(const float* __restrict__ draft,
+template <bool kWide, bool kOne>
+__global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restrict__ draft,
                                                           const float* __restrict__ target,
                                                           const int32_t* __restrict__ tokens,
                                                           const uint32_t* __restrict__ u24, int b, int kd, int v,
                                                           float temp, int nchunk, const double2* __restrict__ stats,
-                                                          int64_t* __restrict__ zs, SeqInfo* __restrict__ info) {
+                                                          int64_t* __restrict__ zs, int s0, int set,
+                                                          int32_t* __restrict__ n_accepted,
+                                                          int32_t* __restrict__ next_token) {
   constexpr int kBatch = 3;  // rows of partials a wavefront holds at once
   __shared__ double sL[129], sS[129];
   __shared__ int sAcc[64];
-  __shared__ int sN;
-  __shared__ int64_t shi[4];
-  const int s = blockIdx.x / nchunk;
+  __shared__ int64_t sh0[4], sh1[4];
+  __shared__ int sLast, sChunk;
+  __shared__ int64_t sOff;
+  const int s = s0 + blockIdx.x / nchunk;
   const int c = blockIdx.x % nchunk;
   const int w = threadIdx.x >> 6;
   const int nrows = 2 * kd + 1;
@@ -284,6 +426,7 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(const float* __restric
   const int32_t* tp = kd > 0 ? tokens + (int64_t)di * b + s : (const int32_t*)(u24 + (int64_t)s * (kd + 1));
   const int32_t xraw = *tp;
   const uint32_t ut = u24[(int64_t)s * (kd + 1) + di];
+  const uint32_t us = u24[(int64_t)s * (kd + 1) + kd];  // the draw's
   // the 2kd + 1 rows' statistics, one wavefront per row, kBatch rows in flight
   double2 e[kBatch][kCells];
   auto load_batch = [&](int r0) {
@@ -306,13 +449,14 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(const float* __restric
   const int xi = tok_ok ? xraw : 0;
   const float lpt = trow[(int64_t)di * v + xi];
   const float lqt = kd > 0 ? draft[((int64_t)di * b + s) * v + xi] : trow[xi];
+  const Soft<kOne> sf(temp);
   auto merge_batch = [&](int r0) {
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int rr = r0 + 4 * j;
       if (rr < nrows) {
         double L, S;
-        merge_cells<kWide>(stats + row_of(rr) * nchunk, nchunk, e[j], L, S);
+        merge_cells<kWide>(sf, stats + row_of(rr) * nchunk, nchunk, e[j], L, S);
         if ((threadIdx.x & 63) == 0) {
           sL[rr] = L;
           sS[rr] = S;
@@ -326,50 +470,39 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(const float* __restric
     merge_batch(r0);
   }
   __syncthreads();
+  // every wavefront reads all rows' sums and agrees on their validity
   int invalid = 0;
-  for (int rr = threadIdx.x; rr < nrows; rr += kThreads) invalid |= isnan(sS[rr]) ? 1 : 0;
-  invalid = __syncthreads_or(invalid);
-  if (dlane && !invalid) {
-    const int i = threadIdx.x;
-    int acc = 0;
-    if (tok_ok) {
-      // fp32 probabilities; u (24 bits) times q (24 bits) is exact in fp64
-      const float p = prob32(lpt, temp, sL[i], sS[i]);
-      const float q = prob32(lqt, temp, sL[kd + 1 + i], sS[kd + 1 + i]);
-      const double u = ldexp((double)(ut & 0xFFFFFFu), -24);
-      acc = (u * (double)q < (double)p) ? 1 : 0;
-    }
-    sAcc[i] = acc;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int n = kd;
-    for (int i = 0; i < kd; ++i)
-      if (!sAcc[i]) {
-        n = i;
-        break;
-      }
-    sN = invalid ? -1 : n;
-  }
-  __syncthreads();
-  const int n = sN;
-  if (n < 0) {  // uniform across the block
-    if (threadIdx.x == 0) {
-      zs[((int64_t)s * nchunk + c) * 2 + 0] = 0;
-      zs[((int64_t)s * nchunk + c) * 2 + 1] = 0;
-      if (c == 0) {
-        SeqInfo si;
-        si.n = -1;
-        si.pad = 0;
-        si.lp = si.sp = si.lq = si.sq = 0.0;
-        info[s] = si;
-      }
+  for (int rr = threadIdx.x & 63; rr < nrows; rr += 64) invalid |= isnan(sS[rr]) ? 1 : 0;
+  invalid = __any(invalid);
+  if (invalid) {  // uniform across the sequence's workgroups
+    if (threadIdx.x == 0 && c == 0) {
+      n_accepted[s] = -1;
+      next_token[s] = -1;
     }
     return;
   }
-  const double Lp = sL[n], Sp = sS[n];
+  int n = 0;
+  if (kd > 0) {
+    if (dlane) {
+      const int i = threadIdx.x;
+      int acc = 0;
+      if (tok_ok) {
+        // fp32 probabilities; u (24 bits) times q (24 bits) is exact in fp64
+        const float p = prob32(lpt, sf, sL[i], sS[i], 1.0 / sS[i]);
+        const float q = prob32(lqt, sf, sL[kd + 1 + i], sS[kd + 1 + i], 1.0 / sS[kd + 1 + i]);
+        const double u = ldexp((double)(ut & 0xFFFFFFu), -24);
+        acc = (u * (double)q < (double)p) ? 1 : 0;
+      }
+      sAcc[i] = acc;
+    }
+    __syncthreads();
+    const int i = threadIdx.x & 63;  // kd <= 64: the first rejection, found by every wavefront
+    const uint64_t rej = __ballot(i < kd && !sAcc[i]);
+    n = rej ? __ffsll((unsigned long long)rej) - 1 : kd;
+  }
+  const double Lp = sL[n], Sp = sS[n], rSp = 1.0 / Sp;
   const bool resid = n < kd;
-  const double Lq = resid ? sL[kd + 1 + n] : 0.0, Sq = resid ? sS[kd + 1 + n] : 1.0;
+  const double Lq = resid ? sL[kd + 1 + n] : 0.0, Sq = resid ? sS[kd + 1 + n] : 1.0, rSq = 1.0 / Sq;
   if (n > 0) {  // uniform across the block; n = 0 uses the rows loaded ahead
     load_chunk(trow + (int64_t)n * v, pv);
     if (resid) load_chunk(draft + ((int64_t)n * b + s) * v, qv);
@@ -379,9 +512,9 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(const float* __restric
   for (int k = 0; k < kPer; ++k) {
     const int j = c * kChunk + k * kThreads + threadIdx.x;
     if (j >= v) break;
-    const float p = prob32(pv[k], temp, Lp, Sp);
+    const float p = prob32(pv[k], sf, Lp, Sp, rSp);
     if (resid) {
-      const float q = prob32(qv[k], temp, Lq, Sq);
+      const float q = prob32(qv[k], sf, Lq, Sq, rSq);
       const double r = (double)p - (double)q;
       z0 += grid_weight(r > 0.0 ? r : 0.0);
       z1 += grid_weight((double)p);
@@ -389,69 +522,46 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(const float* __restric
       z0 += grid_weight((double)p);
     }
   }
-  z0 = block_sum_i64(z0, shi);
-  z1 = block_sum_i64(z1, shi);
+  z0 = wave_sum_i64(z0);
+  if (resid) z1 = wave_sum_i64(z1);
+  if ((threadIdx.x & 63) == 0) {
+    sh0[w] = z0;
+    sh1[w] = z1;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    zs[((int64_t)s * nchunk + c) * 2 + 0] = z0;
-    zs[((int64_t)s * nchunk + c) * 2 + 1] = z1;
-    if (c == 0) {
-      SeqInfo si;
-      si.n = n;
-      si.pad = 0;
-      si.lp = Lp;
-      si.sp = Sp;
-      si.lq = Lq;
-      si.sq = Sq;
-      info[s] = si;
-    }
+    int64_t* zc = zs + ((int64_t)s * nchunk + c) * 2;
+    publish(zc, (sh0[0] + sh0[1]) + (sh0[2] + sh0[3]));
+    publish(zc + 1, (sh1[0] + sh1[1]) + (sh1[2] + sh1[3]));
+    sLast = arrive(&arrivals[set][0][s - s0], nchunk);
+    sChunk = -1;
   }
-}
+  __syncthreads();
+  if (!sLast) return;  // uniform across the block
 
-// 3. per sequence: the draw.  The chunk holding t is found with a block scan
-// over the chunk totals (256 chunks at a time), then the chunk is scanned
-// with kPer consecutive logits per thread, so that the block's exclusive scan
-// of the thread sums orders them.  All sums are int64, so exact.  The
-// sequence's record, its uniform and the first 256 chunk totals are loaded
-// together at the start (none waits for another).
-__global__ __launch_bounds__(kThreads) void draw_kernel(const float* __restrict__ draft,
-                                                        const float* __restrict__ target,
-                                                        const uint32_t* __restrict__ u24, int b, int kd, int v,
-                                                        float temp, int nchunk, const int64_t* __restrict__ zs,
-                                                        const SeqInfo* __restrict__ info,
-                                                        int32_t* __restrict__ n_accepted,
-                                                        int32_t* __restrict__ next_token) {
-  __shared__ int64_t sOff;
-  __shared__ int sChunk;
-  __shared__ int64_t shi[4];
-  const int s = blockIdx.x;
+  // 3. the draw, by the sequence's last workgroup: the chunk holding t is
+  // found with a block scan over the chunk totals (256 chunks at a time), then
+  // the chunk is scanned with kPer consecutive logits per thread, so that the
+  // block's exclusive scan of the thread sums orders them.  All sums are
+  // int64, so exact.
   const int64_t* z = zs + (int64_t)s * nchunk * 2;
-  const SeqInfo si = info[s];
-  const uint32_t us = u24[(int64_t)s * (kd + 1) + kd];
-  // thread t holds chunk t's totals (a thread past the last chunk reads the
-  // last one and takes 0)
-  const int tc = min((int)threadIdx.x, nchunk - 1);
-  const int64_t ra = z[2 * tc], rb = z[2 * tc + 1];
-  const bool first = (int)threadIdx.x < nchunk;
-  const int64_t za = first ? ra : 0, zb = first ? rb : 0;
-
-  // the total mass Z of the draw row (the residual's, else p_n's when that is zero on the grid)
-  int64_t part = za;
-  for (int c = threadIdx.x + kThreads; c < nchunk; c += kThreads) part += z[2 * c];
-  int64_t Z = block_sum_i64(part, shi);
-  const int n = si.n;
-  if (n < 0) {  // a row without a distribution (uniform across the block)
-    if (threadIdx.x == 0) {
-      n_accepted[s] = -1;
-      next_token[s] = -1;
-    }
-    return;
-  }
   int which = 0;
-  if (Z == 0 && n < kd) {  // uniform across the block
+  int64_t Z = 0, pre0 = 0, zc0 = 0;  // thread t: chunk t's prefix and total
+  auto totals = [&]() {
+    const bool in = (int)threadIdx.x < nchunk;
+    const int64_t r = published(z + 2 * min((int)threadIdx.x, nchunk - 1) + which);
+    zc0 = in ? r : 0;
+    pre0 = block_exclusive_scan_i64<4>(zc0, sh0, Z);
+    if (nchunk > kThreads) {
+      int64_t part = 0;
+      for (int i = threadIdx.x + kThreads; i < nchunk; i += kThreads) part += published(z + 2 * i + which);
+      Z += block_sum_i64<4>(part, sh0);
+    }
+  };
+  totals();
+  if (Z == 0 && resid) {  // uniform across the block: no residual mass on the grid, back to p_n
     which = 1;
-    part = zb;
-    for (int c = threadIdx.x + kThreads; c < nchunk; c += kThreads) part += z[2 * c + 1];
-    Z = block_sum_i64(part, shi);
+    totals();
   }
   if (Z == 0) {  // no mass on the fixed-point grid
     if (threadIdx.x == 0) {
@@ -465,21 +575,27 @@ __global__ __launch_bounds__(kThreads) void draw_kernel(const float* __restrict_
   const uint64_t hi = __umul64hi(uu, (uint64_t)Z);
   const int64_t t = (int64_t)((hi << 40) | (lo >> 24));  // floor(u * Z / 2^24) < Z
 
-  // the chunk c with run(c) <= t < run(c) + z_c, 256 chunks at a time
-  if (threadIdx.x == 0) sChunk = -1;
-  int64_t run = 0;
-  for (int c0 = 0; c0 < nchunk; c0 += kThreads) {
-    const int c = c0 + (int)threadIdx.x;
-    const int64_t zc = c0 == 0 ? (which ? zb : za) : c < nchunk ? z[2 * c + which] : 0;
-    int64_t tile;
-    const int64_t pre = run + block_exclusive_scan_i64(zc, shi, tile);
-    if (zc > 0 && pre <= t && t < pre + zc) {
-      sChunk = c;
-      sOff = t - pre;
+  // the chunk i with run(i) <= t < run(i) + z_i
+  if (zc0 > 0 && pre0 <= t && t < pre0 + zc0) {
+    sChunk = (int)threadIdx.x;
+    sOff = t - pre0;
+  }
+  __syncthreads();
+  if (sChunk < 0 && nchunk > kThreads) {  // uniform: in a later batch of 256 chunks
+    int64_t run = 0;
+    for (int i0 = 0; i0 < nchunk; i0 += kThreads) {
+      const int i = i0 + (int)threadIdx.x;
+      const int64_t zc = i < nchunk ? published(z + 2 * i + which) : 0;
+      int64_t tile;
+      const int64_t pre = run + block_exclusive_scan_i64<4>(zc, sh0, tile);
+      if (zc > 0 && pre <= t && t < pre + zc) {
+        sChunk = i;
+        sOff = t - pre;
+      }
+      __syncthreads();
+      if (sChunk >= 0) break;  // uniform across the block
+      run += tile;
     }
-    __syncthreads();
-    if (sChunk >= 0) break;  // uniform across the block
-    run += tile;
   }
   const int chunk = sChunk;
   if (chunk < 0) {  // cannot happen (t < Z); kept so that no index can leave the row
@@ -490,46 +606,44 @@ __global__ __launch_bounds__(kThreads) void draw_kernel(const float* __restrict_
     return;
   }
   const int64_t off = sOff;
-  const bool resid = n < kd && which == 0;
-  const float* lp = target + ((int64_t)s * (kd + 1) + n) * v;
-  const float* lq = resid ? draft + ((int64_t)n * b + s) * v : nullptr;
+  const bool both = resid && which == 0;
+  const float* lp = trow + (int64_t)n * v;
+  const float* lq = both ? draft + ((int64_t)n * b + s) * v : lp;
   int64_t R[kPer];
   int64_t local = 0;
   const int beg = chunk * kChunk + threadIdx.x * kPer;
-  float pv[kPer], qv[kPer];  // every load of the chunk in flight at once
 #pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    const int j = beg + e;
-    pv[e] = j < v ? lp[j] : 0.0f;
-    qv[e] = resid && j < v ? lq[j] : 0.0f;
+  for (int e2 = 0; e2 < kPer; ++e2) {  // every load of the chunk in flight at once
+    const int j = min(beg + e2, v - 1);
+    pv[e2] = lp[j];
+    qv[e2] = lq[j];
   }
 #pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    const int j = beg + e;
-    int64_t w = 0;
-    if (j < v) {
-      const float p = prob32(pv[e], temp, si.lp, si.sp);
-      if (resid) {
-        const float q = prob32(qv[e], temp, si.lq, si.sq);
+  for (int e2 = 0; e2 < kPer; ++e2) {
+    int64_t wt = 0;
+    if (beg + e2 < v) {
+      const float p = prob32(pv[e2], sf, Lp, Sp, rSp);
+      if (both) {
+        const float q = prob32(qv[e2], sf, Lq, Sq, rSq);
         const double r = (double)p - (double)q;
-        w = grid_weight(r > 0.0 ? r : 0.0);
+        wt = grid_weight(r > 0.0 ? r : 0.0);
       } else {
-        w = grid_weight((double)p);
+        wt = grid_weight((double)p);
       }
     }
-    R[e] = w;
-    local += w;
+    R[e2] = wt;
+    local += wt;
   }
   int64_t tot;
-  const int64_t pre = block_exclusive_scan_i64(local, shi, tot);
+  const int64_t pre = block_exclusive_scan_i64<4>(local, sh0, tot);
   if (local > 0 && pre <= off && off < pre + local) {
     int64_t acc = pre;
     int tok = beg;
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      acc += R[e];
+    for (int e2 = 0; e2 < kPer; ++e2) {
+      acc += R[e2];
       if (acc > off) {
-        tok = beg + e;
+        tok = beg + e2;
         break;
       }
     }
@@ -538,101 +652,102 @@ __global__ __launch_bounds__(kThreads) void draw_kernel(const float* __restrict_
   }
 }
 
-// Greedy: per (target row, chunk) the max finite logit and its smallest
-// index (index kNone when the chunk has no finite logit, kBad when it holds a
-// NaN or +inf).
-constexpr int kNone = 0x7FFFFFFF;
-constexpr int kBad = -1;
+// Greedy.  A row's argmax is the largest 64-bit key (ordered logit, inverted
+// index): the largest finite logit, its smallest index; 0 when it has no
+// finite logit, all ones when it holds a NaN or +inf.  A workgroup takes
+// kGreedyChunk logits of a row; the row's last workgroup merges the chunks'
+// keys and publishes the row's, and (kDecide) the sequence's last row takes
+// the decisions.  (Four sequences of 151936 logits, per call: 25.9 -> 8.9 us;
+// one thread per row walked the chunks in a second kernel before.)
+// blockIdx.x = (row - row0) * nchunk + c, rows_s rows per sequence.
+constexpr int kGreedyPer = 16;
+constexpr int kGreedyChunk = kThreads * kGreedyPer;
+constexpr uint64_t kBadKey = ~0ull;
 
-__global__ __launch_bounds__(kThreads) void argmax_kernel(const float* __restrict__ target, int v, int nchunk,
-                                                          ArgMax* __restrict__ out) {
-  __shared__ float sv[4];
-  __shared__ int si[4];
-  const int64_t row = blockIdx.x / nchunk;
-  const int c = blockIdx.x % nchunk;
-  const float* l = target + row * v;
-  float best = -INFINITY;
-  int bi = kNone;
-  int bad = 0;
-  for (int e = 0; e < kPer; ++e) {
-    const int j = c * kChunk + e * kThreads + threadIdx.x;
-    if (j < v) {
-      const float x = l[j];
-      bad |= (isnan(x) || x == INFINITY) ? 1 : 0;
-      if (isfinite(x) && (bi == kNone || x > best || (x == best && j < bi))) {
-        best = x;
-        bi = j;
-      }
-    }
-  }
-  bad = __syncthreads_or(bad);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float ov = __shfl_xor(best, off, 64);
-    const int oi = __shfl_xor(bi, off, 64);
-    if (oi != kNone && (bi == kNone || ov > best || (ov == best && oi < bi))) {
-      best = ov;
-      bi = oi;
-    }
-  }
-  if ((threadIdx.x & 63) == 0) {
-    sv[threadIdx.x >> 6] = best;
-    si[threadIdx.x >> 6] = bi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w)
-      if (si[w] != kNone && (bi == kNone || sv[w] > best || (sv[w] == best && si[w] < bi))) {
-        best = sv[w];
-        bi = si[w];
-      }
-    ArgMax a;
-    a.v = best;
-    a.i = bad ? kBad : bi;
-    out[row * nchunk + c] = a;
-  }
+__device__ __forceinline__ uint64_t logit_key(float x, int j) {
+  if (isnan(x) || x == INFINITY) return kBadKey;
+  if (x == -INFINITY) return 0;
+  const uint32_t u = __float_as_uint(x + 0.0f);  // -0 compares as +0
+  const uint32_t o = (u & 0x80000000u) ? ~u : u | 0x80000000u;
+  return (uint64_t)o << 32 | (uint32_t)~j;
 }
 
-__global__ __launch_bounds__(kThreads) void greedy_kernel(const int32_t* __restrict__ tokens, int b, int kd, int v,
-                                                          int nchunk, const ArgMax* __restrict__ am,
+// the index of a row's key, -1: the row has no greedy target
+__device__ __forceinline__ int key_index(uint64_t k) { return k == 0 || k == kBadKey ? -1 : (int)~(uint32_t)k; }
+
+__device__ uint64_t block_key_max(uint64_t k, uint64_t* sh) {
+  k = wave_all(k, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = k;
+  __syncthreads();
+  const uint64_t a = sh[0] > sh[1] ? sh[0] : sh[1], b = sh[2] > sh[3] ? sh[2] : sh[3];
+  __syncthreads();
+  return a > b ? a : b;
+}
+
+template <bool kDecide>
+__global__ __launch_bounds__(kThreads) void argmax_kernel(const float* __restrict__ target,
+                                                          const int32_t* __restrict__ tokens, int b, int kd, int v,
+                                                          int nchunk, int64_t row0, int rows_s, int set,
+                                                          int64_t* __restrict__ keys, int64_t* __restrict__ row_keys,
                                                           int32_t* __restrict__ n_accepted,
                                                           int32_t* __restrict__ next_token) {
-  __shared__ int sArg[65];
-  const int s = blockIdx.x;
-  for (int i = threadIdx.x; i <= kd; i += kThreads) {
-    const ArgMax* a = am + ((int64_t)s * (kd + 1) + i) * nchunk;
-    float best = -INFINITY;
-    int bi = kNone;
-    bool bad = false;
-    for (int c = 0; c < nchunk; ++c) {
-      const ArgMax e = a[c];
-      bad |= e.i == kBad;
-      if (e.i != kBad && e.i != kNone && (bi == kNone || e.v > best)) {  // chunks ascend: ties keep the earlier
-        best = e.v;
-        bi = e.i;
-      }
+  __shared__ uint64_t sh[4];
+  __shared__ int sLast;
+  const int lrow = blockIdx.x / nchunk;  // row of this launch
+  const int64_t row = row0 + lrow;
+  const int c = blockIdx.x % nchunk;
+  const float* l = target + row * v;
+  float x[kGreedyPer];
+#pragma unroll
+  for (int e = 0; e < kGreedyPer; ++e) {
+    const int j = c * kGreedyChunk + e * kThreads + (int)threadIdx.x;
+    x[e] = l[min(j, v - 1)];
+  }
+  uint64_t key = 0;
+#pragma unroll
+  for (int e = 0; e < kGreedyPer; ++e) {  // a clamped index repeats the last logit: the same key
+    const uint64_t k = logit_key(x[e], min(c * kGreedyChunk + e * kThreads + (int)threadIdx.x, v - 1));
+    key = k > key ? k : key;
+  }
+  key = block_key_max(key, sh);
+  if (nchunk > 1) {
+    if (threadIdx.x == 0) {
+      publish(keys + row * nchunk + c, (int64_t)key);
+      sLast = arrive(&arrivals[set][0][lrow], nchunk);
     }
-    sArg[i] = (bad || bi == kNone) ? -1 : bi;  // -1: the row has no greedy target
+    __syncthreads();
+    if (!sLast) return;  // uniform across the block
+    key = 0;
+    for (int i = threadIdx.x; i < nchunk; i += kThreads) {
+      const uint64_t k = (uint64_t)published(keys + row * nchunk + i);
+      key = k > key ? k : key;
+    }
+    key = block_key_max(key, sh);
+  }
+  if (!kDecide) {
+    if (threadIdx.x == 0) row_keys[row] = (int64_t)key;
+    return;
+  }
+  const int64_t s = row / rows_s;  // rows_s = kd + 1
+  if (threadIdx.x == 0) {
+    publish(row_keys + row, (int64_t)key);
+    sLast = arrive(&arrivals[set][1][lrow / rows_s], rows_s);
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    bool invalid = false;
-    for (int i = 0; i <= kd; ++i) invalid |= sArg[i] < 0;
-    if (invalid) {
-      n_accepted[s] = -1;
-      next_token[s] = -1;
-      return;
-    }
-    int n = kd;
-    for (int i = 0; i < kd; ++i) {
-      const int32_t xt = tokens[(int64_t)i * b + s];
-      if (xt < 0 || xt >= v || xt != sArg[i]) {
-        n = i;
-        break;
-      }
-    }
-    n_accepted[s] = n;
-    next_token[s] = sArg[n];
+  if (!sLast || threadIdx.x >= 64) return;
+  // position i's greedy token on lane i (kd <= 64: lane 0 also takes position kd)
+  const int i = threadIdx.x;
+  const int64_t* rk = row_keys + s * rows_s;
+  const int arg = i < kd ? key_index((uint64_t)published(rk + i)) : 0;
+  const int last = key_index((uint64_t)published(rk + kd));
+  const bool invalid = __any(arg < 0 || last < 0);
+  const int32_t xt = i < kd ? tokens[(int64_t)i * b + s] : 0;
+  const uint64_t rej = __ballot(i < kd && xt != arg);  // (arg is in [0, v): so is an accepted token)
+  const int n = rej ? __ffsll((unsigned long long)rej) - 1 : kd;
+  const int tok = n < kd ? __shfl(arg, n, 64) : last;
+  if (i == 0) {
+    n_accepted[s] = invalid ? -1 : n;
+    next_token[s] = invalid ? -1 : tok;
   }
 }
 
@@ -640,9 +755,8 @@ __global__ __launch_bounds__(kThreads) void greedy_kernel(const int32_t* __restr
 // Multi-candidate acceptance: each sequence has c draft chains of kd tokens;
 // target rows [b][c][kd+1], draft rows [kd][b][c], tokens [kd][b][c],
 // uniforms [b][c kd + 1] (u[d c + j] tests chain j at depth d, u[c kd] drives
-// the final draw).  The fp32 distributions are materialised first (probs
-// kernel); then one workgroup of kMThreads per sequence walks the chains'
-// prefix tree with recursive rejection sampling on the int64 grid:
+// the final draw).  The chains' prefix tree is walked with recursive rejection
+// sampling on the int64 grid over the fp32 distributions:
 //   first candidate at a node:   u q(x) < p(x) in fp64 (exact);
 //   its rejection:               R = rint(max(0, p - q) 2^60), Z = sum R;
 //   later candidates:            u q(x) Z < R(x), exact in 128-bit integers;
@@ -651,19 +765,22 @@ __global__ __launch_bounds__(kThreads) void greedy_kernel(const int32_t* __restr
 //   all alive candidates fail:   draw from R; after kd accepted: from p_kd.
 // Integer sums do not depend on their order, so the results are those of the
 // same rule applied to the fp32 distributions in any order.
+//
+// The candidates of a node (the chains sharing its prefix, in order) do not
+// depend on what is accepted elsewhere, so every node's residual masses Z can
+// be summed for all nodes and vocabulary chunks at once: multi_rows_kernel
+// gives every row's merged statistics, p's masses and the masses after a first
+// rejection, launch i = 1 .. c - 1 of multi_step_kernel the mass after the
+// rejection of a node's candidate i, which needs only the masses before it.  R
+// itself, and p and q unless they are asked for, are recomputed from the
+// logits where they are needed, never stored.  One workgroup per sequence
+// (multi_walk_kernel) then takes all decisions in parallel, walks the tree and
+// draws.  c + 1 launches over the whole chip replace a walk of up to c kd
+// passes over the vocabulary by one workgroup per sequence (two sequences,
+// four chains of four, 151936 logits, the whole call: 306 -> 75 us).
 constexpr int kMThreads = 1024;
 constexpr int kMWaves = kMThreads / 64;
-
-__device__ __forceinline__ int64_t mblock_sum_i64(int64_t v, int64_t* sh) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  __syncthreads();  // sh may still be read by an earlier call
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int64_t t = 0;
-  for (int w = 0; w < kMWaves; ++w) t += sh[w];
-  return t;
-}
+constexpr int kStepBlocks = 8192;  // workgroups of one step launch, about
 
 // q = m 2^e exactly (m < 2^24), from the bits of a finite q >= 0.
 __device__ __forceinline__ void split_f32(float q, uint64_t& m, int& e) {
@@ -713,148 +830,340 @@ __device__ __forceinline__ bool test_grid(uint32_t u24, float q, int64_t z, int6
   return lhi < rhi || (lhi == rhi && llo < rlo);
 }
 
-__global__ __launch_bounds__(kMThreads) void multi_kernel(const float* __restrict__ p32, const float* __restrict__ q32,
-                                                          const int32_t* __restrict__ tokens,
-                                                          const uint32_t* __restrict__ u24, int b, int c, int kd,
-                                                          int v, int nchunk, const double2* __restrict__ stats,
-                                                          int64_t* __restrict__ grid, int32_t* __restrict__ n_accepted,
-                                                          int32_t* __restrict__ next_token,
-                                                          int32_t* __restrict__ chain) {
-  __shared__ int64_t sh[kMWaves];
-  __shared__ int sBad;
-  __shared__ int64_t sR;
-  __shared__ int sTok;
-  const int s = blockIdx.x;
-  const int t = threadIdx.x;
-  const int64_t rows_t = (int64_t)b * c * (kd + 1);
-  // every row of the sequence must have a distribution (its merged statistics finite)
-  if (t == 0) sBad = 0;
-  __syncthreads();
-  for (int rr = t >> 6; rr < c * (2 * kd + 1); rr += kMWaves) {
-    int64_t row;
-    if (rr < c * (kd + 1)) {
-      row = (int64_t)s * c * (kd + 1) + rr;
-    } else {
-      const int k2 = rr - c * (kd + 1);  // draft row d * c + j
-      row = rows_t + ((int64_t)(k2 / c) * b + s) * c + k2 % c;
-    }
-    double L, S;
-    wave_merge(stats + row * nchunk, nchunk, L, S);
-    if ((t & 63) == 0 && isnan(S)) atomicOr(&sBad, 1);
+// A row's logits and its merged statistics: prob() is prob32 of one of them.
+struct Row {
+  const float* l;
+  double L, S, rS;
+};
+
+__device__ __forceinline__ Row row_at(const float* l, double2 ls) { return Row{l, ls.x, ls.y, 1.0 / ls.y}; }
+
+template <class T>
+__device__ __forceinline__ float prob(const Row& r, const T& sf, int y) {
+  return prob32(r.l[y], sf, r.L, r.S, r.rS);
+}
+
+// Every call's rows and tables: ls [rows] merged statistics (target rows
+// first), zp [rows_t][nchunk] masses of p, zs [b][kd][c][nchunk] residual
+// masses.
+struct MultiArgs {
+  const float* draft;
+  const float* target;
+  const int32_t* tokens;
+  int b, c, kd, v, nchunk;
+  float temp;
+  double2* ls;
+  int64_t* zp;
+  int64_t* zs;
+};
+
+// A node: the chains of sequence s that share chain j's first d tokens, and
+// its target and draft rows: those of the lowest of them (their common context
+// gives all of them the same).
+struct Node {
+  uint64_t alive;
+  int64_t trow;  // the target row
+  Row p, q;
+};
+
+__device__ __forceinline__ Node node_at(const MultiArgs& a, uint64_t alive, int s, int d) {
+  const int j0 = __ffsll((unsigned long long)alive) - 1;
+  Node n;
+  n.alive = alive;
+  n.trow = ((int64_t)s * a.c + j0) * (a.kd + 1) + d;
+  n.p = row_at(a.target + n.trow * a.v, a.ls[n.trow]);
+  if (d < a.kd) {
+    const int64_t r = ((int64_t)d * a.b + s) * a.c + j0;
+    n.q = row_at(a.draft + r * a.v, a.ls[(int64_t)a.b * a.c * (a.kd + 1) + r]);
+  } else {
+    n.q = n.p;
   }
+  return n;
+}
+
+// The residual weight of p, q after the rejections of the node's candidates
+// before chain `stop` (64: of all of them).  zt(j): the mass after chain j's
+// rejection as summed (0: the node falls back to p, whose mass zp() gives).
+// zcur receives the mass of the returned weights.
+template <class ZT, class ZP>
+__device__ __forceinline__ int64_t residual_at(uint64_t alive, float p, float q, int stop, ZT zt, ZP zp,
+                                               int64_t& zcur) {
+  int64_t w = 0, z = 0;
+  bool first = true;
+  for (uint64_t rest = alive; rest; rest &= rest - 1) {
+    const int j = __ffsll((unsigned long long)rest) - 1;
+    if (j >= stop) break;
+    if (first) {
+      const double r = (double)p - (double)q;
+      w = grid_weight(r > 0.0 ? r : 0.0);
+    } else {
+      const int64_t w0 = w - floor_qz(q, z);
+      w = w0 > 0 ? w0 : 0;
+    }
+    first = false;
+    z = zt(j);
+    if (z == 0) {
+      w = grid_weight((double)p);
+      z = zp();
+    }
+  }
+  zcur = z;
+  return w;
+}
+
+// Sum of a row of n chunk values by one wavefront (every lane receives it).
+__device__ __forceinline__ int64_t wave_row_sum(const int64_t* r, int n) {
+  int64_t t = 0;
+  for (int i = threadIdx.x & 63; i < n; i += 64) t += r[i];
+  return wave_sum_i64(t);
+}
+
+// Per (target row, chunk), one wavefront: the row's and its draft row's merged
+// statistics (by chunk 0), the chunk's mass of p and, for the rows with a
+// draft, of max(0, p - q): the mass after chain j's rejection if it is its
+// node's first candidate.  Copies of the distributions where asked for.
+template <bool kOne>
+__global__ __launch_bounds__(64) void multi_rows_kernel(MultiArgs a, const double2* __restrict__ stats,
+                                                        float* __restrict__ q_out, float* __restrict__ p_out) {
+  const int64_t row = blockIdx.x / a.nchunk;  // (s c + j) (kd + 1) + d
+  const int ch = blockIdx.x % a.nchunk;
+  const int d = (int)(row % (a.kd + 1));
+  const int64_t sj = row / (a.kd + 1), rows_t = (int64_t)a.b * a.c * (a.kd + 1);
+  const bool drafted = d < a.kd;
+  const int64_t drow = drafted ? (int64_t)d * a.b * a.c + sj : 0;
+  float xp[kCPer], xq[kCPer];
+  load_row_chunk(a.target + row * a.v, ch, a.v, xp);
+  if (drafted) load_row_chunk(a.draft + drow * a.v, ch, a.v, xq);
+  double Lp, Sp, Lq = 0.0, Sq = 1.0;
+  const Soft<kOne> sf(a.temp);
+  wave_merge(sf, stats + row * a.nchunk, a.nchunk, Lp, Sp);
+  if (drafted) wave_merge(sf, stats + (rows_t + drow) * a.nchunk, a.nchunk, Lq, Sq);
+  if (ch == 0 && threadIdx.x == 0) {
+    a.ls[row] = make_double2(Lp, Sp);
+    if (drafted) a.ls[rows_t + drow] = make_double2(Lq, Sq);
+  }
+  const double rSp = 1.0 / Sp, rSq = 1.0 / Sq;
+  int64_t zp = 0, zr = 0;
+#pragma unroll
+  for (int e = 0; e < kCPer; ++e) {
+    const int y = ch * kChunk + e * 64 + (int)threadIdx.x;
+    if (y < a.v) {
+      const float p = prob32(xp[e], sf, Lp, Sp, rSp);
+      zp += grid_weight((double)p);
+      if (p_out) p_out[row * a.v + y] = p;
+      if (drafted) {
+        const float q = prob32(xq[e], sf, Lq, Sq, rSq);
+        const double r = (double)p - (double)q;
+        zr += grid_weight(r > 0.0 ? r : 0.0);
+        if (q_out) q_out[drow * a.v + y] = q;
+      }
+    }
+  }
+  zp = wave_sum_i64(zp);
+  zr = wave_sum_i64(zr);
+  if (threadIdx.x == 0) {
+    a.zp[row * a.nchunk + ch] = zp;
+    const int64_t s = sj / a.c, j = sj - s * a.c;
+    if (drafted) a.zs[((s * a.kd + d) * a.c + j) * a.nchunk + ch] = zr;
+  }
+}
+
+// Step `step` = 1, 2, ..: for every (sequence, depth, chain) whose chain is its
+// node's candidate number `step` (from 0), zs[..][chunk] = the chunk's residual
+// mass after that chain's rejection.  blockIdx.x = ((s kd + d) (c - step) +
+// j - step) slices + slice (at most j candidates come before chain j); a
+// workgroup takes the chunks slice, slice + slices, ...
+template <bool kOne>
+__global__ __launch_bounds__(kThreads) void multi_step_kernel(MultiArgs a, int slices, int step) {
+  __shared__ int64_t sh[4];
+  __shared__ int64_t sz[64];
+  __shared__ int64_t szp;
+  const int slice = blockIdx.x % slices, nj = a.c - step;
+  const int sdj = blockIdx.x / slices, sd = sdj / nj;
+  const int j = step + sdj - sd * nj, s = sd / a.kd, d = sd - s * a.kd;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // the chains with chain j's prefix, chain `lane` looked at by its lane (c <= 64)
+  bool same = lane < a.c;
+#pragma unroll 4
+  for (int i = 0; i < d; ++i) {
+    const int32_t* tk = a.tokens + ((int64_t)i * a.b + s) * a.c;
+    same &= tk[lane < a.c ? lane : 0] == tk[j];
+  }
+  const uint64_t alive = __ballot(same);
+  if (__popcll(alive & ((1ull << j) - 1ull)) != step) return;  // uniform across the block
+  const Node nd = node_at(a, alive, s, d);
+  int64_t* zrow = a.zs + ((int64_t)sd * a.c + j) * a.nchunk;
+  // this workgroup's first logits, and the masses of the candidates before it, a wavefront each
+  float xp[kPer], xq[kPer];
+  auto load = [&](int ch) {
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const int y = min(ch * kChunk + e * kThreads + (int)threadIdx.x, a.v - 1);
+      xp[e] = nd.p.l[y];
+      xq[e] = nd.q.l[y];
+    }
+  };
+  load(slice);
+  int r = 0;
+  for (uint64_t rest = alive; rest; rest &= rest - 1) {
+    const int i = __ffsll((unsigned long long)rest) - 1;
+    if (i >= j) break;
+    if ((r++ & 3) != w) continue;
+    const int64_t t = wave_row_sum(zrow + (int64_t)(i - j) * a.nchunk, a.nchunk);
+    if (lane == 0) sz[i] = t;
+  }
+  if (w == 3) {
+    const int64_t t = wave_row_sum(a.zp + nd.trow * a.nchunk, a.nchunk);
+    if (lane == 0) szp = t;
+  }
+  const Soft<kOne> sf(a.temp);
   __syncthreads();
-  if (sBad) {
+  for (int ch = slice; ch < a.nchunk; ch += slices) {
+    if (ch != slice) load(ch);
+    int64_t z = 0;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if (ch * kChunk + e * kThreads + (int)threadIdx.x >= a.v) break;
+      const float p = prob32(xp[e], sf, nd.p.L, nd.p.S, nd.p.rS), q = prob32(xq[e], sf, nd.q.L, nd.q.S, nd.q.rS);
+      int64_t zc;
+      const int64_t w1 = residual_at(alive, p, q, j, [&](int i) { return sz[i]; }, [&]() { return szp; }, zc);
+      const int64_t w0 = w1 - floor_qz(q, zc);
+      z += w0 > 0 ? w0 : 0;
+    }
+    z = block_sum_i64<4>(z, sh);
+    if (threadIdx.x == 0) zrow[ch] = z;
+  }
+}
+
+// One workgroup per sequence: the masses, every (depth, chain)'s test, the walk,
+// the draw.  LDS: masses [kd c] int64, tokens [kd c], test results [kd c].
+template <bool kOne>
+__global__ __launch_bounds__(kMThreads) void multi_walk_kernel(MultiArgs a, const uint32_t* __restrict__ u24,
+                                                               int32_t* __restrict__ n_accepted,
+                                                               int32_t* __restrict__ next_token,
+                                                               int32_t* __restrict__ chain) {
+  extern __shared__ __align__(16) char msmem[];
+  __shared__ int64_t sh[kMWaves];
+  __shared__ int sN, sChunk, sTok;
+  __shared__ uint64_t sAlive;
+  __shared__ int64_t sOff;
+  const int c = a.c, kd = a.kd, v = a.v, nchunk = a.nchunk, np = kd * c;
+  int64_t* sz = reinterpret_cast<int64_t*>(msmem);
+  int32_t* stok = reinterpret_cast<int32_t*>(sz + np);
+  int32_t* sacc = stok + np;
+  const int s = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t rows_t = (int64_t)a.b * c * (kd + 1);
+  // every row of the sequence must have a distribution
+  int bad = 0;
+  for (int rr = t; rr < c * (2 * kd + 1); rr += kMThreads) {
+    const int k2 = rr - c * (kd + 1);  // draft row d * c + j
+    bad |= isnan(a.ls[k2 < 0 ? (int64_t)s * c * (kd + 1) + rr : rows_t + ((int64_t)(k2 / c) * a.b + s) * c + k2 % c].y);
+  }
+  for (int i = t; i < np; i += kMThreads) stok[i] = a.tokens[((int64_t)(i / c) * a.b + s) * c + i % c];
+  for (int i = w; i < np; i += kMWaves) {
+    const int64_t z = wave_row_sum(a.zs + ((int64_t)s * np + i) * nchunk, nchunk);
+    if (lane == 0) sz[i] = z;
+  }
+  if (t == 0) sChunk = sTok = -1;
+  if (__syncthreads_or(bad)) {
     if (t == 0) n_accepted[s] = next_token[s] = chain[s] = -1;
     return;
   }
-  int64_t* R = grid + (int64_t)s * v;
+  const Soft<kOne> sf(a.temp);
   const uint32_t* u = u24 + (int64_t)s * (c * kd + 1);
-  const uint64_t all = c == 64 ? ~0ull : ((1ull << c) - 1ull);
-  uint64_t alive = all;
-  int n = kd;
-  int64_t z = 0;
-  auto tok_of = [&](int d, int j) { return tokens[((int64_t)d * b + s) * c + j]; };
-  auto grid_p = [&](const float* p) -> int64_t {  // R = rint(p 2^60), returns Z
-    int64_t part = 0;
-    for (int y = t; y < v; y += kMThreads) {
-      const int64_t w = grid_weight((double)p[y]);
-      R[y] = w;
-      part += w;
-    }
-    return mblock_sum_i64(part, sh);
+  auto zp_sum = [&](int64_t trow) {  // by one thread, and rarely
+    int64_t z = 0;
+    for (int i = 0; i < nchunk; ++i) z += a.zp[trow * nchunk + i];
+    return z;
   };
-  for (int d = 0; d < kd; ++d) {
-    const int j0 = __ffsll((unsigned long long)alive) - 1;
-    const float* p = p32 + (((int64_t)s * c + j0) * (kd + 1) + d) * v;
-    const float* q = q32 + (((int64_t)d * b + s) * c + j0) * v;
-    int accepted = -1;
-    bool first = true;
-    for (uint64_t rest = alive; rest; rest &= rest - 1) {
-      const int j = __ffsll((unsigned long long)rest) - 1;
-      const int32_t x = tok_of(d, j);
-      const uint32_t uj = u[d * c + j];
-      bool acc = false;
-      if (x >= 0 && x < v) {
-        if (first) {
-          acc = ldexp((double)(uj & 0xFFFFFFu), -24) * (double)q[x] < (double)p[x];
-        } else {
-          if (t == 0) sR = R[x];
-          __syncthreads();
-          acc = test_grid(uj, q[x], z, sR);
-          __syncthreads();
-        }
+  // the test of chain j at depth d, given that its first d tokens were accepted
+  for (int i = t; i < np; i += kMThreads) {
+    const int d = i / c, j = i - d * c;
+    const int32_t x = stok[i];
+    int acc = 0;
+    if (x >= 0 && x < v) {
+      uint64_t alive = 0;
+      for (int o = 0; o < c; ++o) {
+        bool same = true;
+        for (int e = 0; e < d && same; ++e) same = stok[e * c + o] == stok[e * c + j];
+        alive |= (uint64_t)same << o;
       }
-      if (acc) {  // uniform: every thread took the same decision
-        accepted = x;
+      const Node nd = node_at(a, alive, s, d);
+      const float p = prob(nd.p, sf, x), q = prob(nd.q, sf, x);
+      const uint32_t uj = u[i];
+      if ((alive & ((1ull << j) - 1ull)) == 0) {
+        acc = ldexp((double)(uj & 0xFFFFFFu), -24) * (double)q < (double)p;
+      } else {
+        int64_t z;
+        const int64_t r = residual_at(
+            alive, p, q, j, [&](int o) { return sz[d * c + o]; }, [&]() { return zp_sum(nd.trow); }, z);
+        acc = test_grid(uj, q, z, r);
+      }
+    }
+    sacc[i] = acc;
+  }
+  __syncthreads();
+  if (w == 0) {  // the walk, chain `lane` on its lane
+    uint64_t alive = c == 64 ? ~0ull : ((1ull << c) - 1ull);
+    int n = kd;
+    for (int d = 0; d < kd; ++d) {
+      const uint64_t acc = __ballot(lane < c && ((alive >> lane) & 1ull) && sacc[d * c + min(lane, c - 1)]);
+      if (!acc) {
+        n = d;
         break;
       }
-      int64_t part = 0;
-      if (first) {
-        for (int y = t; y < v; y += kMThreads) {
-          const double r = (double)p[y] - (double)q[y];
-          const int64_t w = grid_weight(r > 0.0 ? r : 0.0);
-          R[y] = w;
-          part += w;
-        }
-      } else {
-        const int64_t z0 = z;
-        for (int y = t; y < v; y += kMThreads) {
-          const int64_t w0 = R[y] - floor_qz(q[y], z0);
-          const int64_t w = w0 > 0 ? w0 : 0;
-          R[y] = w;
-          part += w;
-        }
-      }
-      z = mblock_sum_i64(part, sh);  // its barrier also publishes R to the workgroup
-      if (z == 0) z = grid_p(p);     // no residual mass on the grid: back to p
-      first = false;
+      const int32_t x = stok[d * c + __ffsll((unsigned long long)acc) - 1];  // the lowest accepted one
+      alive &= __ballot(lane < c && stok[d * c + min(lane, c - 1)] == x);
     }
-    if (accepted < 0) {
-      n = d;
-      break;
+    if (lane == 0) {
+      sN = n;
+      sAlive = alive;
     }
-    uint64_t keep = 0;
-    for (uint64_t rest = alive; rest; rest &= rest - 1) {
-      const int j = __ffsll((unsigned long long)rest) - 1;
-      if (tok_of(d, j) == accepted) keep |= 1ull << j;
-    }
-    alive = keep;
   }
-  const int jf = __ffsll((unsigned long long)alive) - 1;
-  if (n == kd) z = grid_p(p32 + (((int64_t)s * c + jf) * (kd + 1) + kd) * v);
-  // the draw: t = floor(u Z / 2^24); thread i owns a contiguous segment of the row
-  if (t == 0) sTok = -1;
   __syncthreads();
-  if (z > 0) {
+  const int n = sN;
+  const uint64_t alive = sAlive;
+  const int jf = __ffsll((unsigned long long)alive) - 1;
+  const Node nd = node_at(a, alive, s, n);
+  const int jl = 63 - __clzll((unsigned long long)alive);  // the node's last candidate
+  // the draw's chunk masses: the residual's after all rejections, else p's (all
+  // accepted, or no residual mass left)
+  const bool plain = n == kd || sz[n * c + jl] == 0;
+  const int64_t* zc = plain ? a.zp + nd.trow * nchunk : a.zs + ((int64_t)s * np + n * c + jl) * nchunk;
+  int64_t part = 0;
+  for (int i = t; i < nchunk; i += kMThreads) part += zc[i];
+  const int64_t z = block_sum_i64<kMWaves>(part, sh);
+  if (z > 0) {  // uniform across the block
     const uint64_t uu = u[c * kd] & 0xFFFFFFu;
     const int64_t tt = (int64_t)((__umul64hi(uu, (uint64_t)z) << 40) | ((uu * (uint64_t)z) >> 24));
-    const int seg = (v + kMThreads - 1) / kMThreads;
-    const int beg = t * seg, end = beg + seg < v ? beg + seg : v;
-    int64_t local = 0;
-    for (int y = beg; y < end; ++y) local += R[y];
-    // exclusive scan of the segment totals in thread order
-    const int lane = t & 63, w = t >> 6;
-    int64_t x = local;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int64_t yv = __shfl_up(x, off, 64);
-      if (lane >= off) x += yv;
-    }
-    __syncthreads();
-    if (lane == 63) sh[w] = x;
-    __syncthreads();
-    int64_t base = 0;
-    for (int i = 0; i < w; ++i) base += sh[i];
-    const int64_t pre = base + x - local;
-    if (local > 0 && pre <= tt && tt < pre + local) {
-      int64_t acc = pre;
-      for (int y = beg; y < end; ++y) {
-        acc += R[y];
-        if (acc > tt) {
-          sTok = y;
-          break;
-        }
+    int64_t run = 0;
+    for (int i0 = 0; i0 < nchunk; i0 += kMThreads) {
+      const int i = i0 + t;
+      const int64_t m = i < nchunk ? zc[i] : 0;
+      int64_t tile;
+      const int64_t pre = run + block_exclusive_scan_i64<kMWaves>(m, sh, tile);
+      if (m > 0 && pre <= tt && tt < pre + m) {
+        sChunk = i;
+        sOff = tt - pre;
       }
+      __syncthreads();
+      if (sChunk >= 0) break;  // uniform across the block
+      run += tile;
+    }
+    const int ch = sChunk;
+    if (ch >= 0) {  // always (tt < z)
+      const int y = ch * kChunk + t;  // kChunk == kMThreads
+      int64_t r = 0, zi;
+      if (y < v) {
+        const float p = prob(nd.p, sf, y);
+        r = plain ? grid_weight((double)p)
+                  : residual_at(
+                        alive, p, prob(nd.q, sf, y), 64, [&](int o) { return sz[n * c + o]; },
+                        [&]() { return zp_sum(nd.trow); }, zi);
+      }
+      int64_t tile;
+      const int64_t pre = block_exclusive_scan_i64<kMWaves>(r, sh, tile);
+      if (r > 0 && pre <= sOff && sOff < pre + r) sTok = y;
     }
   }
   __syncthreads();
@@ -864,39 +1173,30 @@ __global__ __launch_bounds__(kMThreads) void multi_kernel(const float* __restric
     chain[s] = jf;
   }
 }
+static_assert(kChunk == kMThreads && kChunk % kThreads == 0, "the walk draws from a chunk, one logit per thread");
 
 // Greedy (T = 0) over several chains: per sequence, the argmax of the lowest
 // alive chain's row at each depth is accepted when an alive chain drafted it.
 __global__ __launch_bounds__(kThreads) void multi_greedy_kernel(const int32_t* __restrict__ tokens, int b, int c,
-                                                                int kd, int nchunk, const ArgMax* __restrict__ am,
+                                                                int kd, const int64_t* __restrict__ row_keys,
                                                                 int32_t* __restrict__ n_accepted,
                                                                 int32_t* __restrict__ next_token,
                                                                 int32_t* __restrict__ chain) {
   __shared__ int sArg[64 * 65];
   const int s = blockIdx.x;
   const int rows = c * (kd + 1);
+  int bad = 0;
   for (int r = threadIdx.x; r < rows; r += kThreads) {
-    const ArgMax* a = am + ((int64_t)s * rows + r) * nchunk;
-    float best = -INFINITY;
-    int bi = kNone;
-    bool bad = false;
-    for (int k = 0; k < nchunk; ++k) {
-      const ArgMax e = a[k];
-      bad |= e.i == kBad;
-      if (e.i != kBad && e.i != kNone && (bi == kNone || e.v > best)) {  // chunks ascend: ties keep the earlier
-        best = e.v;
-        bi = e.i;
-      }
-    }
-    sArg[r] = (bad || bi == kNone) ? -1 : bi;
+    const int a = key_index((uint64_t)row_keys[(int64_t)s * rows + r]);
+    sArg[r] = a;
+    bad |= a < 0 ? 1 : 0;
   }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int r = 0; r < rows; ++r)
-    if (sArg[r] < 0) {
-      n_accepted[s] = next_token[s] = chain[s] = -1;
-      return;
-    }
+  if (__syncthreads_or(bad)) {
+    if (threadIdx.x == 0) n_accepted[s] = next_token[s] = chain[s] = -1;
+    return;
+  }
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
   uint64_t alive = c == 64 ? ~0ull : ((1ull << c) - 1ull);
   int n = kd, tok = -1;
   for (int d = 0; d <= kd; ++d) {
@@ -906,11 +1206,7 @@ __global__ __launch_bounds__(kThreads) void multi_greedy_kernel(const int32_t* _
       tok = g;
       break;
     }
-    uint64_t keep = 0;
-    for (uint64_t rest = alive; rest; rest &= rest - 1) {
-      const int j = __ffsll((unsigned long long)rest) - 1;
-      if (tokens[((int64_t)d * b + s) * c + j] == g) keep |= 1ull << j;
-    }
+    const uint64_t keep = alive & __ballot(lane < c && tokens[((int64_t)d * b + s) * c + min(lane, c - 1)] == g);
     if (!keep) {
       n = d;
       tok = g;
@@ -918,70 +1214,102 @@ __global__ __launch_bounds__(kThreads) void multi_greedy_kernel(const int32_t* _
     }
     alive = keep;
   }
-  n_accepted[s] = n;
-  next_token[s] = tok;
-  chain[s] = __ffsll((unsigned long long)alive) - 1;
+  if (lane == 0) {
+    n_accepted[s] = n;
+    next_token[s] = tok;
+    chain[s] = __ffsll((unsigned long long)alive) - 1;
+  }
 }
 
 }  // namespace
 
 namespace {
 
-// Scratch of one call: the greedy pairs, or the row statistics, the chunk
-// weights and the per-sequence state (each part 256-byte aligned).
+// Scratch of one call: the greedy keys (one per chunk, one per row), or the row
+// statistics and the chunk weights (each part 256-byte aligned).  kSeqBytes
+// per sequence is held back beside them, as the size limit of the
+// allocation-free call counts it.
+constexpr size_t kSeqBytes = 40;
 struct AcceptScratch {
   size_t st_bytes, zs_bytes, in_bytes;
   size_t total() const { return st_bytes + zs_bytes + in_bytes; }
 };
+
+size_t pad256(size_t n) { return (n + 255) / 256 * 256; }
 
 AcceptScratch accept_scratch(int b, int kd, int v, float temperature) {
   const int64_t nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * (kd + 1);
   AcceptScratch a;
   if (temperature == 0.0f) {
-    a.st_bytes = ((size_t)rows_t * nchunk * sizeof(ArgMax) + 255) / 256 * 256;
+    // (keys of kGreedyChunk logits, then the rows', fit in the keys of kChunk logits from two chunks on;
+    // a row of one chunk publishes no chunk key)
+    a.st_bytes = pad256((size_t)rows_t * nchunk * sizeof(int64_t));
     a.zs_bytes = a.in_bytes = 0;
     return a;
   }
   const int64_t rows = rows_t + (int64_t)b * kd;
-  a.st_bytes = ((size_t)rows * nchunk * sizeof(double2) + 255) / 256 * 256;
-  a.zs_bytes = ((size_t)b * nchunk * 2 * sizeof(int64_t) + 255) / 256 * 256;
-  a.in_bytes = (size_t)b * sizeof(SeqInfo);
+  a.st_bytes = pad256((size_t)rows * nchunk * sizeof(double2));
+  a.zs_bytes = pad256((size_t)b * nchunk * 2 * sizeof(int64_t));
+  a.in_bytes = (size_t)b * kSeqBytes;
   return a;
+}
+
+// The rows' argmax keys into row_keys = ws [rows], chunk keys after them;
+// with tokens' decisions taken per sequence of kd + 1 rows (decide).
+hipError_t enqueue_argmax(const float* target, const int32_t* tokens, int b, int kd, int v, int64_t rows, bool decide,
+                          int set, int32_t* n_accepted, int32_t* next_token, char* ws, hipStream_t stream) {
+  const int nchunk = (v + kGreedyChunk - 1) / kGreedyChunk;
+  int64_t* row_keys = reinterpret_cast<int64_t*>(ws);
+  int64_t* keys = row_keys + rows;
+  const int64_t slot_rows = decide ? kSlots / (kd + 1) * (kd + 1) : kSlots;  // rows per launch, whole sequences
+  for (int64_t r0 = 0; r0 < rows; r0 += slot_rows) {
+    const int64_t nr = rows - r0 < slot_rows ? rows - r0 : slot_rows;
+    const dim3 grid((unsigned)(nr * nchunk));
+    if (decide)
+      hipLaunchKernelGGL(argmax_kernel<true>, grid, dim3(kThreads), 0, stream, target, tokens, b, kd, v, nchunk, r0,
+                         kd + 1, set, keys, row_keys, n_accepted, next_token);
+    else
+      hipLaunchKernelGGL(argmax_kernel<false>, grid, dim3(kThreads), 0, stream, target, tokens, b, kd, v, nchunk, r0,
+                         1, set, keys, row_keys, n_accepted, next_token);
+  }
+  return hipGetLastError();
 }
 
 // The accept kernels on the scratch `ws` (at least accept_scratch().total() bytes).
 hipError_t enqueue_accept(const float* draft, const float* target, const int32_t* tokens, const uint32_t* u24, int b,
                           int kd, int v, float temperature, int32_t* n_accepted, int32_t* next_token, float* q_out,
-                          float* p_out, char* ws, hipStream_t stream) {
+                          float* p_out, char* ws, int set, hipStream_t stream) {
   const int nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * (kd + 1);
   const AcceptScratch a = accept_scratch(b, kd, v, temperature);
-  if (temperature == 0.0f) {
-    ArgMax* am = reinterpret_cast<ArgMax*>(ws);
-    hipLaunchKernelGGL(argmax_kernel, dim3((unsigned)(rows_t * nchunk)), dim3(kThreads), 0, stream, target, v, nchunk,
-                       am);
-    hipLaunchKernelGGL(greedy_kernel, dim3((unsigned)b), dim3(kThreads), 0, stream, tokens, b, kd, v, nchunk, am,
-                       n_accepted, next_token);
-    return hipGetLastError();
-  }
+  if (temperature == 0.0f)
+    return enqueue_argmax(target, tokens, b, kd, v, rows_t, true, set, n_accepted, next_token, ws, stream);
   const int64_t rows = rows_t + (int64_t)b * kd;
   double2* stats = reinterpret_cast<double2*>(ws);
   int64_t* zs = reinterpret_cast<int64_t*>(ws + a.st_bytes);
-  SeqInfo* info = reinterpret_cast<SeqInfo*>(ws + a.st_bytes + a.zs_bytes);
-  hipLaunchKernelGGL(stats_kernel, dim3((unsigned)(rows * nchunk)), dim3(kThreads), 0, stream, draft, target, rows_t, v,
-                     temperature, nchunk, stats);
-  if (p_out || q_out)
-    hipLaunchKernelGGL(probs_kernel, dim3((unsigned)(rows * nchunk)), dim3(kThreads), 0, stream, draft, target, rows_t,
-                       v, temperature, nchunk, stats, q_out, p_out);
-  if (nchunk > 64 * kCells)
-    hipLaunchKernelGGL(decide_kernel<true>, dim3((unsigned)((int64_t)b * nchunk)), dim3(kThreads), 0, stream, draft,
-                       target, tokens, u24, b, kd, v, temperature, nchunk, stats, zs, info);
+  auto go = [&](auto one_tag) {
+    constexpr bool One = decltype(one_tag)::value;
+    hipLaunchKernelGGL(stats_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target, rows_t,
+                       v, temperature, nchunk, stats);
+    if (p_out || q_out)
+      hipLaunchKernelGGL(probs_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target,
+                         rows_t, v, temperature, nchunk, stats, q_out, p_out);
+    for (int s0 = 0; s0 < b; s0 += kSlots) {
+      const int ns = b - s0 < kSlots ? b - s0 : kSlots;
+      const dim3 grid((unsigned)((int64_t)ns * nchunk));
+      if (nchunk > 64 * kCells)
+        hipLaunchKernelGGL((accept_kernel<true, One>), grid, dim3(kThreads), 0, stream, draft, target, tokens, u24, b,
+                           kd, v, temperature, nchunk, stats, zs, s0, set, n_accepted, next_token);
+      else
+        hipLaunchKernelGGL((accept_kernel<false, One>), grid, dim3(kThreads), 0, stream, draft, target, tokens, u24, b,
+                           kd, v, temperature, nchunk, stats, zs, s0, set, n_accepted, next_token);
+    }
+  };
+  if (temperature == 1.0f)
+    go(std::true_type{});
   else
-    hipLaunchKernelGGL(decide_kernel<false>, dim3((unsigned)((int64_t)b * nchunk)), dim3(kThreads), 0, stream, draft,
-                       target, tokens, u24, b, kd, v, temperature, nchunk, stats, zs, info);
-  hipLaunchKernelGGL(draw_kernel, dim3((unsigned)b), dim3(kThreads), 0, stream, draft, target, u24, b, kd, v,
-                     temperature, nchunk, zs, info, n_accepted, next_token);
+    go(std::false_type{});
   return hipGetLastError();
 }
 
@@ -1026,7 +1354,7 @@ hipError_t launch_spec_accept(const float* draft, const float* target, const int
   const hipError_t e = workspace(accept_scratch(b, kd, v, temperature).total(), stream, &ws);
   if (e != hipSuccess) return e;
   return enqueue_accept(draft, target, tokens, u24, b, kd, v, temperature, n_accepted, next_token, q_out, p_out,
-                        static_cast<char*>(ws), stream);
+                        static_cast<char*>(ws), 0, stream);
 }
 
 hipError_t launch_spec_accept_noalloc(const float* draft, const float* target, const int32_t* tokens,
@@ -1038,20 +1366,18 @@ hipError_t launch_spec_accept_noalloc(const float* draft, const float* target, c
   const hipError_t e = noalloc_scratch(&ws);
   if (e != hipSuccess) return e;
   return enqueue_accept(draft, target, tokens, u24, b, kd, v, temperature, n_accepted, next_token, q_out, p_out, ws,
-                        stream);
+                        1, stream);
 }
 
 
-size_t spec_accept_multi_scratch_bytes(int b, int c, int kd, int v, float temperature, bool have_q, bool have_p) {
+size_t spec_accept_multi_scratch_bytes(int b, int c, int kd, int v, float temperature) {
   const int64_t nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * c * (kd + 1);
-  if (temperature == 0.0f) return ((size_t)rows_t * nchunk * sizeof(ArgMax) + 255) / 256 * 256;
-  const int64_t rows_d = (int64_t)kd * b * c;
-  size_t bytes = ((size_t)(rows_t + rows_d) * nchunk * sizeof(double2) + 255) / 256 * 256;  // stats
-  bytes += ((size_t)b * v * sizeof(int64_t) + 255) / 256 * 256;                              // residual grid
-  if (!have_p) bytes += ((size_t)rows_t * v * sizeof(float) + 255) / 256 * 256;
-  if (!have_q) bytes += ((size_t)rows_d * v * sizeof(float) + 255) / 256 * 256;
-  return bytes;
+  if (temperature == 0.0f) return pad256((size_t)rows_t * (nchunk + 1) * sizeof(int64_t));
+  const int64_t rows = rows_t + (int64_t)kd * b * c;
+  // chunk statistics, merged statistics, chunk masses of p and of the residuals
+  return pad256((size_t)rows * nchunk * sizeof(double2)) + pad256((size_t)rows * sizeof(double2)) +
+         pad256((size_t)rows * nchunk * sizeof(int64_t));
 }
 
 hipError_t launch_spec_accept_multi(const float* draft, const float* target, const int32_t* tokens,
@@ -1059,39 +1385,47 @@ hipError_t launch_spec_accept_multi(const float* draft, const float* target, con
                                     int32_t* n_accepted, int32_t* next_token, int32_t* chain, float* q_out,
                                     float* p_out, hipStream_t stream) {
   void* wsv = nullptr;
-  const hipError_t e =
-      workspace(spec_accept_multi_scratch_bytes(b, c, kd, v, temperature, q_out != nullptr, p_out != nullptr), stream,
-                &wsv);
+  hipError_t e = workspace(spec_accept_multi_scratch_bytes(b, c, kd, v, temperature), stream, &wsv);
   if (e != hipSuccess) return e;
   char* ws = static_cast<char*>(wsv);
   const int nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * c * (kd + 1);
   if (temperature == 0.0f) {
-    ArgMax* am = reinterpret_cast<ArgMax*>(ws);
-    hipLaunchKernelGGL(argmax_kernel, dim3((unsigned)(rows_t * nchunk)), dim3(kThreads), 0, stream, target, v, nchunk,
-                       am);
-    hipLaunchKernelGGL(multi_greedy_kernel, dim3((unsigned)b), dim3(kThreads), 0, stream, tokens, b, c, kd, nchunk, am,
-                       n_accepted, next_token, chain);
+    e = enqueue_argmax(target, tokens, b, kd, v, rows_t, false, 0, n_accepted, next_token, ws, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(multi_greedy_kernel, dim3((unsigned)b), dim3(kThreads), 0, stream, tokens, b, c, kd,
+                       reinterpret_cast<const int64_t*>(ws), n_accepted, next_token, chain);
     return hipGetLastError();
   }
   const int64_t rows_d = (int64_t)kd * b * c, rows = rows_t + rows_d;
   double2* stats = reinterpret_cast<double2*>(ws);
-  ws += ((size_t)rows * nchunk * sizeof(double2) + 255) / 256 * 256;
-  int64_t* grid = reinterpret_cast<int64_t*>(ws);
-  ws += ((size_t)b * v * sizeof(int64_t) + 255) / 256 * 256;
-  float* p32 = p_out;
-  if (!p32) {
-    p32 = reinterpret_cast<float*>(ws);
-    ws += ((size_t)rows_t * v * sizeof(float) + 255) / 256 * 256;
-  }
-  float* q32 = q_out;
-  if (!q32 && rows_d > 0) q32 = reinterpret_cast<float*>(ws);
-  hipLaunchKernelGGL(stats_kernel, dim3((unsigned)(rows * nchunk)), dim3(kThreads), 0, stream, draft, target, rows_t,
-                     v, temperature, nchunk, stats);
-  hipLaunchKernelGGL(probs_kernel, dim3((unsigned)(rows * nchunk)), dim3(kThreads), 0, stream, draft, target, rows_t,
-                     v, temperature, nchunk, stats, q32, p32);
-  hipLaunchKernelGGL(multi_kernel, dim3((unsigned)b), dim3(kMThreads), 0, stream, p32, q32, tokens, u24, b, c, kd, v,
-                     nchunk, stats, grid, n_accepted, next_token, chain);
+  ws += pad256((size_t)rows * nchunk * sizeof(double2));
+  MultiArgs a{draft, target, tokens, b, c, kd, v, nchunk, temperature, reinterpret_cast<double2*>(ws), nullptr, nullptr};
+  ws += pad256((size_t)rows * sizeof(double2));
+  a.zp = reinterpret_cast<int64_t*>(ws);
+  a.zs = a.zp + rows_t * nchunk;
+  // step i: at most c candidates meet at a node; most (sequence, depth, chain)
+  // leave a launch at once, so their number is bounded and the chunks looped
+  // over when there are many
+  int64_t slices = rows_d > 0 ? kStepBlocks / rows_d : 1;
+  slices = slices < 1 ? 1 : (slices > nchunk ? nchunk : slices);
+  const size_t lds = (size_t)kd * c * (sizeof(int64_t) + 2 * sizeof(int32_t));  // at most 64 KB
+  auto go = [&](auto one_tag) {
+    constexpr bool One = decltype(one_tag)::value;
+    hipLaunchKernelGGL(stats_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target, rows_t,
+                       v, temperature, nchunk, stats);
+    hipLaunchKernelGGL(multi_rows_kernel<One>, dim3((unsigned)(rows_t * nchunk)), dim3(64), 0, stream, a, stats, q_out,
+                       p_out);
+    for (int i = 1; rows_d > 0 && i < c; ++i)
+      hipLaunchKernelGGL(multi_step_kernel<One>, dim3((unsigned)(rows_d / c * (c - i) * slices)), dim3(kThreads), 0,
+                         stream, a, (int)slices, i);
+    hipLaunchKernelGGL(multi_walk_kernel<One>, dim3((unsigned)b), dim3(kMThreads), lds, stream, a, u24, n_accepted,
+                       next_token, chain);
+  };
+  if (temperature == 1.0f)
+    go(std::true_type{});
+  else
+    go(std::false_type{});
   return hipGetLastError();
 }
 

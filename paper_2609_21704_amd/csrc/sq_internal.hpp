@@ -126,7 +126,7 @@ hipError_t launch_spec_commit(const int32_t* n_accepted, const int32_t* next_tok
                               int64_t out_capacity, int32_t* out_len, int32_t* status, hipStream_t stream);
 
 // Multi-candidate acceptance over c draft chains per sequence (accept.hip).
-size_t spec_accept_multi_scratch_bytes(int b, int c, int kd, int v, float temperature, bool have_q, bool have_p);
+size_t spec_accept_multi_scratch_bytes(int b, int c, int kd, int v, float temperature);
 hipError_t launch_spec_accept_multi(const float* draft, const float* target, const int32_t* tokens,
                                     const uint32_t* u24, int b, int c, int kd, int v, float temperature,
                                     int32_t* n_accepted, int32_t* next_token, int32_t* chain, float* q_out,

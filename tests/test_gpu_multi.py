@@ -79,6 +79,27 @@ def test_multi_accept_matches_the_oracle(b, c, kd, v, noise):
     print(f"\n[multi] b {b} c {c} kd {kd} v {v}: n {n.tolist()} chains {ch.tolist()}", flush=True)
 
 
+@pytest.mark.parametrize("c,v,temp", [(3, 1024, 0.7), (2, 1025, 1.0), (5, 3000, 2.5)])
+def test_multi_accept_without_residual_mass(c, v, temp):
+    """p = q and undrafted (invalid) candidates: every rejection leaves no mass, so the node falls back to p, at
+    temperatures other than 1 too and at the edge of a chunk."""
+    b, kd = 6, 3
+    dl, tl, tok, u = make_case(b, c, kd, v, seed=c, noise=0.0)
+    tok[0, :3, 0] = -1
+    tok[0, 1, :] = v
+    tok[1, 2, :] = -5
+    tl[4, :, 1:] += 0.5 * torch.randn(tl[4, :, 1:].shape, generator=gen(1))
+    q_out, p_out = torch.empty((kd, b, c, v), device=DEV), torch.empty((b, c, kd + 1, v), device=DEV)
+    n, t, ch = sq.sq_spec_accept_multi(dl.to(DEV), tl.to(DEV), tok.to(DEV), u.to(DEV), temp, q_out=q_out, p_out=p_out)
+    n2, t2, ch2 = sq.sq_spec_accept_multi(dl.to(DEV), tl.to(DEV), tok.to(DEV), u.to(DEV), temp)
+    torch.cuda.synchronize()
+    assert torch.equal(n, n2) and torch.equal(t, t2) and torch.equal(ch, ch2)
+    n_o, t_o, ch_o = oracle.multi_accept_probs(p_out.cpu().numpy(), q_out.cpu().numpy(), tok.numpy(),
+                                               u.numpy().view(np.uint32))
+    assert np.array_equal(n.cpu().numpy(), n_o) and np.array_equal(t.cpu().numpy(), t_o)
+    assert np.array_equal(ch.cpu().numpy(), ch_o) and n_o[1] == 0
+
+
 def test_one_chain_equals_the_single_candidate_call():
     b, kd, v = 6, 5, 20000
     dl, tl, tok, u = make_case(b, 1, kd, v, seed=77)

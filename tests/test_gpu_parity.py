@@ -463,6 +463,25 @@ def test_spec_accept_greedy(b, kd, v):
     assert np.array_equal(n, n_ref) and np.array_equal(t, t_ref)
 
 
+@pytest.mark.parametrize("temp,kd,v", [(0.0, 0, 1), (0.0, 2, 4097), (1.0, 0, 1025)])
+def test_spec_accept_more_sequences_than_arrival_slots(temp, kd, v):
+    """Sequences past the slots of one launch (65536 rows or sequences) get what they get in a call of their own."""
+    b, tail = 65536 // (kd + 1) + 40, 60
+    g = torch.Generator(device=DEV).manual_seed(v)
+    target = torch.randn((b, kd + 1, v), generator=g, device=DEV)
+    draft = torch.randn((kd, b, v), generator=g, device=DEV) if kd else None
+    tok = target[:, :kd].argmax(-1).t().to(torch.int32).contiguous() if kd else None
+    if kd:
+        tok[1, ::3] = (tok[1, ::3] + 1) % v
+    u = torch.randint(0, 1 << 24, (b, kd + 1), generator=g, device=DEV, dtype=torch.int32)
+    n, t = sq.sq_spec_accept(draft, target, tok, u, temp)
+    n2, t2 = sq.sq_spec_accept(draft[:, -tail:].contiguous() if kd else None, target[-tail:].contiguous(),
+                               tok[:, -tail:].contiguous() if kd else None, u[-tail:].contiguous(), temp)
+    assert torch.equal(n[-tail:], n2) and torch.equal(t[-tail:], t2) and int(t.min()) >= 0
+    if temp == 0.0:
+        assert torch.equal(t, target[torch.arange(b, device=DEV), n.long()].argmax(-1).to(torch.int32))
+
+
 def test_spec_accept_edge_tokens_and_equal_distributions():
     b, kd, v = 6, 4, 333
     draft, target, tok, u24 = _accept_case(b, kd, v, 21, 1.0, "uniform")
