@@ -68,6 +68,12 @@ def load() -> ctypes.CDLL:
             "sq_verify_gemm_f16_acc": ([P, I64, I64, P, I64, P, P], S),
             "sq_spec_commit": ([P, P, P, I32, I32, P, P, P, P, I64, P, P, P], S),
             "sq_spec_accept_multi": ([P, P, P, P, I32, I32, I32, I32, F, P, P, P, P, P, P], S),
+            "sq_prefill_linear_f16": ([P, I64, I64, P, I64, P, S, P], S),
+            "sq_prefill_linear_w4": ([P, I64, I64, P, P, P, I64, P, S, P], S),
+            "sq_prefill_linear_w8": ([P, I64, I64, P, P, I64, P, S, P], S),
+            "sq_prefill_rope_kv_f16": ([P, P, I32, I32, I32, I32, P, I32, I64, I64, ctypes.c_double, P, P, P, P, P],
+                                       S),
+            "sq_prefill_attention_f16": ([P, P, P, I32, I32, I32, I32, P, I32, I64, I64, P, P], S),
             "sq_kv_adopt_f16": ([P, P, I32, I32, I32, I32, I64, P, P, P, I32, I32, P], S),
             "sq_spec_commit_multi": ([P, P, P, P, I32, I32, I32, P, P, P, P, I64, P, P, P], S),
         }
@@ -435,7 +441,8 @@ def _cache_dims(k_cache, v_cache):
 
 
 def sq_rope_kv_f16(qkv, bias, pos_base, pos_offset: int, rows_per_seq: int, hq: int, k_cache, v_cache,
-                   len_bound: int | None = None, theta: float = 1e6, q_out=None, status=None):
+                   len_bound: int | None = None, theta: float = 1e6, q_out=None, status=None,
+                   _entry="sq_rope_kv_f16"):
     """Bias + RoPE of the q|k|v rows, keys and values into the cache; returns q_out [m][hq][128] fp16."""
     b, hkv, cap = _cache_dims(k_cache, v_cache)
     m = b * rows_per_seq
@@ -449,14 +456,14 @@ def sq_rope_kv_f16(qkv, bias, pos_base, pos_offset: int, rows_per_seq: int, hq: 
         _expect(bias, torch.float16, (nh * HEAD_DIM,), "bias")
     _expect(pos_base, torch.int32, (b,), "pos_base")
     _expect(q_out, torch.float16, (m, hq, HEAD_DIM), "q_out")
-    _check(load().sq_rope_kv_f16(_ptr(qkv), _ptr(bias), b, rows_per_seq, hq, hkv, _ptr(pos_base), int(pos_offset),
-                                 int(len_bound), cap, float(theta), _ptr(q_out), _ptr(k_cache), _ptr(v_cache),
-                                 _ptr(status), _stream(qkv.device)), "sq_rope_kv_f16")
+    fn = getattr(load(), _entry)
+    _check(fn(_ptr(qkv), _ptr(bias), b, rows_per_seq, hq, hkv, _ptr(pos_base), int(pos_offset), int(len_bound), cap,
+              float(theta), _ptr(q_out), _ptr(k_cache), _ptr(v_cache), _ptr(status), _stream(qkv.device)), _entry)
     return q_out
 
 
 def sq_attention_f16(q, k_cache, v_cache, pos_base, pos_offset: int, rows_per_seq: int,
-                     len_bound: int | None = None, out=None):
+                     len_bound: int | None = None, out=None, _entry="sq_attention_f16"):
     """Causal GQA attention of the block rows over the cache; returns out [m][hq][128] fp16."""
     b, hkv, cap = _cache_dims(k_cache, v_cache)
     m, hq, hd = q.shape
@@ -470,9 +477,9 @@ def sq_attention_f16(q, k_cache, v_cache, pos_base, pos_offset: int, rows_per_se
     _expect(pos_base, torch.int32, (b,), "pos_base")
     if out.dtype != torch.float16 or out.numel() != m * hq * HEAD_DIM:
         raise ValueError("out must be float16 [m][hq][128]")
-    _check(load().sq_attention_f16(_ptr(q), _ptr(k_cache), _ptr(v_cache), b, rows_per_seq, hq, hkv, _ptr(pos_base),
-                                   int(pos_offset), int(len_bound), cap, _ptr(out), _stream(q.device)),
-           "sq_attention_f16")
+    fn = getattr(load(), _entry)
+    _check(fn(_ptr(q), _ptr(k_cache), _ptr(v_cache), b, rows_per_seq, hq, hkv, _ptr(pos_base), int(pos_offset),
+              int(len_bound), cap, _ptr(out), _stream(q.device)), _entry)
     return out
 
 
@@ -604,3 +611,63 @@ def sq_spec_commit_multi(n_accepted, next_token, chain, draft_tokens, c: int, pe
     _check(load().sq_spec_commit_multi(_ptr(n_accepted), _ptr(next_token), _ptr(chain), _ptr(draft_tokens), b, c, kd,
                                        _ptr(pending), _ptr(prev), _ptr(pos_base), _ptr(out_tokens), cap, _ptr(out_len),
                                        _ptr(status), _stream(n_accepted.device)), "sq_spec_commit_multi")
+
+
+# ------------------------------------------------------------------ prefill
+# (include/specquant_prefill.h: projections, rotation and attention of blocks of any number of rows)
+PREFILL_STORE, PREFILL_ADD, PREFILL_SILU = 0, 1, 2
+
+
+def _prefill_out(x, n, y, out):
+    m, k = x.shape
+    dtype, cols = (torch.float16, n // 2) if out == PREFILL_SILU else (torch.float32, n)
+    if x.dtype != torch.float16 or y.dtype != dtype or y.numel() != m * cols:
+        raise ValueError("x must be float16 [m][k]; y float32 [m][n], or float16 [m][n / 2] with PREFILL_SILU")
+    return m, k
+
+
+def sq_prefill_linear_f16(x, w16, y, out: int = PREFILL_STORE) -> bool:
+    """y = (or +=, or silu(gate) * up of) x . W16^T at any number of rows; False where no kernel takes the shape."""
+    n = w16.shape[0]
+    m, k = _prefill_out(x, n, y, out)
+    _dev(x, w16, y)
+    _expect(w16, torch.float16, (n, k), "w16")
+    return _fused(load().sq_prefill_linear_f16(_ptr(x), m, k, _ptr(w16), n, _ptr(y), out, _stream(x.device)),
+                  "sq_prefill_linear_f16")
+
+
+def sq_prefill_linear_w4(x, codes, scales, zeros, y, out: int = PREFILL_STORE) -> bool:
+    """The same with the INT4 g128 dequantized weights."""
+    n = codes.shape[0]
+    m, k = _prefill_out(x, n, y, out)
+    _dev(x, codes, scales, zeros, y)
+    _expect(codes, torch.uint8, (n, k // 2), "codes")
+    _expect(scales, torch.float16, (n, k // 128), "scales")
+    _expect(zeros, torch.float16, (n, k // 128), "zeros")
+    return _fused(load().sq_prefill_linear_w4(_ptr(x), m, k, _ptr(codes), _ptr(scales), _ptr(zeros), n, _ptr(y), out,
+                                              _stream(x.device)), "sq_prefill_linear_w4")
+
+
+def sq_prefill_linear_w8(x, codes, scales, y, out: int = PREFILL_STORE) -> bool:
+    """The same with the FP8 E4M3 dequantized weights."""
+    n = codes.shape[0]
+    m, k = _prefill_out(x, n, y, out)
+    _dev(x, codes, scales, y)
+    _expect(codes, torch.uint8, (n, k), "codes")
+    _expect(scales, torch.float32, (n,), "scales")
+    return _fused(load().sq_prefill_linear_w8(_ptr(x), m, k, _ptr(codes), _ptr(scales), n, _ptr(y), out,
+                                              _stream(x.device)), "sq_prefill_linear_w8")
+
+
+def sq_prefill_rope_kv_f16(qkv, bias, pos_base, pos_offset: int, rows_per_seq: int, hq: int, k_cache, v_cache,
+                           len_bound: int | None = None, theta: float = 1e6, q_out=None, status=None):
+    """sq_rope_kv_f16 for blocks of any number of rows (the same bits)."""
+    return sq_rope_kv_f16(qkv, bias, pos_base, pos_offset, rows_per_seq, hq, k_cache, v_cache, len_bound, theta, q_out,
+                          status, _entry="sq_prefill_rope_kv_f16")
+
+
+def sq_prefill_attention_f16(q, k_cache, v_cache, pos_base, pos_offset: int, rows_per_seq: int,
+                             len_bound: int | None = None, out=None):
+    """sq_attention_f16 for blocks of any number of rows."""
+    return sq_attention_f16(q, k_cache, v_cache, pos_base, pos_offset, rows_per_seq, len_bound, out,
+                            _entry="sq_prefill_attention_f16")

@@ -10,6 +10,8 @@
 //   attn_merge_kernel   merge of the slots in slot order
 //   attn_chunk_lds_kernel<true>  the chunk kernel that also does rope_kv_kernel's
 //                       work for its block (one launch less per layer)
+//   prefill_rope_kernel, prefill_attn_kernel  rope_kv_kernel's and the
+//                       attention's work for blocks of many rows (prompts)
 //   silu_mul_kernel     t = f16(g / (1 + exp(-g)) * u)
 //   commit_kernel       emitted tokens, next pending token, position
 //   kv_adopt_kernel, commit_multi_kernel  the same with several draft chains per sequence
@@ -783,6 +785,196 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const float* __restrict_
   o[1] = f32_to_f16_bits(a1 / l);
 }
 
+// ---------------------------------------------------------------- prefill
+// rope_kv_kernel for blocks of many rows (the same arithmetic, the same bits):
+// a workgroup takes 16 consecutive rows of a sequence and one of gridDim.z
+// shares of the heads.  The cosines and sines are formed once for all its
+// heads, and the values of 16 positions are written as one 32-byte run per
+// dimension where the positions allow it (2000 rows, 36 heads: 21 us; with
+// one share, too few workgroups to fill the chip, 63 us).
+constexpr int kRopeRows = 16;
+
+__global__ __launch_bounds__(256) void prefill_rope_kernel(const float* __restrict__ qkv,
+                                                           const uint16_t* __restrict__ bias, int hq, int hkv, int rps,
+                                                           const int32_t* __restrict__ pos_base, int pos_offset,
+                                                           int64_t len_bound, int64_t capacity, double theta,
+                                                           uint16_t* __restrict__ q_out, uint16_t* __restrict__ kc,
+                                                           uint16_t* __restrict__ vc, int32_t* __restrict__ status) {
+  __shared__ float2 tab[kRopeRows][64];
+  const int bi = blockIdx.y, j0 = blockIdx.x * kRopeRows;
+  const int nr = rps - j0 < kRopeRows ? rps - j0 : kRopeRows;
+  const int t = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t p0 = (int64_t)pos_base[bi] + pos_offset + j0;
+  const double freq = rope_freq(t, theta);
+  for (int r = wave; r < nr; r += 4) tab[r][t] = rope_cos_sin(p0 + r, freq);
+  __syncthreads();
+  const int nh = hq + 2 * hkv, share = blockIdx.z, shares = gridDim.z;
+  const int64_t row0 = (int64_t)bi * rps + j0;
+  if (share == 0 && threadIdx.x < nr && (p0 + (int)threadIdx.x < 0 || p0 + (int)threadIdx.x >= len_bound)) flag(status, kBadPos);
+  // queries and keys: a wavefront per (row, head), lane t the pair (t, t + 64)
+#pragma unroll 2
+  for (int i = wave + 4 * share; i < nr * (hq + hkv); i += 4 * shares) {
+    const int r = i / (hq + hkv), hh = i - r * (hq + hkv);
+    const float* src = qkv + ((row0 + r) * nh + hh) * kHd;
+    float a = src[t], e = src[t + 64];
+    const int64_t pos = p0 + r;
+    uint16_t* dst = hh < hq ? q_out + ((row0 + r) * hq + hh) * kHd
+                            : kc + (((int64_t)bi * hkv + (hh - hq)) * capacity + pos) * kHd;
+    if (pos < 0 || pos >= len_bound) {
+      if (hh < hq) {
+        dst[t] = kNanF16;
+        dst[t + 64] = kNanF16;
+      }
+      continue;
+    }
+    if (bias) {
+      a += f16_bits_to_f32(bias[hh * kHd + t]);
+      e += f16_bits_to_f32(bias[hh * kHd + t + 64]);
+    }
+    float ra, re;
+    rope_turn(a, e, tab[r][t], ra, re);
+    dst[t] = f32_to_f16_bits(ra);
+    dst[t + 64] = f32_to_f16_bits(re);
+  }
+  // values: a thread per (kv head, dimension), its 16 positions
+  const bool run = nr == kRopeRows && p0 >= 0 && p0 + kRopeRows <= len_bound && (p0 & 7) == 0;
+  for (int i = threadIdx.x + 256 * share; i < hkv * kHd; i += 256 * shares) {
+    const int g = i / kHd, dv = i - g * kHd;
+    const float* src = qkv + (row0 * nh + hq + hkv + g) * kHd + dv;
+    const float bv = bias ? f16_bits_to_f32(bias[(hq + hkv + g) * kHd + dv]) : 0.f;
+    uint16_t* vo = vc + (((int64_t)bi * hkv + g) * kHd + dv) * capacity + p0;
+    uint16_t v[kRopeRows];
+#pragma unroll
+    for (int r = 0; r < kRopeRows; ++r) {
+      const float s = src[(int64_t)(r < nr ? r : nr - 1) * nh * kHd];
+      v[r] = f32_to_f16_bits(bias ? s + bv : s);
+    }
+    if (run) {  // uniform across the workgroup
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        u32x4 c;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) c[x] = v[8 * h + 2 * x] | (uint32_t)v[8 * h + 2 * x + 1] << 16;
+        *reinterpret_cast<u32x4*>(vo + 8 * h) = c;
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < kRopeRows; ++r)
+        if (r < nr && p0 + r >= 0 && p0 + r < len_bound) vo[r] = v[r];
+    }
+  }
+}
+
+// Causal attention of a block of many rows: a workgroup takes 64 consecutive
+// rows of one sequence and query head, a tile of 16 per wavefront, and walks
+// all chunks up to its last row's position, staged through the two LDS
+// buffers of attn_chunk_lds_kernel (the same arithmetic per chunk).  Every row
+// is finished where it starts, so nothing is merged.  The longest workgroups
+// (the latest rows) are launched first.
+__global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))) void prefill_attn_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, int hq, int hkv,
+    int rps, int64_t capacity, const int32_t* __restrict__ pos_base, int pos_offset, int64_t len_bound,
+    uint16_t* __restrict__ out) {
+  extern __shared__ __align__(16) char smem[];
+  half_t* lbuf = reinterpret_cast<half_t*>(smem);  // [2][kLdsChunk]
+  const int hh = blockIdx.x, bi = blockIdx.z;
+  const int r0 = (int)(gridDim.y - 1 - blockIdx.y) * 64;  // the workgroup's first row
+  const int64_t bg = (int64_t)bi * hkv + hh / (hq / hkv);
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t p0 = (int64_t)pos_base[bi] + pos_offset;
+  const int rlast = r0 + 63 < rps - 1 ? r0 + 63 : rps - 1;
+  const int64_t pmax = p0 + rlast;
+  const int64_t klast = pmax < capacity - 1 ? pmax : capacity - 1;  // rows past the cache read none of it
+  const int nt = klast < 0 ? 0 : (int)(klast / kChunk) + 1;
+  const int qt = r0 / 16 + wave;  // this wavefront's tile: rows 16 qt .. 16 qt + 15
+  const AttnTile a{hq, rps, 1, rps};
+  const bool owner = 16 * qt < rps;
+  half8_t qf[4];
+  {
+    const int r = 16 * qt + li;
+    const half8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    const half8_t* qp =
+        reinterpret_cast<const half8_t*>(q + (((int64_t)bi * rps + (r < rps ? r : rps - 1)) * hq + hh) * kHd + 32 * lg);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qf[s] = r < rps ? qp[s] : zero8;
+  }
+  u32x4 pre[kLdsCells];
+  auto load_chunk = [&](int64_t key0) {
+#pragma unroll
+    for (int i = 0; i < kLdsCells; ++i) {
+      const int c = tid + kLdsThreads * i;
+      if (i < kLdsCells / 2) {
+        pre[i] = *reinterpret_cast<const u32x4*>(kc + (bg * capacity + key0 + (c >> 4)) * kHd + (c & 15) * 8);
+      } else {
+        const int c2 = c - kChunk * kHd / 8;
+        pre[i] = *reinterpret_cast<const u32x4*>(vc + (bg * kHd + (c2 >> 3)) * capacity + key0 + (c2 & 7) * 8);
+      }
+    }
+  };
+  auto store_chunk = [&](half_t* b) {
+#pragma unroll
+    for (int i = 0; i < kLdsCells; ++i) {
+      const int c = tid + kLdsThreads * i;
+      if (i < kLdsCells / 2) {
+        *reinterpret_cast<u32x4*>(b + (c >> 4) * kLdsKeyStride + (c & 15) * 8) = pre[i];
+      } else {
+        const int c2 = c - kChunk * kHd / 8;
+        *reinterpret_cast<u32x4*>(b + 64 * kLdsKeyStride + (c2 >> 3) * kLdsValStride + (c2 & 7) * 8) = pre[i];
+      }
+    }
+  };
+  float m = -__builtin_inff(), l = 0.f;
+  float4_t o[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) o[dt] = float4_t{0.f, 0.f, 0.f, 0.f};
+  if (nt > 0) {
+    load_chunk(0);
+    store_chunk(lbuf);
+  }
+  for (int t = 0; t < nt; ++t) {
+    const int64_t key0 = (int64_t)t * kChunk;
+    if (t + 1 < nt) load_chunk(key0 + kChunk);
+    // the LDS writes of buffer t % 2 are done; the next chunk's loads stay in flight
+    lds_barrier();
+    const half_t* b = lbuf + (t & 1) * kLdsChunk;
+    if (owner && key0 <= p0 + 16 * qt + 15) {  // uniform: the tile's last row reaches the chunk
+      const bool tail = key0 + kChunk - 1 > pmax;  // values of keys after pmax are zeroed (stale entries)
+      auto kfrag = [&](int kt, int s4) {
+        return *reinterpret_cast<const half8_t*>(b + (16 * kt + li) * kLdsKeyStride + 32 * lg + 8 * s4);
+      };
+      auto vfrag = [&](int t2, int dt) {
+        const int ka = 32 * t2 + 4 * lg, kb = ka + 16;
+        const half_t* vr = b + 64 * kLdsKeyStride + (16 * dt + li) * kLdsValStride;
+        const half4_t va = *reinterpret_cast<const half4_t*>(vr + ka);
+        const half4_t vb = *reinterpret_cast<const half4_t*>(vr + kb);
+        half8_t f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          f[e] = (!tail || key0 + ka + e <= pmax) ? va[e] : (half_t)0;
+          f[4 + e] = (!tail || key0 + kb + e <= pmax) ? vb[e] : (half_t)0;
+        }
+        return f;
+      };
+      attn_update_src(a, p0, qt, li, lg, qf, kfrag, vfrag, key0, m, l, o);
+    }
+    // buffer (t + 1) % 2 was last read before this chunk's barrier
+    if (t + 1 < nt) store_chunk(lbuf + ((t + 1) & 1) * kLdsChunk);
+  }
+  if (!owner) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 16 * qt + 4 * lg + i;
+    const float lr = __shfl(l, 4 * lg + i, kWave);  // row 4 lg + i's sum, held by lane 4 lg + i
+    if (r >= rps) continue;
+    const int64_t pos = p0 + r;
+    const bool bad = pos < 0 || pos >= len_bound;
+    uint16_t* dst = out + (((int64_t)bi * rps + r) * hq + hh) * kHd + li;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) dst[16 * dt] = bad ? kNanF16 : f32_to_f16_bits(o[dt][i] / lr);
+  }
+}
+
 // ------------------------------------------------------------- SiLU . up
 __global__ __launch_bounds__(256) void silu_mul_kernel(const float* __restrict__ gu, int64_t m, int64_t inter,
                                                        uint16_t* __restrict__ t) {
@@ -1003,6 +1195,31 @@ hipError_t launch_rope_attention(const float* qkv, const uint16_t* bias, int b, 
                      part_o, part_ml, rs);
   hipLaunchKernelGGL(attn_merge_kernel, dim3((unsigned)(b * rps), (unsigned)hq), dim3(64), 0, stream, part_o,
                      part_ml, hq, hkv, rps, nslots, span, nq_pad, pos_base, pos_offset, len_bound, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_prefill_rope_kv(const float* qkv, const uint16_t* bias, int b, int rps, int hq, int hkv,
+                                  const int32_t* pos_base, int pos_offset, int64_t len_bound, int64_t capacity,
+                                  double theta, uint16_t* q_out, uint16_t* kc, uint16_t* vc, int32_t* status,
+                                  hipStream_t stream) {
+  const int blocks = (rps + kRopeRows - 1) / kRopeRows;
+  // shares of the heads: about four workgroups per CU
+  int64_t shares = (int64_t)cu_count() * 4 / ((int64_t)blocks * b);
+  shares = shares < 1 ? 1 : (shares > 8 ? 8 : shares);
+  hipLaunchKernelGGL(prefill_rope_kernel, dim3((unsigned)blocks, (unsigned)b, (unsigned)shares), dim3(256), 0, stream, qkv, bias, hq, hkv, rps, pos_base, pos_offset, len_bound, capacity, theta, q_out, kc,
+                     vc, status);
+  return hipGetLastError();
+}
+
+hipError_t launch_prefill_attention(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int b, int rps, int hq,
+                                    int hkv, int64_t capacity, const int32_t* pos_base, int pos_offset,
+                                    int64_t len_bound, uint16_t* out, hipStream_t stream) {
+  // row blocks on grid.y (at most 65535 x 64 rows, more than a grid of three dimensions could index together)
+  const int blocks = (rps + 63) / 64;
+  if (blocks > 65535) return hipErrorInvalidValue;
+  const size_t lds = (size_t)2 * kLdsChunk * sizeof(uint16_t);
+  hipLaunchKernelGGL(prefill_attn_kernel, dim3((unsigned)hq, (unsigned)blocks, (unsigned)b), dim3(kLdsThreads), lds,
+                     stream, q, kc, vc, hq, hkv, rps, capacity, pos_base, pos_offset, len_bound, out);
   return hipGetLastError();
 }
 

@@ -1,0 +1,413 @@
+// Projections of a prompt's rows (prefill, the passes that fill the caches of
+// both models before SS III-D.2 starts): y = x . W'^T for hundreds to
+// thousands of activation rows, with the FP16 parent or the INT4 / FP8 draft
+// copy.  The streaming kernels take at most 64 rows, so a prompt of a thousand
+// tokens read every weight 32 times through them; here a weight tile meets
+// 128 or 256 rows and the matrix cores bound the time.
+//
+// A workgroup of 8 wavefronts (two per SIMD) forms a tile of BM rows x 256
+// outputs, each wavefront BM / 2 x 64 of it, in steps of 64 k staged in two
+// LDS buffers: a step's loads are issued before the previous step's products
+// and awaited after them.  Activations, and FP16 weights, go from memory to
+// LDS directly (16 bytes a lane); quantized weights pass through registers,
+// where they become halves exactly: INT4 q - z by the mantissa trick of the
+// streaming kernels, a byte permute setting a pair in k order; FP8 by
+// v_cvt_scalef32_pk_f16_fp8.  LDS rows are 128 bytes with their eight 16-byte
+// cells exchanged by the row number (cell ^ row % 8), so that the 16 rows of a
+// fragment read fall in different banks; a direct load applies the exchange
+// to its source address, as its LDS address cannot.
+//
+// Products: v_mfma_f32_16x16x32_f16 with the weights as the A operand, so that
+// a lane ends with four consecutive outputs of one row (one 16-byte store).
+// INT4: the products of a 128-k group (two steps) accumulate by themselves and
+// are added once, times the group's fp32 scale: exact products of q - z and x
+// and one rounding of each scaled group sum, as in the streaming kernels.
+// FP8: the row scale multiplies the total.
+//
+// Where the tiles do not fill the CUs, K is cut into S parts (blockIdx
+// beyond the tiles) whose fp32 partial tiles a second kernel adds in order.
+// BM and S are the pair with the least estimated time (choose()).
+// 2000 rows by the 37888 x 3584 gate|up matrix: FP16 0.87, FP8 1.0, INT4 0.62
+// PFLOP/s: the fragment reads keep LDS as busy as the matrix cores, and INT4
+// adds its conversions; placing these between the products instead of after
+// them delays the fragment reads behind their LDS writes (877 -> 944 us).
+// Prompts in 64-row blocks through the streaming kernels ran at 0.13.
+// Tiles go to the XCDs in contiguous runs, all row tiles of an output tile
+// next to each other, so that the workgroups of an XCD share weight and
+// activation panels in its L2.
+#include "sq_device.hpp"
+#include "sq_internal.hpp"
+
+namespace sq {
+namespace {
+
+enum : int { kW4 = 0, kW8 = 1, kF16 = 2 };
+constexpr int kThreads = 512;
+constexpr int kBN = 256;  // outputs per tile
+constexpr int kBK = 64;   // k per step
+constexpr int kRowBytes = kBK * 2;
+
+typedef __attribute__((address_space(1))) const uint32_t gword;
+typedef __attribute__((address_space(3))) uint32_t lword;
+
+// 16 bytes per lane from memory to LDS: lane l's go to dst + 16 l.
+__device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds((gword*)src, (lword*)dst, 16, 0, 0);
+}
+
+template <int KIND>
+constexpr int code_bytes_per_row_step() {
+  return KIND == kW4 ? kBK / 2 : (KIND == kW8 ? kBK : kBK * 2);
+}
+
+// Weight row of tile row r: consecutive outputs, or (SiLU) per wavefront 32
+// gate rows, then the 32 up rows of the same outputs.
+template <bool SILU>
+__device__ __forceinline__ int64_t weight_row(int64_t n0, int r, int64_t n) {
+  if constexpr (!SILU) {
+    const int64_t row = n0 + r;
+    return row < n ? row : n - 1;
+  } else {
+    const int64_t half = n >> 1;
+    const int64_t col = n0 + (r >> 6) * 32 + (r & 31);
+    return (col < half ? col : half - 1) + ((r >> 5) & 1 ? half : 0);
+  }
+}
+
+template <int KIND, int BM, bool SILU>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_gemm_kernel(
+    const uint16_t* __restrict__ x, int64_t m, int64_t k, const uint8_t* __restrict__ w,
+    const uint16_t* __restrict__ scales16, const uint16_t* __restrict__ zeros16, const float* __restrict__ scales32,
+    int64_t n, void* __restrict__ y, int out, float* __restrict__ partial, int mtiles, int ntiles, int part_steps) {
+  extern __shared__ __align__(16) char smem[];
+  constexpr int MT = BM / 32, NT = 4;         // 16-row tiles per wavefront
+  constexpr int kABytes = BM * kRowBytes, kBBytes = kBN * kRowBytes;
+  constexpr int kAIter = kABytes / 16 / kThreads, kBIter = kBBytes / 16 / kThreads;
+  char* abuf = smem;                          // [2][BM][128 bytes]
+  char* bbuf = smem + 2 * kABytes;            // [2][256][128 bytes]
+  float* sbuf = reinterpret_cast<float*>(smem + 2 * kABytes + 2 * kBBytes);  // INT4: [2][256] group scales
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+
+  // contiguous runs of tiles per XCD (workgroups go to the XCDs in turn)
+  const int total = gridDim.x, per = total >> 3, rem = total & 7;
+  const int xcd = blockIdx.x & 7;
+  const int tile = xcd * per + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
+  const int mi = tile % mtiles, nz = tile / mtiles, ni = nz % ntiles, part = nz / ntiles;
+  const int64_t m0 = (int64_t)mi * BM;
+  const int64_t n0 = (int64_t)ni * (SILU ? kBN / 2 : kBN);
+  const int steps_all = (int)(k / kBK);
+  const int s0 = part * part_steps;
+  const int s1 = s0 + part_steps < steps_all ? s0 + part_steps : steps_all;
+
+  // source offsets of this thread's direct cells: cell c = (8 i + wave) 64 + lane of the tile is row
+  // c / 8, LDS cell c % 8, memory cell (c % 8) ^ (row % 8)
+  uint32_t aoff[kAIter], boff[KIND == kF16 ? kBIter : 1];
+#pragma unroll
+  for (int i = 0; i < kAIter; ++i) {
+    const int c = (8 * i + wave) * 64 + lane, r = c >> 3;
+    const int64_t row = m0 + r < m ? m0 + r : m - 1;
+    aoff[i] = (uint32_t)((row - m0) * k * 2) + 16 * ((c & 7) ^ (r & 7));
+  }
+  if constexpr (KIND == kF16) {
+#pragma unroll
+    for (int i = 0; i < kBIter; ++i) {
+      const int c = (8 * i + wave) * 64 + lane, r = c >> 3;
+      boff[i] = (uint32_t)(weight_row<SILU>(n0, r, n) * k * 2) + 16 * ((c & 7) ^ (r & 7));
+    }
+  }
+  const char* xb = reinterpret_cast<const char*>(x + m0 * k);
+  // quantized: thread t holds 32 consecutive codes of tile row t / 2
+  const int qrow = tid >> 1, qhalf = tid & 1;
+  const int64_t wrow = weight_row<SILU>(n0, qrow, n);
+  const uint8_t* qsrc = w + wrow * (KIND == kW4 ? k >> 1 : k) + qhalf * (KIND == kW4 ? 16 : 32);
+  const int64_t grow = wrow * (k >> 7);
+  u32x4 qc[KIND == kW8 ? 2 : 1];
+  uint32_t qz = 0, qs = 0;
+
+  auto issue = [&](int s, int buf) {
+    const int64_t kb = (int64_t)s * kRowBytes;
+#pragma unroll
+    for (int i = 0; i < kAIter; ++i)
+      load_to_lds(xb + kb + aoff[i], abuf + buf * kABytes + (8 * i + wave) * 1024);
+    if constexpr (KIND == kF16) {
+#pragma unroll
+      for (int i = 0; i < kBIter; ++i)
+        load_to_lds(w + kb + boff[i], bbuf + buf * kBBytes + (8 * i + wave) * 1024);
+    } else if constexpr (KIND == kW8) {
+      const u32x4* p = reinterpret_cast<const u32x4*>(qsrc + (int64_t)s * kBK);
+      qc[0] = p[0];
+      qc[1] = p[1];
+    } else {
+      qc[0] = *reinterpret_cast<const u32x4*>(qsrc + (int64_t)s * (kBK / 2));
+      if ((s & 1) == 0) {  // a group's first step
+        qz = zeros16[grow + (s >> 1)];
+        qs = scales16[grow + (s >> 1)];
+      }
+    }
+  };
+  uint32_t mask = 0x00F0000Fu, magic = 0x54006400u;
+  if constexpr (KIND == kW4) asm("" : "+v"(mask), "+v"(magic));
+  // the registers' codes as halves into buffer buf
+  auto convert = [&](int s, int buf) {
+    if constexpr (KIND != kF16) {
+      char* row = bbuf + buf * kBBytes + qrow * kRowBytes;
+      half2_t cz;
+      auto code_pair = [&](uint32_t b) {
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, (b & mask) | magic) - cz);
+      };
+      if constexpr (KIND == kW4) {
+        cz = __builtin_bit_cast(half2_t, qz | (qz << 16)) + half2_t{(half_t)1024.0f, (half_t)64.0f};
+        if ((s & 1) == 0 && qhalf == 0) sbuf[((s >> 1) & 1) * kBN + qrow] = f16_bits_to_f32((uint16_t)qs);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {  // 8 codes each
+        u32x4 o;
+        if constexpr (KIND == kW4) {
+          // byte i of the word in both halves: code 2 i in bits 0-3 (1024 + q), code 2 i + 1 in bits 4-7 (64 + q)
+          const uint32_t qw = qc[0][j];
+          o[0] = code_pair(__builtin_amdgcn_perm(qw, qw, 0x00000000u));
+          o[1] = code_pair(__builtin_amdgcn_perm(qw, qw, 0x01010101u));
+          o[2] = code_pair(__builtin_amdgcn_perm(qw, qw, 0x02020202u));
+          o[3] = code_pair(__builtin_amdgcn_perm(qw, qw, 0x03030303u));
+        } else {
+          const uint32_t w0 = qc[j >> 1][2 * (j & 1)], w1 = qc[j >> 1][2 * (j & 1) + 1];
+          o[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, false));
+          o[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, true));
+          o[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, false));
+          o[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, true));
+        }
+        *reinterpret_cast<u32x4*>(row + 16 * ((qhalf * 4 + j) ^ (qrow & 7))) = o;
+      }
+    }
+  };
+
+  float4_t acc[MT][NT], grp[KIND == kW4 ? MT : 1][KIND == kW4 ? NT : 1];
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[a][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+  // fragment of 16 rows from row r0: lane l holds row r0 + l % 16, memory cells 4 kk + l / 16
+  const int fr = (lane & 15) * kRowBytes, fc0 = 16 * ((lane >> 4) ^ (lane & 7)), fc1 = 16 * ((4 + (lane >> 4)) ^ (lane & 7));
+  auto compute = [&](int s, int buf) {
+    const char* ab = abuf + buf * kABytes + wm * (BM / 2) * kRowBytes + fr;
+    const char* bb = bbuf + buf * kBBytes + wn * 64 * kRowBytes + fr;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const int fc = kk ? fc1 : fc0;
+      half8_t wf[NT], xf[MT];
+#pragma unroll
+      for (int b = 0; b < NT; ++b) wf[b] = *reinterpret_cast<const half8_t*>(bb + b * 16 * kRowBytes + fc);
+#pragma unroll
+      for (int a = 0; a < MT; ++a) xf[a] = *reinterpret_cast<const half8_t*>(ab + a * 16 * kRowBytes + fc);
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+          if constexpr (KIND == kW4) {
+            const float4_t c0 = (s & 1) == 0 && kk == 0 ? float4_t{0.f, 0.f, 0.f, 0.f} : grp[a][b];
+            grp[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[b], xf[a], c0, 0, 0, 0);
+          } else {
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[b], xf[a], acc[a][b], 0, 0, 0);
+          }
+        }
+    }
+    if constexpr (KIND == kW4) {
+      if (s & 1) {  // the group's last step (K slices start at whole groups)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+          const float4_t sc =
+              *reinterpret_cast<const float4_t*>(sbuf + ((s >> 1) & 1) * kBN + wn * 64 + b * 16 + 4 * (lane >> 4));
+#pragma unroll
+          for (int a = 0; a < MT; ++a) acc[a][b] += sc * grp[a][b];
+        }
+      }
+    }
+  };
+  auto sync = [&]() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+  };
+
+  issue(s0, 0);
+  convert(s0, 0);
+  sync();
+  auto step = [&](int s, int buf) {
+    if (s + 1 < s1) issue(s + 1, buf ^ 1);
+    compute(s, buf);
+    if (s + 1 < s1) convert(s + 1, buf ^ 1);
+    sync();
+  };
+  // (two steps a turn: the buffers and the halves of an INT4 group alternate; s0 is even for INT4)
+  for (int s = s0; s < s1; s += 2) {
+    step(s, 0);
+    if (s + 1 < s1) step(s + 1, 1);
+  }
+
+  // outputs: lane l holds outputs 4 (l / 16) .. +4 of a 16-output tile for row l % 16 of a row tile
+  const int q4 = 4 * (lane >> 4);
+  if constexpr (KIND == kW8) {
+#pragma unroll
+    for (int b = 0; b < NT; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float sc = scales32[weight_row<SILU>(n0, wn * 64 + b * 16 + q4 + r, n)];
+#pragma unroll
+        for (int a = 0; a < MT; ++a) acc[a][b][r] *= sc;
+      }
+  }
+  const bool vec = (n & 3) == 0;
+#pragma unroll
+  for (int a = 0; a < MT; ++a) {
+    const int64_t row = m0 + wm * (BM / 2) + a * 16 + (lane & 15);
+    if (row >= m) continue;
+    if (SILU && !partial) {
+      const int64_t half = n >> 1;
+      uint16_t* t = reinterpret_cast<uint16_t*>(y) + row * half;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int64_t col = n0 + wn * 32 + b * 16 + q4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (col + r < half) t[col + r] = silu_gate_bits(acc[a][b][r], acc[a][b + 2][r]);
+      }
+      continue;
+    }
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+      // (SiLU partials: rows [m][n] as without it, gates then ups)
+      const int64_t col = SILU ? n0 + wn * 32 + (b & 1) * 16 + q4 : n0 + wn * 64 + b * 16 + q4;
+      const int64_t end = SILU ? n >> 1 : n;
+      float* o = (partial ? partial + (int64_t)part * m * n : reinterpret_cast<float*>(y)) + row * n + col +
+                 (SILU && b >= 2 ? n >> 1 : 0);
+      const bool add = !partial && out == 1;
+      if (vec && (!SILU || (n & 7) == 0) && col + 3 < end) {
+        float4_t v = acc[a][b];
+        if (add) v = *reinterpret_cast<const float4_t*>(o) + v;
+        *reinterpret_cast<float4_t*>(o) = v;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (col + r < end) o[r] = (add ? o[r] : 0.f) + acc[a][b][r];
+      }
+    }
+  }
+}
+
+// The K parts' partial outputs in part order, then the output form: 0 y =, 1
+// y +=, 2 t = silu(gate) * up.
+__global__ __launch_bounds__(256) void prefill_reduce_kernel(const float* __restrict__ partial, int parts, int64_t m,
+                                                             int64_t n, void* __restrict__ y, int out) {
+  const int64_t mn = m * n, half = n >> 1, total = out == 2 ? m * half : mn;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
+    if (out == 2) {
+      const int64_t row = i / half, g = row * n + (i - row * half);
+      float a = 0.f, b = 0.f;
+      for (int s = 0; s < parts; ++s) {
+        a += partial[s * mn + g];
+        b += partial[s * mn + g + half];
+      }
+      reinterpret_cast<uint16_t*>(y)[i] = silu_gate_bits(a, b);
+    } else {
+      float v = 0.f;
+      for (int s = 0; s < parts; ++s) v += partial[s * mn + i];
+      float* o = reinterpret_cast<float*>(y) + i;
+      *o = out == 1 ? *o + v : v;
+    }
+  }
+}
+
+struct Plan {
+  int bm, parts, part_steps;
+};
+
+// The pair (rows per tile, K parts) of least estimated time: rounds of tiles
+// over the CUs, times steps, times a step's time (1.3 us at BM = 256, 0.8 us at
+// 128, from the measured rates with all CUs busy; INT4 has no registers for 256), plus
+// the partial outputs' way to memory and back.
+Plan choose(int64_t m, int64_t n, int64_t k, bool w4) {
+  const int64_t cus = cu_count(), nt = (n + kBN - 1) / kBN, steps = k / kBK;
+  Plan best{128, 1, (int)steps};
+  double tbest = 1e30;
+  for (int bm = 128; bm <= (w4 ? 128 : 256); bm += 128) {
+    const int64_t tiles = (m + bm - 1) / bm * nt;
+    const double tstep = bm == 256 ? 1.3 : 0.8;
+    for (int parts = 1; parts <= 16; ++parts) {
+      int64_t ps = (steps + parts - 1) / parts;
+      ps += ps & 1;  // whole INT4 groups
+      if (parts > 1 && (ps < 4 || (int64_t)(parts - 1) * ps >= steps)) break;
+      if (parts > 1 && (double)parts * m * n * 4 > 512e6) break;
+      double t = (double)((tiles * parts + cus - 1) / cus) * ((double)ps * tstep + 4.0);
+      if (parts > 1) t += 4.0 + (double)parts * m * n * 8 / 4e6;
+      if (t < tbest) {
+        tbest = t;
+        best = Plan{bm, parts, (int)ps};
+      }
+    }
+  }
+  return best;
+}
+
+template <int KIND>
+hipError_t prefill_launch(const uint16_t* x, int64_t m, int64_t k, const uint8_t* w, const uint16_t* scales16,
+                          const uint16_t* zeros16, const float* scales32, int64_t n, void* y, int out,
+                          hipStream_t stream) {
+  if (k % (KIND == kW4 ? 128 : kBK) != 0 || m < 1 || m > (int64_t(1) << 20)) return hipErrorNotSupported;
+  // 32-bit offsets inside a weight matrix and a row tile
+  if ((double)n * (double)k * 2 >= 4294967296.0 || (double)k * 2 * 256 >= 4294967296.0) return hipErrorNotSupported;
+  const Plan p = choose(m, n, k, KIND == kW4);
+  const int64_t mt = (m + p.bm - 1) / p.bm;
+  const int64_t nt = out == 2 ? (n / 2 + kBN / 2 - 1) / (kBN / 2) : (n + kBN - 1) / kBN;
+  const int64_t tiles = mt * nt * p.parts;
+  if (tiles > (int64_t(1) << 22)) return hipErrorNotSupported;  // a grid holds fewer than 2^32 threads
+  float* partial = nullptr;
+  if (p.parts > 1) {
+    void* ws = nullptr;
+    const hipError_t e = workspace((size_t)p.parts * m * n * sizeof(float), stream, &ws);
+    if (e != hipSuccess) return e;
+    partial = static_cast<float*>(ws);
+  }
+  auto go = [&](auto kernel, int bm) {
+    const size_t lds = (size_t)2 * (bm + kBN) * kRowBytes + (KIND == kW4 ? 2 * kBN * sizeof(float) : 0);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(kThreads), lds, stream, x, m, k, w, scales16, zeros16,
+                       scales32, n, y, out, partial, (int)mt, (int)nt, p.part_steps);
+  };
+  if constexpr (KIND == kW4) {
+    out == 2 ? go(prefill_gemm_kernel<KIND, 128, true>, 128) : go(prefill_gemm_kernel<KIND, 128, false>, 128);
+  } else {
+    if (p.bm == 256)
+      out == 2 ? go(prefill_gemm_kernel<KIND, 256, true>, 256) : go(prefill_gemm_kernel<KIND, 256, false>, 256);
+    else
+      out == 2 ? go(prefill_gemm_kernel<KIND, 128, true>, 128) : go(prefill_gemm_kernel<KIND, 128, false>, 128);
+  }
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess || p.parts == 1) return err;
+  const int64_t total = out == 2 ? m * (n / 2) : m * n;
+  int64_t blocks = (total + 255) / 256;
+  if (blocks > 8192) blocks = 8192;
+  hipLaunchKernelGGL(prefill_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, partial, p.parts, m, n, y,
+                     out);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefill_w4(const uint16_t* x, int64_t m, int64_t k, const uint8_t* codes, const uint16_t* scales,
+                             const uint16_t* zeros, int64_t n, void* y, int out, hipStream_t stream) {
+  return prefill_launch<kW4>(x, m, k, codes, scales, zeros, nullptr, n, y, out, stream);
+}
+
+hipError_t launch_prefill_w8(const uint16_t* x, int64_t m, int64_t k, const uint8_t* codes, const float* scales,
+                             int64_t n, void* y, int out, hipStream_t stream) {
+  return prefill_launch<kW8>(x, m, k, codes, nullptr, nullptr, scales, n, y, out, stream);
+}
+
+hipError_t launch_prefill_f16(const uint16_t* x, int64_t m, int64_t k, const uint16_t* w, int64_t n, void* y, int out,
+                              hipStream_t stream) {
+  return prefill_launch<kF16>(x, m, k, reinterpret_cast<const uint8_t*>(w), nullptr, nullptr, nullptr, n, y, out,
+                              stream);
+}
+
+}  // namespace sq

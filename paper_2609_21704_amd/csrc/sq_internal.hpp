@@ -70,6 +70,16 @@ hipError_t launch_linear_w8(const uint16_t* x, int m, int64_t k, const uint8_t* 
 hipError_t launch_linear_f16(const uint16_t* x, int m, int64_t k, const uint16_t* w, int64_t n, void* y,
                              bool f16_out, hipStream_t stream);
 
+// Projections of many rows (prefill.hip): out 0 y =, 1 y += (fp32), 2 t =
+// f16(silu(gate) * up); hipErrorNotSupported (nothing enqueued) for shapes
+// they do not take.
+hipError_t launch_prefill_f16(const uint16_t* x, int64_t m, int64_t k, const uint16_t* w, int64_t n, void* y, int out,
+                              hipStream_t stream);
+hipError_t launch_prefill_w4(const uint16_t* x, int64_t m, int64_t k, const uint8_t* codes, const uint16_t* scales,
+                             const uint16_t* zeros, int64_t n, void* y, int out, hipStream_t stream);
+hipError_t launch_prefill_w8(const uint16_t* x, int64_t m, int64_t k, const uint8_t* codes, const float* scales,
+                             int64_t n, void* y, int out, hipStream_t stream);
+
 // Sum of S split-K partials [S][mn] fp32 into y[mn] (fixed order s = 0..S-1).
 hipError_t launch_splitk_reduce(const float* partial, int splits, int64_t mn, void* y, bool f16_out,
                                 hipStream_t stream);
@@ -120,6 +130,15 @@ hipError_t launch_rope_attention(const float* qkv, const uint16_t* bias, int b, 
                                  int64_t capacity, const int32_t* pos_base, int pos_offset, int64_t len_bound,
                                  double theta, uint16_t* kc, uint16_t* vc, uint16_t* out, int32_t* status,
                                  hipStream_t stream);
+// Blocks of any number of rows per sequence (prefill): the rotation of
+// launch_rope_kv (the same bits), and causal attention over the cache.
+hipError_t launch_prefill_rope_kv(const float* qkv, const uint16_t* bias, int b, int rps, int hq, int hkv,
+                                  const int32_t* pos_base, int pos_offset, int64_t len_bound, int64_t capacity,
+                                  double theta, uint16_t* q_out, uint16_t* kc, uint16_t* vc, int32_t* status,
+                                  hipStream_t stream);
+hipError_t launch_prefill_attention(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int b, int rps, int hq,
+                                    int hkv, int64_t capacity, const int32_t* pos_base, int pos_offset,
+                                    int64_t len_bound, uint16_t* out, hipStream_t stream);
 hipError_t launch_silu_mul(const float* gu, int64_t m, int64_t inter, uint16_t* t, hipStream_t stream);
 hipError_t launch_spec_commit(const int32_t* n_accepted, const int32_t* next_token, const int32_t* drafts, int b,
                               int kd, int32_t* pending, int32_t* prev, int32_t* pos_base, int32_t* out_tokens,

@@ -41,6 +41,7 @@ from .rounds import Stack, round_uniforms  # noqa: F401  (round_uniforms: per-ro
 
 EPS = 1e-6
 THETA = 1e6
+PREFILL_ROWS = 4096  # rows of a prefill pass, at most (its activations: about 0.4 GB at the 7B sizes)
 # tensor ids for synth.stream_seed (distinct from those of rounds)
 _EMBED, _NORM_IN, _NORM_POST, _NORM_FINAL, _BIAS, _PROMPT = range(20, 26)
 
@@ -216,7 +217,7 @@ class SpecDecoder:
         """One pass of the block (first [R], rest [rps-1][R], R = batch x
         chains) at positions pos_base + offset + j through the draft (or
         parent) model, writing its cache entries; logits [R * (1 or rps)][V]
-        f32 out."""
+        f32 out, or None: only the cache entries are wanted."""
         cfg, w, b = self.cfg, self.w, self.buf
         M = self.R * rps
         if M > b.h.shape[0]:
@@ -228,6 +229,10 @@ class SpecDecoder:
         delta = None  # a projection output not yet added into h
         for l in range(w.layers):
             self._norm_linear(draft, (l, "qkv"), h, w.in_norm[l], delta, x, qkv)
+            if logits is None and l + 1 == w.layers and not self.attn_hook:  # nothing reads the last layer's output
+                sq.sq_rope_kv_f16(qkv, w.qkv_bias[l], self.pos_base, offset, rps, cfg.q_heads, cache.k[l],
+                                  cache.v[l], len_bound=lb, theta=THETA, q_out=q, status=self.status)
+                return
             if not (self.fuse and self.attn_hook is None and
                     sq.sq_rope_attention_f16(qkv, w.qkv_bias[l], self.pos_base, offset, rps, cfg.q_heads,
                                              cache.k[l], cache.v[l], a, len_bound=lb, theta=THETA,
@@ -245,9 +250,45 @@ class SpecDecoder:
                 self._norm_linear(draft, (l, "gate_up"), h, w.post_norm[l], delta, x, gu)
                 sq.sq_silu_mul_f16(gu, t)
             delta = self._residual_linear(draft, (l, "down"), t, h, y)
+        if logits is None:
+            return
         group = rps if last_only else 1
         xf = b.xf[:M // group]
         self._norm_linear(draft, (cfg.layers, "lm_head"), h, w.final_norm, delta, xf, logits, group=group)
+
+    def _prefill_pass(self, draft: bool, tokens, n: int, offset: int):
+        """One pass of tokens [R * n] (sequence-major) at positions offset + j that only fills the model's cache: no
+        logits, and of the last layer no more than its keys and values.  Any number of rows; False (nothing done)
+        where a projection's row length has no kernel for them."""
+        cfg, w = self.cfg, self.w
+        if not w.stack.prefill_takes(draft, w.layers):
+            return False
+        M, H, dev = self.R * n, cfg.hidden, self.device
+        cache = self.dcache if draft else self.pcache
+        lb = offset + n
+        f16, f32 = torch.float16, torch.float32
+        h, x = torch.empty((M, H), dtype=f32, device=dev), torch.empty((M, H), dtype=f16, device=dev)
+        qkv = torch.empty((M, cfg.q_dim + 2 * cfg.kv_dim), dtype=f32, device=dev)
+        q = torch.empty((M, cfg.q_heads, HEAD_DIM), dtype=f16, device=dev)
+        a, t = torch.empty_like(q), torch.empty((M, cfg.intermediate), dtype=f16, device=dev)
+        sq.sq_embed_block_f16(w.embed, tokens, h=h, status=self.status)
+        for l in range(w.layers):
+            sq.sq_add_rmsnorm_f16(h, w.in_norm[l], EPS, x=x)
+            w.stack.prefill_linear(draft, (l, "qkv"), x, qkv)
+            sq.sq_prefill_rope_kv_f16(qkv, w.qkv_bias[l], self.pos_base, offset, n, cfg.q_heads, cache.k[l],
+                                      cache.v[l], len_bound=lb, theta=THETA, q_out=q, status=self.status)
+            if l + 1 == w.layers and not self.attn_hook:
+                break
+            if self.attn_hook:
+                self.attn_hook(True, n, offset)
+            sq.sq_prefill_attention_f16(q, cache.k[l], cache.v[l], self.pos_base, offset, n, len_bound=lb, out=a)
+            if self.attn_hook:
+                self.attn_hook(False, n, offset)
+            w.stack.prefill_linear(draft, (l, "o"), a.view(M, cfg.q_dim), h, sq.PREFILL_ADD)
+            sq.sq_add_rmsnorm_f16(h, w.post_norm[l], EPS, x=x)
+            w.stack.prefill_linear(draft, (l, "gate_up"), x, t, sq.PREFILL_SILU)
+            w.stack.prefill_linear(draft, (l, "down"), t, h, sq.PREFILL_ADD)
+        return True
 
     def prefill(self, prompt: torch.Tensor, chunk: int | None = None, models=(True, False), lengths=None):
         """Feed prompt [B][Lp] (int32) but its last token to both models
@@ -277,15 +318,18 @@ class SpecDecoder:
         prompt = host.to(self.device)
         R = self.R
         self.pos_base.zero_()
-        V = self.cfg.vocab
         for draft in models:
-            c = max(1, min(chunk or 64, 64 // R))
-            for s in range(0, Lp - 1, c):
+            # blocks of up to PREFILL_ROWS rows; a block of up to 64 goes through the streaming projections
+            c = max(1, min(chunk or PREFILL_ROWS, PREFILL_ROWS // R))
+            s = 0
+            while s < Lp - 1:
                 n = min(c, Lp - 1 - s)
-                first = prompt[:, s].contiguous()
-                rest = prompt[:, s + 1:s + n].t().contiguous() if n > 1 else None
-                logits = torch.empty((R * n, V), dtype=torch.float32, device=self.device)
-                self.forward(draft, first, rest, n, s, logits, last_only=False, len_bound=s + n)
+                if R * n <= 64 or not self._prefill_pass(draft, prompt[:, s:s + n].reshape(-1), n, s):
+                    n = min(n, 64 // R)
+                    first = prompt[:, s].contiguous()
+                    rest = prompt[:, s + 1:s + n].t().contiguous() if n > 1 else None
+                    self.forward(draft, first, rest, n, s, None, last_only=False, len_bound=s + n)
+                s += n
         self.pos_base.copy_((lens - 1).to(torch.int32))
         self.pending.copy_(last)
         self.prev.copy_(before)

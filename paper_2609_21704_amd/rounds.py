@@ -79,6 +79,20 @@ class Stack:
     def verify_gemm(self, key, x, y):
         sq.sq_verify_gemm_f16(x, self.w16[key], y=y)
 
+    # Prompts: blocks of any number of rows (row lengths of whole 64- or 128-k steps).
+    def prefill_takes(self, draft: bool, layers: int) -> bool:
+        grain = 128 if draft and self.variant == "int4" else 64
+        return all(k % grain == 0 and n * k < 1 << 31 for l, name, n, k in self.mats if l < layers and name != "lm_head")
+
+    def prefill_linear(self, draft: bool, key, x, y, out: int = sq.PREFILL_STORE):
+        if not draft:
+            done = sq.sq_prefill_linear_f16(x, self.w16[key], y, out)
+        else:
+            fn = sq.sq_prefill_linear_w4 if self.variant == "int4" else sq.sq_prefill_linear_w8
+            done = fn(x, *self.draft[key], y, out)
+        if not done:
+            raise RuntimeError(f"no prefill kernel takes {tuple(x.shape)} by {key}")
+
     # The decoder's fused forms (False: the shape's kernel has none, nothing enqueued).
     def draft_gemv_rmsnorm(self, key, h, norm_w, eps, group, y) -> bool:
         if self.variant != "int4":
