@@ -15,13 +15,10 @@
 
 static_assert(sq::kNoAllocScratchBytes == SQ_NOALLOC_SCRATCH_BYTES, "one size for the static scratch array");
 
-// Large matrices stream through the matrix-core kernel; small ones (where
-// its fixed cost of staging activations and combining chunks, about 4 us more
-// than the others', dominates) and m > 16 use the vector-ALU GEMV and the
-// tile-per-workgroup GEMM, which measured faster there.  Thresholds in weight
-// bytes.
+// FP16 up to 8 rows: large matrices stream through linear_kernel, small ones
+// through tile_kernel; above 8 rows the launchers choose.  Thresholds in
+// weight bytes.
 constexpr int64_t kLinearMinBytesF16 = int64_t(28) << 20;  // between 3584^2 and 4608 x 3584 (7B o, q|k|v)
-constexpr int64_t kLinearMinBytesF16Wide = int64_t(4) << 20;  // m > 16: between 1152 x 896 and 896 x 4864
 constexpr int64_t kLinearMinBytesW8 = int64_t(64) << 20;
 constexpr int64_t kRowsMinBytesF16 = int64_t(4) << 20;  // 0.5B gate|up 896 x 4864 takes it, 896 x 896 not
 constexpr int64_t kRowsMaxRowsF16 = 32768;              // 14B gate|up 27648 x 5120 takes it, 7B 37888 x 3584 not
@@ -208,7 +205,7 @@ sq_status sq_qgemv_w4a16(const uint16_t* x, int64_t m, int64_t k, const uint8_t*
   const Range ins[] = {{x, (size_t)m * k * 2}, {codes, nk / 2}, {scales, nk / 64}, {zeros, nk / 64}};
   if (any_alias(outs, ins)) return SQ_ERR_ALIAS;
   (void)hipGetLastError();
-  // the GEMVs up to m = 8, the matrix-core kernel (activation tiles of 16 rows) beyond
+  // up to m = 8 the GEMVs' launcher (which takes what the matrix cores do faster to them), beyond the matrix cores
   if (m > 8)
     return device_status(sq::launch_linear_w4(x, (int)m, k, codes, scales, zeros, n, y, y_dtype == SQ_F16, stream));
   return device_status(sq::launch_gemv_w4(x, (int)m, k, codes, scales, zeros, n, y, y_dtype == SQ_F16, stream));
@@ -226,10 +223,9 @@ sq_status sq_qgemv_w8a16(const uint16_t* x, int64_t m, int64_t k, const uint8_t*
   const Range ins[] = {{x, (size_t)m * k * 2}, {codes, nk}, {scales, (size_t)n * 4}};
   if (any_alias(outs, ins)) return SQ_ERR_ALIAS;
   (void)hipGetLastError();
-  // the matrix-core kernel from its size on at m >= 3, where its chunk
-  // bookkeeping fits (it enqueues nothing when it returns hipErrorNotSupported);
-  // at m <= 2 the GEMVs stream faster at every size (measured)
-  // (above m = 8 only the matrix-core kernel)
+  // the streaming matrix-core kernel for large matrices at m >= 3 (at m <= 2 the
+  // GEMVs stream faster at every size, measured), the GEMVs' launcher for the
+  // others up to m = 8
   hipError_t e = hipErrorNotSupported;
   if (m > 8 || (m >= 3 && n * k >= kLinearMinBytesW8))
     e = sq::launch_linear_w8(x, (int)m, k, codes, scales, n, y, y_dtype == SQ_F16, stream);
@@ -251,14 +247,13 @@ sq_status sq_verify_gemm_f16(const uint16_t* x, int64_t m, int64_t k, const uint
   (void)hipGetLastError();
   // row blocks on the vector ALUs for m <= 8 from 4 MiB of weights up to
   // 32768 rows (their activations and row slots must fit in LDS), the
-  // matrix-core streaming kernel for larger matrices (m > 16: from 4 MiB),
-  // else the tiled GEMM
+  // matrix-core streaming kernel for larger matrices, else tile_kernel
   // (measured crossovers; each returns hipErrorNotSupported, enqueuing
   // nothing, for a shape it does not take)
   hipError_t e = hipErrorNotSupported;
   if (m <= 8 && n * k * 2 >= kRowsMinBytesF16 && n <= kRowsMaxRowsF16)
     e = sq::launch_gemm_rows_f16(x, (int)m, k, w16, n, y, y_dtype == SQ_F16, stream);
-  if (e == hipErrorNotSupported && n * k * 2 >= (m > 16 ? kLinearMinBytesF16Wide : kLinearMinBytesF16))
+  if (e == hipErrorNotSupported && (m > 8 || n * k * 2 >= kLinearMinBytesF16))
     e = sq::launch_linear_f16(x, (int)m, k, w16, n, y, y_dtype == SQ_F16, stream);
   if (e == hipErrorNotSupported) e = sq::launch_gemm_f16(x, (int)m, k, w16, n, y, y_dtype == SQ_F16, stream);
   return device_status(e);

@@ -1,88 +1,134 @@
-// Parent verification GEMM with the FP16 parent (SpecQuant SS III-D.3: the
-// parent Q16 = W16 checks all drafted positions of a block in one pass).
-// Two kernels here: gemm_rows_kernel (m <= 8, row blocks on the vector ALUs,
-// described at the kernel) and gemm_f16_kernel (the tiled matrix-core GEMM
-// below); the large matrices stream through linear_kernel (m <= 16 from
-// 28 MiB of weights, m = 17..64 from 4 MiB).
+// Projections of small matrices on the matrix cores, and the parent
+// verification of up to 8 rows on the vector ALUs.
 //
-// y[m][n] = sum_c x[m][c] * W[n][c] with m = b * (kd + 1) rows (5 to 36 at the
-// configurations of interest).  The weight stream dominates (2 bytes per
-// weight, read once); at m = 36 the contraction exceeds what the vector ALUs
-// can sustain at HBM speed, so it runs on the matrix cores:
-// v_mfma_f32_16x16x32_f16, with the m rows padded to 16-row tiles.
+// tile_kernel (INT4 and FP8 drafts, SpecQuant SS III-D.2; FP16 parent, SS
+// III-D.3):
+//   y[m][n] = sum_c x[m][c] * W'[n][c],  m <= 64 rows,
+// for matrices whose weights are not the cost: a few MB arrive within a
+// couple of memory round trips, so what counts is that all loads are under way
+// at once and that nothing is staged before the first product.  A workgroup
+// of NW wavefronts takes one 16-row tile at a time; they split its K into
+// interleaved 128-wide steps, hold U steps' weights and activations in
+// registers and fetch the next U while the matrix cores work.  The
+// activations come straight from L2 (16 MT rows a step): for large matrices
+// that outgrows the weights, and linear_kernel, which keeps them in LDS, takes
+// over.  The NW partial tiles are summed through LDS, a tree over the
+// wavefronts.
 //
 // Operand mapping (16x16x32, wave64): lane l holds A[l%16][8(l/16) .. +8) and
 // B[8(l/16) .. +8)[l%16]; the result lane l holds D[4(l/16) + r][l%16].  A is
-// the activation tile (rows m), B the weight tile (B[c][j] = W[n0 + j][c]).
-// A lane loads 64 contiguous bytes of one weight row per 128-wide k step, so
-// four lanes cover 256 contiguous bytes of a row; MFMA t (t = 0..3) consumes
-// the lane's k offsets 32(l/16) + 8t .. +8, and the A fragment is read with
-// the same k permutation, which leaves the sum unchanged.
+// the activation tile (rows m), B the weight tile (B[c][j] = W'[n0 + j][c]).
+// Product t (t = 0 .. 3) of a step takes its k in order, 32 t + 8(l/16) .. +8 per
+// lane, so that one load of activations (and of FP16 weights) covers 64
+// contiguous bytes of a row across its four lanes: with 32 consecutive k per
+// lane every 16-byte piece lay in a cache line segment of its own, and the L1
+// delivered a quarter of its rate (3584 x 3584 INT4, m = 64: 19.2 -> 18.0 us).
+// The codes of INT4 and FP8 steps are loaded 32 consecutive k per lane (16 or
+// 32 bytes) and exchanged between the four lanes of a row by permlane swaps.
+// The products of a step accumulate by themselves and are added
+// once, which keeps the roundings at the sum's full size few (an INT4 step is
+// one 128-element group, added times its scale).
 //
-// The grid is persistent: a workgroup walks 16-row tiles; its four wavefronts
-// split each tile's K into interleaved 128-wide steps and fetch the next
-// item's operands while the matrix cores work on the current one.  The four
-// partial tiles are summed through LDS in wavefront order.
+// gemm_rows_kernel: m <= 8, row blocks on the vector ALUs, described there.
 #include "sq_device.hpp"
 #include "sq_internal.hpp"
 
 namespace sq {
 namespace {
 
-constexpr int kThreads = 256;
+enum : int { kW4 = 0, kW8 = 1, kF16 = 2 };
 constexpr int kStep = 128;  // k elements per wavefront step
 
 __device__ __forceinline__ half8_t load_h8(const uint16_t* p) {
   return __builtin_bit_cast(half8_t, *reinterpret_cast<const u32x4*>(p));
 }
 
-template <int MT, int U>
+// w[i] of lane quarter q becomes the w[q] of quarter i.
+__device__ __forceinline__ void transpose_quarters(uint32_t (&w)[4]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto p = __builtin_amdgcn_permlane32_swap(w[i], w[i + 2], false, false);
+    const uint32_t p0 = p[0], p1 = p[1];  // scalar copies: vector element lvalues are misread
+    w[i] = p0;
+    w[i + 2] = p1;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    const auto p = __builtin_amdgcn_permlane16_swap(w[i], w[i + 1], false, false);
+    const uint32_t p0 = p[0], p1 = p[1];
+    w[i] = p0;
+    w[i + 1] = p1;
+  }
+}
+
+template <int KIND, int MT, int U>
 struct Item {
-  half8_t b[U][4];       // weight fragments
-  half8_t a[U][MT][4];   // activation fragments
+  u32x4 b[U][KIND == kW4 ? 1 : (KIND == kW8 ? 2 : 4)];  // the lane's 32 weights of each step
+  half8_t a[U][MT][4];                                  // activation fragments
+  uint32_t s[KIND == kW4 ? U : 1], z[KIND == kW4 ? U : 1];
 };
 
-// Operands of item j of a tile for this wavefront: steps (j U + u) * 4 + wave.
-template <int MT, int U>
-__device__ __forceinline__ void load_item(Item<MT, U>& it, const uint16_t* __restrict__ x, int m_rows, int64_t k,
-                                          const uint16_t* __restrict__ w, int64_t n, int64_t tile, int j, int wave,
-                                          int li, int lk) {
+// Operands of item j of a tile for this wavefront: steps (j U + u) * NW + wave.
+// Weights and activations past the row's end are zero.
+template <int KIND, int MT, int U, int NW>
+__device__ __forceinline__ void load_item(Item<KIND, MT, U>& it, const uint16_t* __restrict__ x, int m_rows, int64_t k,
+                                          const uint8_t* __restrict__ w, const uint16_t* __restrict__ scales16,
+                                          const uint16_t* __restrict__ zeros16, int64_t n, int64_t tile, int j,
+                                          int wave, int li, int lk) {
+  constexpr int NL = KIND == kW4 ? 1 : (KIND == kW8 ? 2 : 4), KL = 32 / NL;  // loads, k per load
   const int64_t row = (tile * 16 + li) < n ? (tile * 16 + li) : (n - 1);
-  const uint16_t* wrow = w + row * k;
+  const uint8_t* wrow = w + row * (KIND == kW4 ? k >> 1 : (KIND == kW8 ? k : 2 * k));
   const half8_t zero8 = {};
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int64_t step = ((int64_t)j * U + u) * 4 + wave;
+    const int64_t step = ((int64_t)j * U + u) * NW + wave;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int64_t kidx = step * kStep + (KIND == kF16 ? 32 * i + 8 * lk : 32 * lk + KL * i);
+      it.b[u][i] = kidx < k ? *reinterpret_cast<const u32x4*>(wrow + (KIND == kW4 ? kidx >> 1 : (KIND == kW8 ? kidx : 2 * kidx)))
+                            : u32x4{0u, 0u, 0u, 0u};
+    }
+    if constexpr (KIND == kW4) {
+      const int64_t groups = k >> 7, gi = row * groups + (step < groups ? step : groups - 1);
+      it.s[u] = scales16[gi];
+      it.z[u] = zeros16[gi];
+    }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int64_t kidx = step * kStep + 32 * lk + 8 * t;
-      const bool ok = kidx < k;
-      it.b[u][t] = ok ? load_h8(wrow + kidx) : zero8;
+      const int64_t kidx = step * kStep + 32 * t + 8 * lk;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int mr = mt * 16 + li;
-        it.a[u][mt][t] = (ok && mr < m_rows) ? load_h8(x + (int64_t)mr * k + kidx) : zero8;
+        it.a[u][mt][t] = (kidx < k && mr < m_rows) ? load_h8(x + (int64_t)mr * k + kidx) : zero8;
       }
     }
   }
 }
 
-template <int MT, int U, bool F16Out>
-__global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const uint16_t* __restrict__ x, int m_rows, int64_t k,
-                                                            const uint16_t* __restrict__ w, int64_t n,
-                                                            void* __restrict__ y) {
-  __shared__ float red[4][MT * 256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int KIND, int MT, int U, int NW>
+__global__ __launch_bounds__(NW * 64) void tile_kernel(const uint16_t* __restrict__ x, int m_rows, int64_t k,
+                                                       const uint8_t* __restrict__ w,
+                                                       const uint16_t* __restrict__ scales16,
+                                                       const uint16_t* __restrict__ zeros16,
+                                                       const float* __restrict__ scales32, int64_t n,
+                                                       void* __restrict__ y, int out_mode) {
+  __shared__ float red[NW][MT * 256];
+  constexpr int nthr = NW * 64;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, lk = lane >> 4;
   const int64_t ntile = (n + 15) / 16;
   const int64_t nsteps = (k + kStep - 1) / kStep;
-  const int nitem = (int)((nsteps + 4 * U - 1) / (4 * U));  // the same for every wavefront
+  const int nitem = (int)((nsteps + NW * U - 1) / (NW * U));  // the same for every wavefront
   int64_t tile = blockIdx.x;
   int j = 0;
   if (tile >= ntile) return;  // uniform across the workgroup
 
-  Item<MT, U> cur;
-  load_item<MT, U>(cur, x, m_rows, k, w, n, tile, 0, wave, li, lk);
+  uint32_t mask = 0x00F0000Fu, magic = 0x54006400u;
+  if constexpr (KIND == kW4) asm("" : "+v"(mask), "+v"(magic));
+
+  Item<KIND, MT, U> cur;
+  load_item<KIND, MT, U, NW>(cur, x, m_rows, k, w, scales16, zeros16, n, tile, 0, wave, li, lk);
   float4_t acc[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -94,16 +140,69 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const uint16_t* __re
       j_n = 0;
       tile_n = tile + gridDim.x;
     }
-    Item<MT, U> nxt;
-    if (tile_n < ntile) load_item<MT, U>(nxt, x, m_rows, k, w, n, tile_n, j_n, wave, li, lk);
+    Item<KIND, MT, U> nxt;
+    if (tile_n < ntile)
+      load_item<KIND, MT, U, NW>(nxt, x, m_rows, k, w, scales16, zeros16, n, tile_n, j_n, wave, li, lk);
 
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      float4_t grp[MT], grp2[KIND == kW4 ? 1 : MT];
+      uint32_t qa[4], qb[4];  // the codes of product t: qa[t] (and qb[t])
+      if constexpr (KIND != kF16) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < 4; ++t) {
+          qa[t] = KIND == kW4 ? cur.b[u][0][t] : cur.b[u][KIND == kW8 ? t >> 1 : 0][2 * (t & 1)];
+          qb[t] = KIND == kW4 ? 0u : cur.b[u][KIND == kW8 ? t >> 1 : 0][2 * (t & 1) + 1];
+        }
+        transpose_quarters(qa);
+        if constexpr (KIND == kW8) transpose_quarters(qb);
+      }
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cur.a[u][mt][t], cur.b[u][t], acc[mt], 0, 0, 0);
+      for (int t = 0; t < 4; ++t) {
+        half8_t bw;
+        if constexpr (KIND == kW4) {
+          // byte b of the word in both halves: code 2 b in bits 0-3 (1024 + q), code 2 b + 1 in bits 4-7 (64 + q)
+          const uint32_t qw = qa[t], zz = cur.z[u];
+          const half2_t cz = __builtin_bit_cast(half2_t, zz | (zz << 16)) + half2_t{(half_t)1024.0f, (half_t)64.0f};
+          const half2_t d0 =
+              __builtin_bit_cast(half2_t, (__builtin_amdgcn_perm(qw, qw, 0x00000000u) & mask) | magic) - cz;
+          const half2_t d1 =
+              __builtin_bit_cast(half2_t, (__builtin_amdgcn_perm(qw, qw, 0x01010101u) & mask) | magic) - cz;
+          const half2_t d2 =
+              __builtin_bit_cast(half2_t, (__builtin_amdgcn_perm(qw, qw, 0x02020202u) & mask) | magic) - cz;
+          const half2_t d3 =
+              __builtin_bit_cast(half2_t, (__builtin_amdgcn_perm(qw, qw, 0x03030303u) & mask) | magic) - cz;
+          bw = half8_t{d0[0], d0[1], d1[0], d1[1], d2[0], d2[1], d3[0], d3[1]};
+        } else if constexpr (KIND == kW8) {
+          const uint32_t w0 = qa[t], w1 = qb[t];
+          const half2_t h0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, false);
+          const half2_t h1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, true);
+          const half2_t h2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, false);
+          const half2_t h3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, true);
+          bw = half8_t{h0[0], h0[1], h1[0], h1[1], h2[0], h2[1], h3[0], h3[1]};
+        } else {
+          const u32x4 raw = cur.b[u][t];
+          bw = __builtin_bit_cast(half8_t, raw);
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          if (KIND == kW4 || t < 2)
+            grp[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cur.a[u][mt][t], bw,
+                                                             t == 0 ? float4_t{0.f, 0.f, 0.f, 0.f} : grp[mt], 0, 0, 0);
+          else
+            grp2[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                cur.a[u][mt][t], bw, t == 2 ? float4_t{0.f, 0.f, 0.f, 0.f} : grp2[mt], 0, 0, 0);
+        }
+      }
+      if constexpr (KIND == kW4) {  // (a step past the row's end adds its scale times zero activations)
+        const float s = f16_bits_to_f32((uint16_t)cur.s[u]);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt] += s * grp[mt];
+      } else {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt] += grp[mt] + grp2[mt];
+      }
+    }
 
     if (j == nitem - 1) {
 #pragma unroll
@@ -114,12 +213,28 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const uint16_t* __re
       }
       __syncthreads();
       const int64_t n0 = tile * 16;
-      for (int idx = threadIdx.x; idx < MT * 256; idx += kThreads) {
-        const float v = ((red[0][idx] + red[1][idx]) + red[2][idx]) + red[3][idx];
+      for (int idx = threadIdx.x; idx < MT * 256; idx += nthr) {
+        float p[NW];  // a tree over the wavefronts
+#pragma unroll
+        for (int q = 0; q < NW; ++q) p[q] = red[q][idx];
+#pragma unroll
+        for (int h = 1; h < NW; h *= 2)
+#pragma unroll
+          for (int q = 0; q + h < NW; q += 2 * h) p[q] += p[q + h];
+        float v = p[0];
         const int mt = idx >> 8, r = (idx >> 6) & 3, l = idx & 63;
         const int mr = mt * 16 + 4 * (l >> 4) + r;
         const int64_t col = n0 + (l & 15);
-        if (mr < m_rows && col < n) store_out<F16Out>(y, (int64_t)mr * n + col, v);
+        if (mr < m_rows && col < n) {
+          if constexpr (KIND == kW8) v *= scales32[col];
+          const int64_t o = (int64_t)mr * n + col;
+          if (out_mode == kOutF16)
+            reinterpret_cast<uint16_t*>(y)[o] = f32_to_f16_bits(v);
+          else if (out_mode == kOutAcc)
+            reinterpret_cast<float*>(y)[o] += v;
+          else
+            reinterpret_cast<float*>(y)[o] = v;
+        }
       }
       __syncthreads();
     }
@@ -130,17 +245,31 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const uint16_t* __re
   }
 }
 
-template <int MT, int U>
-hipError_t gemm_mt(const uint16_t* x, int m, int64_t k, const uint16_t* w, int64_t n, void* y, bool f16_out,
+template <int KIND, int MT, int U, int NW>
+hipError_t tile_go(const uint16_t* x, int m, int64_t k, const uint8_t* w, const uint16_t* scales16,
+                   const uint16_t* zeros16, const float* scales32, int64_t n, void* y, int out_mode,
                    hipStream_t stream) {
-  const int64_t ntile = (n + 15) / 16;
-  const int64_t cap = (int64_t)cu_count() * 4;
-  const dim3 grid((unsigned)(ntile < cap ? ntile : cap));
-  if (f16_out)
-    hipLaunchKernelGGL((gemm_f16_kernel<MT, U, true>), grid, dim3(kThreads), 0, stream, x, m, k, w, n, y);
-  else
-    hipLaunchKernelGGL((gemm_f16_kernel<MT, U, false>), grid, dim3(kThreads), 0, stream, x, m, k, w, n, y);
+  const int64_t ntile = (n + 15) / 16, cap = (int64_t)cu_count() * 4;
+  hipLaunchKernelGGL((tile_kernel<KIND, MT, U, NW>), dim3((unsigned)(ntile < cap ? ntile : cap)), dim3(64 * NW), 0,
+                     stream, x, m, k, w, scales16, zeros16, scales32, n, y, out_mode);
   return hipGetLastError();
+}
+
+// Eight wavefronts a tile; four where three or more row tiles meet more output
+// tiles than CUs (9728 x 896 INT4, m = 48: 13.1 -> 10.8 us).  Two steps held at
+// a time for up to 8 rows and one tile per CU, else one (3584 x 3584 INT4,
+// two / one: m = 4 5.7 / 6.1 us, m = 16 7.4 / 7.0).
+template <int KIND>
+hipError_t tile_dispatch(const uint16_t* x, int m, int64_t k, const uint8_t* w, const uint16_t* scales16,
+                         const uint16_t* zeros16, const float* scales32, int64_t n, void* y, int out_mode,
+                         hipStream_t stream) {
+  const bool one_round = (n + 15) / 16 <= cu_count();
+  auto go = [&](auto f) { return f(x, m, k, w, scales16, zeros16, scales32, n, y, out_mode, stream); };
+  if (m <= 16) return m <= 8 && one_round ? go(tile_go<KIND, 1, 2, 8>) : go(tile_go<KIND, 1, 1, 8>);
+  if (m <= 32) return go(tile_go<KIND, 2, 1, 8>);
+  if (m <= 48) return one_round ? go(tile_go<KIND, 3, 1, 8>) : go(tile_go<KIND, 3, 1, 4>);
+  if (m <= 64) return one_round ? go(tile_go<KIND, 4, 1, 8>) : go(tile_go<KIND, 4, 1, 4>);
+  return hipErrorInvalidValue;
 }
 
 // Verification over row blocks for small m (m <= 8): at 5 flops per weight
@@ -161,8 +290,7 @@ hipError_t gemm_mt(const uint16_t* x, int m, int64_t k, const uint16_t* w, int64
 // in a 64-bit slot by atomic exchange (the value travels inside the atomic, so
 // no fence is needed): the second to arrive adds slice 0's + slice 1's in that
 // order, stores the result and empties the slot for the next launch.
-// Output modes: y fp32, y fp16, or y fp32 added to.
-enum : int { kOutF32 = 0, kOutF16 = 1, kOutAcc = 2 };
+// Output modes as above.
 
 template <int M, int NA, int NWV, int XB, int D, int KS, bool NRM>
 __global__ __launch_bounds__(1024) void gemm_rows_kernel(const uint16_t* __restrict__ x, int64_t k,
@@ -551,11 +679,18 @@ hipError_t launch_gemm_rows_f16(const uint16_t* x, int m, int64_t k, const uint1
 
 hipError_t launch_gemm_f16(const uint16_t* x, int m, int64_t k, const uint16_t* w, int64_t n, void* y, bool f16_out,
                            hipStream_t stream) {
-  if (m <= 16) return gemm_mt<1, 2>(x, m, k, w, n, y, f16_out, stream);
-  if (m <= 32) return gemm_mt<2, 1>(x, m, k, w, n, y, f16_out, stream);
-  if (m <= 48) return gemm_mt<3, 1>(x, m, k, w, n, y, f16_out, stream);
-  if (m <= 64) return gemm_mt<4, 1>(x, m, k, w, n, y, f16_out, stream);
-  return hipErrorInvalidValue;
+  return tile_dispatch<kF16>(x, m, k, reinterpret_cast<const uint8_t*>(w), nullptr, nullptr, nullptr, n, y,
+                             f16_out ? kOutF16 : kOutF32, stream);
+}
+
+hipError_t launch_tile_w4(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const uint16_t* scales,
+                          const uint16_t* zeros, int64_t n, void* y, int out_mode, hipStream_t stream) {
+  return tile_dispatch<kW4>(x, m, k, codes, scales, zeros, nullptr, n, y, out_mode, stream);
+}
+
+hipError_t launch_tile_w8(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const float* scales, int64_t n,
+                          void* y, int out_mode, hipStream_t stream) {
+  return tile_dispatch<kW8>(x, m, k, codes, nullptr, nullptr, scales, n, y, out_mode, stream);
 }
 
 }  // namespace sq

@@ -1,6 +1,7 @@
 // Dequant-fused draft GEMVs (SpecQuant SS III-D.2: the draft parent Q4 or Q8
 // produces the speculative tokens; every draft step streams the whole
-// quantized stack once at m = 1 .. 8 activation rows).
+// quantized stack once at m = 1 .. 4 activation rows; from three rows on the
+// launchers below take most shapes to the matrix-core kernels instead).
 //
 // The kernels are HBM-bound: each weight byte is read once, with 16-byte
 // loads, 32 contiguous bytes per lane per row.  Two work splits, chosen per
@@ -236,10 +237,6 @@ struct XStage {
     }
   }
 };
-
-// Output modes of the projection kernels: y fp32, y fp16, y fp32 added to, or
-// (SILU, tasks of a gate and an up row) t = f16(silu(gate) * up) [m][n / 2].
-enum : int { kOutF32 = 0, kOutF16 = 1, kOutAcc = 2, kOutSilu = 3 };
 
 __device__ __forceinline__ void store_mode(void* y, int64_t idx, float v, int out_mode) {
   if (out_mode == kOutF16)
@@ -1101,10 +1098,6 @@ hipError_t gemv_dispatch(const uint16_t* x, int m, int64_t k, const uint8_t* cod
     case 2: return gemv_m<2, W8>(x, k, codes, scales16, zeros16, scales32, n, y, out_mode, nrm, stream);
     case 3: return gemv_m<3, W8>(x, k, codes, scales16, zeros16, scales32, n, y, out_mode, nrm, stream);
     case 4: return gemv_m<4, W8>(x, k, codes, scales16, zeros16, scales32, n, y, out_mode, nrm, stream);
-    case 5: return gemv_m<5, W8>(x, k, codes, scales16, zeros16, scales32, n, y, out_mode, nrm, stream);
-    case 6: return gemv_m<6, W8>(x, k, codes, scales16, zeros16, scales32, n, y, out_mode, nrm, stream);
-    case 7: return gemv_m<7, W8>(x, k, codes, scales16, zeros16, scales32, n, y, out_mode, nrm, stream);
-    case 8: return gemv_m<8, W8>(x, k, codes, scales16, zeros16, scales32, n, y, out_mode, nrm, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1124,17 +1117,43 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int64_t mn, vo
   return hipGetLastError();
 }
 
+// From three rows on the matrix cores beat the vector ALUs wherever the
+// weights or the rows suffice: always from five rows; at three and four, small
+// matrices (tile_takes) and, through linear_kernel, large ones.  Measured at
+// m = 3 / 4, GEMV against linear_kernel (us): INT4 9728 x 896 9.7 / 10.4 : 7.4,
+// 17920 x 1536 13.2 / 13.9 : 9.9, 151936 x 3584 82 / 97 : 62 (at m = 8 200 : 64),
+// 1536 x 8960 9.3 / 12.3 : 10.3 / 11.2, 4608 x 3584 7.4 / 8.4 : 8.4, 7168 x 5120 12.2 /
+// 15.3 : 11.6.  Accumulated outputs follow the plain projection (the same
+// bits), where the GEMV took them: activations in one K slice.
 hipError_t launch_gemv_w4(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const uint16_t* scales,
                           const uint16_t* zeros, int64_t n, void* y, bool f16_out, hipStream_t stream,
                           const NormSrc* nrm, bool accum, bool silu) {
   const int mode = silu ? kOutSilu : (accum ? kOutAcc : (f16_out ? kOutF16 : kOutF32));
+  if (m >= 3) {
+    if (nrm || silu) return hipErrorNotSupported;
+    if (accum && k > (int64_t)(kLdsBudget / ((size_t)m * 2)) / 128 * 128) return hipErrorNotSupported;
+    if (tile_takes(n, k) || tile_takes_long(n, k, m, 6, 32))
+      return launch_tile_w4(x, m, k, codes, scales, zeros, n, y, mode, stream);
+    const double work = (double)m * (double)n * (double)k;
+    if (m >= 5 || work >= (n >= 8192 ? 24e6 : (k >= 8192 ? 50e6 : 70e6)))
+      return launch_linear_w4_mode(x, m, k, codes, scales, zeros, n, y, mode, stream);
+  }
   return gemv_dispatch<false>(x, m, k, codes, scales, zeros, nullptr, n, y, mode, nrm, stream);
 }
 
+// FP8: the GEMV keeps three and four rows of mid-sized matrices (m = 4, GEMV
+// against linear_kernel: 4608 x 3584 8.7 : 9.2 us, 1536 x 8960 8.6 : 12.9, 17920 x
+// 1536 12.9 : 11.3; m = 5 11.3 : 9.5, 12.9 : 13.3, 13.7 : 11.5), and tile_kernel short
+// rows up to 16 activation rows (17920 x 1536, m = 8: 11.0 : 11.6).
 hipError_t launch_gemv_w8(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const float* scales, int64_t n,
                           void* y, bool f16_out, hipStream_t stream) {
-  return gemv_dispatch<true>(x, m, k, codes, nullptr, nullptr, scales, n, y, f16_out ? kOutF16 : kOutF32, nullptr,
-                             stream);
+  const int mode = f16_out ? kOutF16 : kOutF32;
+  if (m >= 3) {
+    if (tile_takes_w8(n, k, m)) return launch_tile_w8(x, m, k, codes, scales, n, y, mode, stream);
+    if (m >= 5 || (m == 4 && n >= 8192 && (double)n * (double)k >= 7.5e6))
+      return launch_linear_w8_mode(x, m, k, codes, scales, n, y, mode, stream);
+  }
+  return gemv_dispatch<true>(x, m, k, codes, nullptr, nullptr, scales, n, y, mode, nullptr, stream);
 }
 
 }  // namespace sq

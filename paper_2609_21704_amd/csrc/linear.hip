@@ -221,11 +221,16 @@ __device__ __forceinline__ half8_t as_h8(u32x4 v) { return __builtin_bit_cast(ha
 
 // (several activation tiles hold more registers; a CU runs one workgroup of 8
 // wavefronts, two per SIMD)
+// Workgroup meeting slots of one-slice launches at few rows (256 workgroups, m <= 8), empty between launches:
+// such calls need no workspace, also as a first call inside a stream capture.
+constexpr size_t kMeetSlots = 256 * 8 * 16;
+static __device__ unsigned long long meet_slots[kMeetSlots];
+
 template <int KIND, int NW, int MT>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : 2)))
 void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t kslice, const uint8_t* __restrict__ w,
                    const uint16_t* __restrict__ scales16, const uint16_t* __restrict__ zeros16,
-                   const float* __restrict__ scales32, int64_t n, void* __restrict__ y, int f16_out,
+                   const float* __restrict__ scales32, int64_t n, void* __restrict__ y, int out_mode,
                    float* __restrict__ split_out, int64_t nwg_max, int chunk_units, unsigned long long* xchg,
                    unsigned long long* slice_xchg, int direct) {
   extern __shared__ __align__(16) char smem[];
@@ -296,8 +301,10 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
     if constexpr (KIND == kW8) val *= scales32[row];
     if (split_out)
       split_out[((int64_t)split * M + m) * n + row] = val;
-    else if (f16_out)
+    else if (out_mode == kOutF16)
       reinterpret_cast<uint16_t*>(y)[(int64_t)m * n + row] = f32_to_f16_bits(val);
+    else if (out_mode == kOutAcc)
+      reinterpret_cast<float*>(y)[(int64_t)m * n + row] += val;
     else
       reinterpret_cast<float*>(y)[(int64_t)m * n + row] = val;
   };
@@ -307,9 +314,15 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
     int arow[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) arow[mt] = mt * 16 + col < M ? mt * 16 + col : 0;
-    float4_t acc[MT];
+    // two running sums, added at the chunk's end (FP8: of 128 k at a time): fewer roundings at the
+    // sum's full size (3584 k, relative to 64 bits, before / after: FP8 1.63e-7 / 0.82e-7,
+    // FP16 1.55e-7 / 1.20e-7, INT4 0.78e-7 / 0.68e-7)
+    // (from three row tiles on the registers are worth more: 37888 x 3584 INT4 at m = 36
+    // 40.6 us, with two sums 41.4; four tiles would spill)
+    constexpr bool kTwo = MT < 3;
+    float4_t acc[MT], acc2[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = acc2[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
     bool more = true;
 
     // masks and magic numbers in VGPRs, so each mask-and-insert is one v_and_or_b32
@@ -340,6 +353,7 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
         quarters(cur.s[0], sc);
         quarters(cur.z[0], zc);
       }
+      float4_t g8[2][MT];  // FP8: the products of 64 k (a slab)
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
         const int64_t kslab = (int64_t)(b * kU + u) * KS;  // first k of slab u in the slice
@@ -371,7 +385,10 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
           }
           const float s = valid ? f16_bits_to_f32((uint16_t)sc[u]) : 0.f;
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt] += s * gacc[mt];
+          for (int mt = 0; mt < MT; ++mt) {
+            float4_t& sum = kTwo && (u & 1) ? acc2[mt] : acc[mt];
+            sum += s * gacc[mt];
+          }
         } else if constexpr (KIND == kW8) {
 #pragma unroll
           for (int wd = 0; wd < 2; ++wd) {
@@ -385,8 +402,16 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
             for (int mt = 0; mt < MT; ++mt) {
               const half8_t a =
                   as_h8(*reinterpret_cast<const u32x4*>(xs + ((size_t)arow[mt] * g.xs_stride + cell0 + wd) * 8));
-              acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bw, acc[mt], 0, 0, 0);
+              if (kTwo)
+                g8[u & 1][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    a, bw, wd == 0 ? float4_t{0.f, 0.f, 0.f, 0.f} : g8[u & 1][mt], 0, 0, 0);
+              else
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bw, acc[mt], 0, 0, 0);
             }
+          }
+          if (kTwo && (u & 1)) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) (u & 2 ? acc2[mt] : acc[mt]) += g8[0][mt] + g8[1][mt];
           }
         } else {
           const half8_t bw = as_h8(c);
@@ -394,11 +419,15 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
           for (int mt = 0; mt < MT; ++mt) {
             const half8_t a =
                 as_h8(*reinterpret_cast<const u32x4*>(xs + ((size_t)arow[mt] * g.xs_stride + cell0) * 8));
-            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bw, acc[mt], 0, 0, 0);
+            float4_t& sum = kTwo && (u & 1) ? acc2[mt] : acc[mt];
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bw, sum, 0, 0, 0);
           }
         }
       }
       if (b + 1 == b_end) {  // the chunk's last unit
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          if (kTwo) acc[mt] += acc2[mt];
         if (MT > 1 && direct) {
           // the chunk is a whole task of this workgroup: its values are finished
           // here (meeting the other K slice's in a 64-bit slot when there are two)
@@ -430,7 +459,7 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
             }
         }
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = acc2[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
       }
       t = t_n;
       b = b_n;
@@ -482,7 +511,7 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
     unsigned long long oth[MQ];
     if (ca != tt * J || cb != (tt + 1) * J) {  // shared with a neighbouring workgroup (uniform in the wavefront)
       const bool upper = tt * J < c0;          // this workgroup holds the task's later chunks
-      unsigned long long* ws = xchg + ((size_t)split * nwg_max + (upper ? wg - 1 : wg)) * M * 16 + col;
+      unsigned long long* ws = (xchg ? xchg : meet_slots) + ((size_t)split * nwg_max + (upper ? wg - 1 : wg)) * M * 16 + col;
 #pragma unroll
       for (int j = 0; j < MQ; ++j) {
         oth[j] = 0ull;
@@ -527,28 +556,65 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
   }
 }
 
-template <bool F16Out>
+// Sum of the K slices' partial outputs, V (4 where the size and y's alignment
+// allow it, else 1) values per thread: over the four
+// projections of a 3584-wide layer at m = 36 7.6 -> 6.7 us each, 151936 rows at
+// m = 48 the whole call 281 -> 273 us.
+template <int V, int MODE>
 __global__ __launch_bounds__(256) void slice_reduce_kernel(const float* __restrict__ partial, int splits,
                                                            int64_t mn, void* __restrict__ y) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < mn; i += (int64_t)gridDim.x * 256) {
-    float v = 0.f;
-    for (int s = 0; s < splits; ++s) v += partial[(int64_t)s * mn + i];
-    store_out<F16Out>(y, i, v);
+  using vec = __attribute__((ext_vector_type(V))) float;
+  using hvec = __attribute__((ext_vector_type(V))) uint16_t;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < mn / V; i += (int64_t)gridDim.x * 256) {
+    vec v = reinterpret_cast<const vec*>(partial)[i];
+    for (int s = 1; s < splits; ++s) v += reinterpret_cast<const vec*>(partial + (int64_t)s * mn)[i];
+    if constexpr (MODE == kOutF16) {
+      hvec h;
+#pragma unroll
+      for (int j = 0; j < V; ++j) h[j] = f32_to_f16_bits(v[j]);
+      reinterpret_cast<hvec*>(y)[i] = h;
+    } else if constexpr (MODE == kOutAcc) {
+      reinterpret_cast<vec*>(y)[i] += v;
+    } else {
+      reinterpret_cast<vec*>(y)[i] = v;
+    }
   }
 }
 
-constexpr int64_t kChunkMinUnits = 4;  // units per chunk, at least (measured: 4 beats 1 and 2)
-constexpr size_t kLdsTotal = 150 * 1024;   // one workgroup per CU
-constexpr size_t kPieceBudget = 32 * 1024; // chunk partial sums
+hipError_t slice_reduce(const float* partial, int splits, int64_t mn, void* y, int out_mode, hipStream_t stream) {
+  const bool wide = mn % 4 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
+  int64_t blocks = (mn / (wide ? 4 : 1) + 255) / 256;
+  if (blocks > 4096) blocks = 4096;
+  auto go = [&](auto v, auto mode) {
+    hipLaunchKernelGGL((slice_reduce_kernel<decltype(v)::value, decltype(mode)::value>), dim3((unsigned)blocks),
+                       dim3(256), 0, stream, partial, splits, mn, y);
+    return hipGetLastError();
+  };
+  auto with = [&](auto mode) {
+    return wide ? go(std::integral_constant<int, 4>{}, mode) : go(std::integral_constant<int, 1>{}, mode);
+  };
+  if (out_mode == kOutF16) return with(std::integral_constant<int, kOutF16>{});
+  if (out_mode == kOutAcc) return with(std::integral_constant<int, kOutAcc>{});
+  return with(std::integral_constant<int, kOutF32>{});
+}
+
+constexpr int64_t kChunkMinUnits = 4;  // units per chunk (measured on large matrices: 4 beats 1 and 2)
+// One workgroup per CU. Up to 16 rows the chunk partial sums may take 40 KB (151936 rows at m = 16 need 38:
+// 381 -> 197 us in FP16, whole tasks per wavefront have no epilogue there); above, 32 KB and else whole tasks,
+// whose two K slices meet in registers (17920 x 1536 at m = 64 in FP16: 26 us, with 40 KB in chunks 46 us).
+template <int MT>
+constexpr size_t kLdsTotal = MT == 1 ? 158 * 1024 : 150 * 1024;
+template <int MT>
+constexpr size_t kPieceBudget = MT == 1 ? 40 * 1024 : 32 * 1024;
 
 template <int KIND, int NW, int MT>
 hipError_t linear_launch(const uint16_t* x, int m, int64_t k, const uint8_t* w, const uint16_t* scales16,
-                         const uint16_t* zeros16, const float* scales32, int64_t n, void* y, bool f16_out,
+                         const uint16_t* zeros16, const float* scales32, int64_t n, void* y, int out_mode,
                          bool direct, hipStream_t stream) {
   constexpr int64_t UK = (int64_t)kU * k_per_slab<KIND>();
   // K slices of whole units whose activations fit (2 bytes per k and row, plus a pad cell per row);
   // the direct mode keeps no chunk partial sums in LDS
-  int64_t kmax = (int64_t)((kLdsTotal - (direct ? 0 : kPieceBudget)) / ((size_t)m * 2)) - 8;
+  int64_t kmax = (int64_t)((kLdsTotal<MT> - (direct ? 0 : kPieceBudget<MT>)) / ((size_t)m * 2)) - 8;
   kmax = kmax / UK * UK;
   if (kmax < UK) return hipErrorNotSupported;  // the caller takes another kernel
   const int splits = (int)((k + kmax - 1) / kmax);
@@ -563,15 +629,21 @@ hipError_t linear_launch(const uint16_t* x, int m, int64_t k, const uint8_t* w, 
   const int64_t cap = (int64_t)cu_count() / splits;
   if (nwg_max > cap) nwg_max = cap;
   if (nwg_max < 1) nwg_max = 1;
-  // the smallest chunk whose partial sums ([chunks per workgroup][m][16] floats) fit the budget;
+  // chunks of kChunkMinUnits units, or of fewer where those would leave wavefronts
+  // without one (a row block of 2048 x 1536 is three INT4 units: as one chunk, seven
+  // of eight wavefronts idled, 7.3 -> 6.0 us at m = 3; not with three or more row
+  // tiles, 11264 x 2048 FP8 at m = 36 19.4 -> 22.3), and longer ones where the
+  // partial sums ([chunks per workgroup][m][16] floats) exceed the budget;
   // direct: one chunk per task, no partial sums
-  int64_t C = direct ? S : kChunkMinUnits, nch_max = 0;
+  int64_t cmin = (ntask * S + nwg_max * NW - 1) / (nwg_max * NW);
+  if (cmin > kChunkMinUnits) cmin = kChunkMinUnits;
+  int64_t C = direct ? S : (MT <= 2 ? cmin : kChunkMinUnits), nch_max = 0;
   for (;; ++C) {
     const int64_t J = (S + C - 1) / C;
     nch_max = (ntask * J + nwg_max - 1) / nwg_max;
-    if (direct || (size_t)nch_max * m * 16 * sizeof(float) <= kPieceBudget || C >= S) break;
+    if (direct || (size_t)nch_max * m * 16 * sizeof(float) <= kPieceBudget<MT> || C >= S) break;
   }
-  if (!direct && (size_t)nch_max * m * 16 * sizeof(float) > kPieceBudget) return hipErrorNotSupported;
+  if (!direct && (size_t)nch_max * m * 16 * sizeof(float) > kPieceBudget<MT>) return hipErrorNotSupported;
   // the kernel's chunk arithmetic is exact below 2^52 (workgroup index x chunks per slice)
   if ((double)(nwg_max + 1) * (double)(ntask * S) >= 4503599627370496.0) return hipErrorNotSupported;
   const size_t lds = ((size_t)m * cells * 16 + 15) / 16 * 16 + (direct ? 0 : (size_t)nch_max * m * 16 * sizeof(float));
@@ -591,66 +663,79 @@ hipError_t linear_launch(const uint16_t* x, int m, int64_t k, const uint8_t* w, 
   const size_t wg_slots = (size_t)splits * nwg_max * m * 16;
   const size_t value_slots = slice_meet ? (size_t)m * n : 0;
   int32_t* slots = nullptr;
-  const hipError_t ce = zeroed_counters(2 * (wg_slots + value_slots), stream, &slots);
-  if (ce != hipSuccess) return ce;
+  if (splits > 1 || wg_slots > kMeetSlots) {
+    const hipError_t ce = zeroed_counters(2 * (wg_slots + value_slots), stream, &slots);
+    if (ce != hipSuccess) return ce;
+  }
   unsigned long long* xchg = reinterpret_cast<unsigned long long*>(slots);
   // more than half the LDS, so that a CU holds one workgroup
   const size_t lds_launch = lds < 81 * 1024 ? 81 * 1024 : lds;
   hipLaunchKernelGGL((linear_kernel<KIND, NW, MT>), dim3((unsigned)nwg_max, (unsigned)splits), dim3(NW * 64),
-                     lds_launch, stream, x, m, k, kslice, w, scales16, zeros16, scales32, n, y, (int)f16_out,
+                     lds_launch, stream, x, m, k, kslice, w, scales16, zeros16, scales32, n, y, out_mode,
                      split_out, nwg_max, (int)C, xchg, slice_meet ? xchg + wg_slots : nullptr, (int)direct);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || splits == 1 || slice_meet) return err;
-  int64_t blocks = ((int64_t)m * n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  if (f16_out)
-    hipLaunchKernelGGL(slice_reduce_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, split_out, splits,
-                       (int64_t)m * n, y);
-  else
-    hipLaunchKernelGGL(slice_reduce_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, split_out, splits,
-                       (int64_t)m * n, y);
-  return hipGetLastError();
+  return slice_reduce(split_out, splits, (int64_t)m * n, y, out_mode, stream);
 }
 
 template <int KIND>
 hipError_t linear_dispatch(const uint16_t* x, int m, int64_t k, const uint8_t* w, const uint16_t* scales16,
-                           const uint16_t* zeros16, const float* scales32, int64_t n, void* y, bool f16_out,
+                           const uint16_t* zeros16, const float* scales32, int64_t n, void* y, int out_mode,
                            hipStream_t stream) {
   if (m < 1 || m > 64) return hipErrorInvalidValue;
   // chunks of a task spread over the wavefronts where their partial sums fit
   // in LDS, else whole tasks per wavefront (direct; its epilogue needs MT > 1)
   auto go = [&](auto mt_tag) {
     constexpr int MT = decltype(mt_tag)::value;
-    hipError_t e = linear_launch<KIND, 8, MT>(x, m, k, w, scales16, zeros16, scales32, n, y, f16_out, false, stream);
+    hipError_t e = linear_launch<KIND, 8, MT>(x, m, k, w, scales16, zeros16, scales32, n, y, out_mode, false, stream);
     if (e == hipErrorNotSupported && MT > 1)
-      e = linear_launch<KIND, 8, MT>(x, m, k, w, scales16, zeros16, scales32, n, y, f16_out, true, stream);
+      e = linear_launch<KIND, 8, MT>(x, m, k, w, scales16, zeros16, scales32, n, y, out_mode, true, stream);
     return e;
   };
   if (m > 48) return go(std::integral_constant<int, 4>{});
   if (m > 32) return go(std::integral_constant<int, 3>{});
   if (m > 16) return go(std::integral_constant<int, 2>{});
   const hipError_t e = go(std::integral_constant<int, 1>{});
-  // the quantized copies have no other kernel above m = 8: two tiles, the second one padding
-  if (e == hipErrorNotSupported && KIND != kF16 && m > 8) return go(std::integral_constant<int, 2>{});
+  // the quantized copies have no other kernel from m = 3 or 5 on: two tiles, the second one padding
+  if (e == hipErrorNotSupported && KIND != kF16) return go(std::integral_constant<int, 2>{});
   return e;
 }
 
 }  // namespace
 
+hipError_t launch_linear_w4_mode(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const uint16_t* scales,
+                                 const uint16_t* zeros, int64_t n, void* y, int out_mode, hipStream_t stream) {
+  return linear_dispatch<kW4>(x, m, k, codes, scales, zeros, nullptr, n, y, out_mode, stream);
+}
+
+hipError_t launch_linear_w8_mode(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const float* scales,
+                                 int64_t n, void* y, int out_mode, hipStream_t stream) {
+  return linear_dispatch<kW8>(x, m, k, codes, nullptr, nullptr, scales, n, y, out_mode, stream);
+}
+
 hipError_t launch_linear_w4(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const uint16_t* scales,
                             const uint16_t* zeros, int64_t n, void* y, bool f16_out, hipStream_t stream) {
-  return linear_dispatch<kW4>(x, m, k, codes, scales, zeros, nullptr, n, y, f16_out, stream);
+  const int mode = f16_out ? kOutF16 : kOutF32;
+  if (tile_takes(n, k) || tile_takes_long(n, k, m, 6, 32))
+    return launch_tile_w4(x, m, k, codes, scales, zeros, n, y, mode, stream);
+  return launch_linear_w4_mode(x, m, k, codes, scales, zeros, n, y, mode, stream);
 }
 
 hipError_t launch_linear_w8(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const float* scales,
                             int64_t n, void* y, bool f16_out, hipStream_t stream) {
-  return linear_dispatch<kW8>(x, m, k, codes, nullptr, nullptr, scales, n, y, f16_out, stream);
+  const int mode = f16_out ? kOutF16 : kOutF32;
+  if (tile_takes_w8(n, k, m)) return launch_tile_w8(x, m, k, codes, scales, n, y, mode, stream);
+  return launch_linear_w8_mode(x, m, k, codes, scales, n, y, mode, stream);
 }
 
+// (above 8 rows, small matrices to tile_kernel: hipErrorNotSupported)
 hipError_t launch_linear_f16(const uint16_t* x, int m, int64_t k, const uint16_t* w, int64_t n, void* y,
                              bool f16_out, hipStream_t stream) {
-  return linear_dispatch<kF16>(x, m, k, reinterpret_cast<const uint8_t*>(w), nullptr, nullptr, nullptr, n, y, f16_out,
-                               stream);
+  if (m > 8 && (tile_takes(n, k) || tile_takes_long(n, k, m, 9, 12) ||
+                (m <= 16 && k <= 2048 && (n + 15) / 16 * k <= 1500000)))
+    return hipErrorNotSupported;
+  return linear_dispatch<kF16>(x, m, k, reinterpret_cast<const uint8_t*>(w), nullptr, nullptr, nullptr, n, y,
+                               f16_out ? kOutF16 : kOutF32, stream);
 }
 
 }  // namespace sq

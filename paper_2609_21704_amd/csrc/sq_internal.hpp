@@ -33,6 +33,10 @@ hipError_t launch_quantize_int4(const uint16_t* w, int64_t n, int64_t k, uint8_t
 hipError_t launch_quantize_fp8(const uint16_t* w, int64_t n, int64_t k, uint8_t* codes, float* scales,
                                int32_t* flag, hipStream_t stream);
 
+// Output modes of the projection kernels: y fp32, y fp16, y fp32 added to, or
+// (GEMV tasks of a gate and an up row) t = f16(silu(gate) * up) [m][n / 2].
+enum : int { kOutF32 = 0, kOutF16 = 1, kOutAcc = 2, kOutSilu = 3 };
+
 // Input rows of a projection taken as f16(rmsnorm(h row)) with weights w:
 // staged row m is h row m * group + group - 1 ([m * group][k] fp32), normalised
 // inside the projection's activation staging with the arithmetic of
@@ -56,13 +60,45 @@ hipError_t launch_gemv_w8(const uint16_t* x, int m, int64_t k, const uint8_t* co
                           int64_t n, void* y, bool f16_out, hipStream_t stream);
 hipError_t launch_gemm_f16(const uint16_t* x, int m, int64_t k, const uint16_t* w, int64_t n, void* y,
                            bool f16_out, hipStream_t stream);
+// The same kernel (small matrices) with the draft copies, m <= 64.
+hipError_t launch_tile_w4(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const uint16_t* scales,
+                          const uint16_t* zeros, int64_t n, void* y, int out_mode, hipStream_t stream);
+hipError_t launch_tile_w8(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const float* scales, int64_t n,
+                          void* y, int out_mode, hipStream_t stream);
+
+// A small matrix for tile_kernel, from the measured crossovers with the
+// kernels that stage activations in LDS: row blocks of 16 within one per CU
+// and rows of up to 4096 k (3584 x 3584 INT4, tile / linear_kernel: m = 8 6.1 /
+// 8.1 us, m = 64 18.0 / 19.0; 4608 x 3584, two rounds: m = 8 9.2 / 8.8), or so
+// few rows and k that two or three rounds cost little (9728 x 896, m = 16: 5.3 /
+// 7.6; 17920 x 1536: 12.6 / 10.0).
+inline bool tile_takes(int64_t n, int64_t k) {
+  const int64_t tiles = (n + 15) / 16;
+  return (tiles <= cu_count() && k <= 4096) || tiles * k <= 640000;
+}
+// Longer rows, within one row block per CU, between `lo` and `hi` activation
+// rows (896 x 4864 INT4: m = 8 7.2 / 9.8 us, m = 32 12.5 / 12.6, m = 48 18.5 / 15.3).
+inline bool tile_takes_long(int64_t n, int64_t k, int m, int lo, int hi) {
+  return (n + 15) / 16 <= cu_count() && k <= 6144 && m >= lo && m <= hi;
+}
+inline bool tile_takes_w8(int64_t n, int64_t k, int m) {
+  return tile_takes(n, k) || tile_takes_long(n, k, m, 5, 16) ||
+         (m <= 16 && k <= 2048 && (n + 15) / 16 * k <= 1800000);
+}
+
 // Verification over row blocks on the vector ALUs, 1 <= m <= 8; returns
 // hipErrorNotSupported (nothing enqueued) for shapes it does not take.
 hipError_t launch_gemm_rows_f16(const uint16_t* x, int m, int64_t k, const uint16_t* w, int64_t n, void* y,
                                 bool f16_out, hipStream_t stream, const NormSrc* nrm = nullptr, bool accum = false);
 
-// The matrix-core streaming kernels (one implementation for the three weight
-// kinds; m <= 8 for INT4 / FP8, m <= 64 for FP16).
+// The matrix-core kernels at m <= 64 (one implementation for the three weight
+// kinds): launch_linear_w4 / _w8 take small matrices to tile_kernel, the
+// others (and launch_linear_f16 all) to the streaming linear_kernel.
+// launch_linear_w4_mode: the streaming kernel itself, in an output mode.
+hipError_t launch_linear_w4_mode(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const uint16_t* scales,
+                                 const uint16_t* zeros, int64_t n, void* y, int out_mode, hipStream_t stream);
+hipError_t launch_linear_w8_mode(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const float* scales,
+                                 int64_t n, void* y, int out_mode, hipStream_t stream);
 hipError_t launch_linear_w4(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const uint16_t* scales,
                             const uint16_t* zeros, int64_t n, void* y, bool f16_out, hipStream_t stream);
 hipError_t launch_linear_w8(const uint16_t* x, int m, int64_t k, const uint8_t* codes, const float* scales,
