@@ -23,6 +23,8 @@
 // at position pos_base[b] + pos_offset + j.  The round never moves cache data:
 // removing the rejected part of a block only moves pos_base, and the entries
 // past it are overwritten before any row can attend to them.
+#include <cmath>
+
 #include "sq_device.hpp"
 #include "sq_internal.hpp"
 
@@ -134,14 +136,55 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(float* __restrict__ h,
 // query rows and new cache entries (the same bits): pair (t, t + 64) of a head
 // turns by pos * theta^(-2t/128), the angle and its cosine and sine in fp64,
 // the turn itself in fp32 with every product rounded on its own.
-__device__ __forceinline__ double rope_freq(int t, double theta) {
-  return pow(theta, -2.0 * (double)t / (double)kHd);
+// Both functions are short series here: the library's pow and sincos, with their
+// branches for every argument, are code that a launch fetches to run once
+// (with the items' shorter code a rotating attention of 4 x 9 rows over 64
+// positions took 12.1 us, 14.1 before; the attention alone 8.0).
+struct RopeBase {  // ln theta = hi + lo
+  double hi, lo;
+};
+
+// theta^(-2t/128) = exp(-(t / 64) ln theta), the exponent in two parts, the exponential by its Taylor series to
+// degree 13 on |r| <= ln 2 / 2 (next term 4e-18).
+__device__ __forceinline__ double rope_freq(int t, RopeBase base) {
+  const double s = (double)t * (-1.0 / 64.0);
+  const double x = s * base.hi, xl = __builtin_fma(s, base.hi, -x) + s * base.lo;
+  const double n = rint(x * 0x1.71547652b82fep+0);
+  double r = __builtin_fma(n, -0x1.62e42fefa39efp-1, x);
+  r = __builtin_fma(n, -0x1.abc9e3b39803fp-56, r) + xl;
+  double p = 1.0 / 6227020800.0;
+  const double c[] = {1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0,
+                      1.0 / 5040.0,      1.0 / 720.0,      1.0 / 120.0,     1.0 / 24.0,     1.0 / 6.0,
+                      0.5,               1.0,              1.0};
+#pragma unroll
+  for (int i = 0; i < 13; ++i) p = __builtin_fma(p, r, c[i]);
+  return ldexp(p, (int)n);
 }
 
+// Cosine and sine of pos * freq: the angle less n pi / 2 by fused steps with pi / 2 in three parts (the first is
+// exact below 2^31), what the second rounds off carried along, and the Taylor series to degrees 16 and 17 on
+// |r| <= pi / 4 (next terms below 5e-17); 2.3e-16 of the values at most over angles up to 1e6.
 __device__ __forceinline__ float2 rope_cos_sin(int64_t pos, double freq) {
-  double sn, cs;
-  sincos((double)pos * freq, &sn, &cs);
-  return make_float2((float)cs, (float)sn);
+  const double x = (double)pos * freq;
+  const double n = rint(x * 0x1.45f306dc9c883p-1);
+  const double r1 = __builtin_fma(-n, 0x1.921fb54442d18p+0, x);
+  const double r = __builtin_fma(-n, 0x1.1a62633145c07p-54, r1);
+  const double tail = __builtin_fma(-n, -0x1.f1976b7ed8fbcp-110, __builtin_fma(-n, 0x1.1a62633145c07p-54, r1 - r));
+  const double z = r * r;
+  double ps = 1.0 / 355687428096000.0, pc = 1.0 / 20922789888000.0;
+  const double cs[] = {-1.0 / 1307674368000.0, 1.0 / 6227020800.0, -1.0 / 39916800.0, 1.0 / 362880.0,
+                       -1.0 / 5040.0,          1.0 / 120.0,        -1.0 / 6.0};
+  const double cc[] = {-1.0 / 87178291200.0, 1.0 / 479001600.0, -1.0 / 3628800.0, 1.0 / 40320.0, -1.0 / 720.0,
+                       1.0 / 24.0};
+#pragma unroll
+  for (int i = 0; i < 7; ++i) ps = __builtin_fma(ps, z, cs[i]);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) pc = __builtin_fma(pc, z, cc[i]);
+  const double sn = r + __builtin_fma(r * z, ps, tail);
+  const double co = __builtin_fma(-0.5, z, 1.0) + __builtin_fma(z * z, pc, -r * tail);
+  const int q = (int)(int64_t)n & 3;
+  const double a = q & 1 ? sn : co, b = q & 1 ? co : sn;  // |cosine|, |sine| of the angle
+  return make_float2((float)((q + 1) & 2 ? -a : a), (float)(q & 2 ? -b : b));
 }
 
 __device__ __forceinline__ void rope_turn(float a, float e, float2 cs, float& ra, float& re) {
@@ -153,7 +196,7 @@ __device__ __forceinline__ void rope_turn(float a, float e, float2 cs, float& ra
 // One wavefront per (row, head); lane t handles the pair (t, t + 64).
 __global__ __launch_bounds__(64) void rope_kv_kernel(const float* __restrict__ qkv, const uint16_t* __restrict__ bias,
                                                      int hq, int hkv, int rps, const int32_t* __restrict__ pos_base,
-                                                     int pos_offset, int64_t len_bound, int64_t capacity, double theta,
+                                                     int pos_offset, int64_t len_bound, int64_t capacity, RopeBase base,
                                                      uint16_t* __restrict__ q_out, uint16_t* __restrict__ kc,
                                                      uint16_t* __restrict__ vc, int32_t* __restrict__ status) {
   const int r = blockIdx.x, hh = blockIdx.y;
@@ -171,7 +214,7 @@ __global__ __launch_bounds__(64) void rope_kv_kernel(const float* __restrict__ q
     be = f16_bits_to_f32(bias[hh * kHd + t + 64]);
   }
   const bool rot = hh < hq + hkv;
-  const double freq = rot ? rope_freq(t, theta) : 0.0;
+  const double freq = rot ? rope_freq(t, base) : 0.0;
   if (pos < 0 || pos >= len_bound) {
     if (hh < hq) {
       q_out[((int64_t)r * hq + hh) * kHd + t] = kNanF16;
@@ -287,17 +330,41 @@ __device__ __forceinline__ void attn_mask_v(int64_t key0, int64_t pmax, int lg, 
   }
 }
 
+// v_exp_f32 alone: exp2f's extra steps only serve results below 2^-126.
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// max / sum over the four lanes li + 16 (0..3) that share a query row
+template <class OP>
+__device__ __forceinline__ float quad_fold(float v, OP op) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t p0 = p[0], p1 = p[1];
+  const uint32_t w = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(float, p0), __builtin_bit_cast(float, p1)));
+  const auto r = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  const uint32_t r0 = r[0], r1 = r[1];
+  return op(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1));
+}
+__device__ __forceinline__ float quad_max(float v) {
+  return quad_fold(v, [](float x, float y) { return fmaxf(x, y); });
+}
+__device__ __forceinline__ float quad_sum(float v) {
+  return quad_fold(v, [](float x, float y) { return x + y; });
+}
+
 // One chunk (keys key0 .. key0 + 63) into tile qt's running (m, l, O); the
 // key fragment (kt, s) and value fragment (t2, dt) come from kfrag / vfrag,
-// each called where the matrix cores take it.
-template <class KF, class VF>
+// each called where the matrix cores take it.  FULL: every row of the tile
+// reads every key (no mask).  l is this lane's share of the row's sum: the
+// caller adds the four lanes' (quad_sum) when it has seen all its chunks.
+// The vector ALUs bound this (16 scores a lane against 48 matrix products of
+// the wavefront): no 64-bit compares, the scale folded into one fma a score,
+// O rescaled only where a maximum grew, row maxima folded by lane swaps (four
+// layers of 4 sequences x 9 rows at 8192 positions 145 -> 127 us).
+template <bool FULL, class KF, class VF>
 __device__ __forceinline__ void attn_update_src(const AttnTile& a, int64_t p0, int qt, int li, int lg,
                                                 const half8_t (&qf)[4], KF kfrag, VF vfrag, int64_t key0, float& m,
                                                 float& l, float4_t (&o)[8]) {
   const float sl2 = 1.4426950408889634f * 0.08838834764831845f;  // log2(e) / sqrt(128)
-  const int qi = 16 * qt + li;
-  const bool qok = qi < a.nq;
-  const int j = qok ? qi / a.G : 0;
   float4_t st[4];
 #pragma unroll
   for (int kt = 0; kt < 4; ++kt) {
@@ -306,22 +373,25 @@ __device__ __forceinline__ void attn_update_src(const AttnTile& a, int64_t p0, i
     for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kfrag(kt, s), qf[s], acc, 0, 0, 0);
     st[kt] = acc;
   }
-  const int64_t qpos = p0 + j;
-  float cm = -__builtin_inff();
+  if constexpr (!FULL) {
+    const int qi = 16 * qt + li;
+    // the last key of the chunk that this row reads, less 4 lg
+    const int64_t lim64 = qi < a.nq ? p0 + qi / a.G - key0 : -1;
+    const int lim = (int)(lim64 < -1 ? -1 : (lim64 > kChunk ? kChunk : lim64)) - 4 * lg;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) st[kt][i] = 16 * kt + i <= lim ? st[kt][i] : -__builtin_inff();
+  }
+  float cm = st[0][0];
 #pragma unroll
   for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t key = key0 + 16 * kt + 4 * lg + i;
-      const float v = (qok && key <= qpos) ? st[kt][i] * sl2 : -__builtin_inff();
-      st[kt][i] = v;
-      cm = fmaxf(cm, v);
-    }
-  cm = fmaxf(cm, __shfl_xor(cm, 16, kWave));
-  cm = fmaxf(cm, __shfl_xor(cm, 32, kWave));
-  const float mn = fmaxf(m, cm);
+    for (int i = 0; i < 4; ++i) cm = fmaxf(cm, st[kt][i]);
+  cm = quad_max(fmaxf(cm, -__builtin_inff()));  // (scores of NaN alone count as none)
+  const float mn = fmaxf(m, cm * sl2);
   const bool none = mn == -__builtin_inff();  // no key of this row so far
-  const float alpha = none ? 1.f : exp2f(m - mn);
+  const float alpha = none ? 1.f : exp2_fast(m - mn);
   // p = hi + lo, both binary16 (hi = f16(p), lo = f16(p - hi), the difference
   // exact in fp32): two products with the values carry p to about 2^-22
   float psum = 0.f;
@@ -330,25 +400,27 @@ __device__ __forceinline__ void attn_update_src(const AttnTile& a, int64_t p0, i
   for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float p = none ? 0.f : exp2f(st[kt][i] - mn);
+      const float p = none ? 0.f : exp2_fast(__builtin_fmaf(st[kt][i], sl2, -mn));
       const half_t ph = (half_t)p;
       psum += p;
       pf[kt >> 1][(kt & 1) * 4 + i] = ph;
       pl[kt >> 1][(kt & 1) * 4 + i] = (half_t)(p - (float)ph);
     }
-  psum += __shfl_xor(psum, 16, kWave);
-  psum += __shfl_xor(psum, 32, kWave);
   l = l * alpha + psum;
   m = mn;
-  // rows 4 lg + i of the output tile take the factor of query 4 lg + i
-  float ar[4];
+  if (__any(alpha != 1.f)) {
+    // rows 4 lg + i of the output tile take the factor of query 4 lg + i
+    float ar[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) ar[i] = __shfl(alpha, 4 * lg + i, kWave);
+    for (int i = 0; i < 4; ++i) ar[i] = __shfl(alpha, 4 * lg + i, kWave);
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[dt][i] *= ar[i];
+  }
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) {
     float4_t acc = o[dt];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] *= ar[i];
     const half8_t v0 = vfrag(0, dt), v1 = vfrag(1, dt);
     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(pl[0], v0, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(pl[1], v1, acc, 0, 0, 0);
@@ -362,7 +434,7 @@ __device__ __forceinline__ void attn_update(const AttnTile& a, int64_t p0, int q
                                             const half8_t (&qf)[4], const half8_t (&kf)[4][4],
                                             const half8_t (&vf)[2][8], int64_t key0, float& m, float& l,
                                             float4_t (&o)[8]) {
-  attn_update_src(
+  attn_update_src<false>(
       a, p0, qt, li, lg, qf, [&](int kt, int s) { return kf[kt][s]; }, [&](int t2, int dt) { return vf[t2][dt]; },
       key0, m, l, o);
 }
@@ -399,6 +471,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) po[(int64_t)(16 * qt + 4 * lg + i) * kHd + 16 * dt + li] = o[dt][i];
+    l = quad_sum(l);
     if (lg == 0) pml[16 * qt + li] = make_float2(m, l);
   };
 
@@ -453,6 +526,39 @@ constexpr int kLdsChunk = 64 * kLdsKeyStride + kHd * kLdsValStride;  // halves p
 constexpr int kLdsThreads = 256;
 constexpr int kLdsCells = 2 * kChunk * kHd * 2 / 16 / kLdsThreads;  // 16-byte cells per thread and chunk: 8
 
+// A chunk staged in LDS (rows of kLdsKeyStride / kLdsValStride halves) into
+// tile qt's sums; p0row: the position of the tile's first row.  Values of keys
+// after pmax are zeroed (stale entries).
+__device__ __forceinline__ void attn_update_lds(const AttnTile& a, int64_t p0, int64_t p0row, int64_t pmax, int qt,
+                                                int li, int lg, const half8_t (&qf)[4], const half_t* b, int64_t key0,
+                                                float& m, float& l, float4_t (&o)[8]) {
+  auto kfrag = [&](int kt, int s4) {
+    return *reinterpret_cast<const half8_t*>(b + (16 * kt + li) * kLdsKeyStride + 32 * lg + 8 * s4);
+  };
+  auto vfrag = [&](int t2, int dt) {
+    const half_t* vr = b + 64 * kLdsKeyStride + (16 * dt + li) * kLdsValStride + 32 * t2 + 4 * lg;
+    const half4_t va = *reinterpret_cast<const half4_t*>(vr);
+    const half4_t vb = *reinterpret_cast<const half4_t*>(vr + 16);
+    return __builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  if (key0 + kChunk - 1 <= p0row) {  // uniform
+    attn_update_src<true>(a, p0, qt, li, lg, qf, kfrag, vfrag, key0, m, l, o);
+    return;
+  }
+  const int64_t last64 = pmax - key0;  // the last key of the chunk that any row reads, less 4 lg
+  const int last = (int)(last64 < kChunk ? (last64 < -1 ? -1 : last64) : kChunk) - 4 * lg;
+  auto vfrag_tail = [&](int t2, int dt) {
+    half8_t f = vfrag(t2, dt);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      f[e] = 32 * t2 + e <= last ? f[e] : (half_t)0;
+      f[4 + e] = 32 * t2 + 16 + e <= last ? f[4 + e] : (half_t)0;
+    }
+    return f;
+  };
+  attn_update_src<false>(a, p0, qt, li, lg, qf, kfrag, vfrag_tail, key0, m, l, o);
+}
+
 // The attention that also does rope_kv_kernel's work for its block: the
 // sources of the rotation (the q|k|v projection rows) and where the new keys
 // and values go.  At most 64 query rows per (sequence, kv head) and 16 rows
@@ -460,7 +566,7 @@ constexpr int kLdsCells = 2 * kChunk * kHd * 2 / 16 / kLdsThreads;  // 16-byte c
 struct RopeSrc {
   const float* qkv;      // [b rps][(hq + 2 hkv) * 128] fp32
   const uint16_t* bias;  // [(hq + 2 hkv) * 128] fp16, or null
-  double theta;
+  RopeBase base;
   int64_t len_bound;
   uint16_t* kc;  // the caches, written at the block's valid positions
   uint16_t* vc;
@@ -517,41 +623,37 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
   };
 
   load_chunk(slot0);  // before the positions arrive: the slot's first chunk lies in the cache
-  // ROPE: item idx = tid + 256 it is row-head r = idx / 16 (query rows qi < nq
-  // of kv head g, then row j's key, then row j's value) and pairs 4 (idx % 16)
-  // .. +4; its q|k|v sources do not depend on the positions
-  const int nh = hq + 2 * hkv;
-  const int nitems = ROPE ? (a.nq + 2 * rps) * 16 : 0;
+  // ROPE: a thread's item `it` is row-head r = tid / 16 + 16 it (query rows qi <
+  // nq of kv head g, then row j's key, then row j's value) and pairs t0 .. t0 +
+  // 4; its q|k|v sources do not depend on the positions.  The code is kept
+  // short: it runs once per launch, so its instruction fetches are its cost.
+  const int nh = hq + 2 * hkv, t0 = 4 * (tid & 15);
+  const int nrows = ROPE ? a.nq + 2 * rps : 0;
+  const int ginv = 65536 / a.G + 1;  // r / G = (r ginv) >> 16 for r G < 65536
   float4_t ulo[ROPE ? kRopeItems : 1], uhi[ROPE ? kRopeItems : 1];
   half4_t blo[ROPE ? kRopeItems : 1], bhi[ROPE ? kRopeItems : 1];
-  auto item = [&](int idx, int& j, int& head, int& kind) {  // kind 0 query, 1 key, 2 value
-    const int r = idx >> 4;
+  auto item = [&](int r, int& j, int& head) {
     if (r < a.nq) {
-      j = r / a.G;
+      j = (r * ginv) >> 16;
       head = g * a.G + (r - j * a.G);
-      kind = 0;
-    } else if (r < a.nq + rps) {
-      j = r - a.nq;
-      head = hq + g;
-      kind = 1;
     } else {
-      j = r - a.nq - rps;
-      head = hq + hkv + g;
-      kind = 2;
+      const bool value = r >= a.nq + rps;
+      j = r - a.nq - (value ? rps : 0);
+      head = hq + g + (value ? hkv : 0);
     }
   };
   if constexpr (ROPE) {
 #pragma unroll
     for (int it = 0; it < kRopeItems; ++it) {
-      const int idx = tid + kLdsThreads * it;
-      if (idx < nitems) {
-        int j, head, kind;
-        item(idx, j, head, kind);
-        const float* src = rs.qkv + ((int64_t)(bi * rps + j) * nh + head) * kHd + 4 * (idx & 15);
+      const int r = (tid >> 4) + 16 * it;
+      if (r < nrows) {
+        int j, head;
+        item(r, j, head);
+        const float* src = rs.qkv + (int64_t)((bi * rps + j) * nh + head) * kHd + t0;
         ulo[it] = *reinterpret_cast<const float4_t*>(src);
         uhi[it] = *reinterpret_cast<const float4_t*>(src + 64);
         if (rs.bias) {
-          const uint16_t* bp = rs.bias + head * kHd + 4 * (idx & 15);
+          const uint16_t* bp = rs.bias + head * kHd + t0;
           blo[it] = *reinterpret_cast<const half4_t*>(bp);
           bhi[it] = *reinterpret_cast<const half4_t*>(bp + 64);
         }
@@ -560,7 +662,7 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
   }
   const int64_t p0 = (int64_t)pos_base[bi] + pos_offset;
   // the pair of every table entry this thread fills is tid % 64 (256 threads a row step)
-  const double freq = ROPE ? rope_freq(tid & 63, rs.theta) : 0.0;
+  const double freq = ROPE ? rope_freq(tid & 63, rs.base) : 0.0;
   const int64_t pmax = p0 + rps - 1;
   if constexpr (ROPE) {
     if (slot == 0 && g == 0 && tid < rps && (p0 + tid < 0 || p0 + tid >= rs.len_bound)) flag(rs.status, kBadPos);
@@ -572,10 +674,6 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
   const bool owner = wave < nqt;
   half8_t qf[4];
   half_t* newkv = lbuf + 2 * kLdsChunk;  // [2][rps][128]: the block's keys, then its values
-  // a valid position of the block, in this slot: its new entry goes to the caches from here
-  auto store_kv = [&](int64_t pos) {
-    return pos >= 0 && pos < rs.len_bound && pos >= slot0 && pos < slot0 + (int64_t)span * kChunk;
-  };
   if constexpr (ROPE) {
     half_t* qb = lbuf + kLdsChunk;                        // [nq][128] rotated query rows
     float2* tab = reinterpret_cast<float2*>(qb + 64 * kHd);  // [rps][64] cosine, sine of (row, pair)
@@ -583,11 +681,10 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
     lds_barrier();
 #pragma unroll
     for (int it = 0; it < kRopeItems; ++it) {
-      const int idx = tid + kLdsThreads * it;
-      if (idx < nitems) {
-        int j, head, kind;
-        item(idx, j, head, kind);
-        const int t0 = 4 * (idx & 15);
+      const int r = (tid >> 4) + 16 * it;
+      if (r < nrows) {
+        int j, head;
+        item(r, j, head);
         half4_t lo, hi;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
@@ -596,27 +693,39 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
             u += (float)blo[it][x];
             v += (float)bhi[it][x];
           }
-          if (kind < 2) rope_turn(u, v, tab[j * 64 + t0 + x], u, v);
-          const half_t hu = (half_t)u, hv = (half_t)v;  // scalar copies: vector element lvalues are
-          lo[x] = hu;                                   // misread by bit_cast
-          hi[x] = hv;
-          if (kind == 2 && store_kv(p0 + j)) {
-            uint16_t* vo = rs.vc + ((int64_t)bg * kHd + t0 + x) * capacity + p0 + j;
-            vo[0] = __builtin_bit_cast(uint16_t, hu);
-            vo[(int64_t)64 * capacity] = __builtin_bit_cast(uint16_t, hv);
-          }
+          float ru, rv;
+          rope_turn(u, v, tab[j * 64 + t0 + x], ru, rv);
+          lo[x] = (half_t)(r < a.nq + rps ? ru : u);  // values are not turned
+          hi[x] = (half_t)(r < a.nq + rps ? rv : v);
         }
-        half_t* dst = kind == 0 ? qb + (idx >> 4) * kHd : newkv + ((kind - 1) * rps + j) * kHd;
+        half_t* dst = r < a.nq ? qb + r * kHd : newkv + (r - a.nq) * kHd;
         *reinterpret_cast<half4_t*>(dst + t0) = lo;
         *reinterpret_cast<half4_t*>(dst + t0 + 64) = hi;
-        if (kind == 1 && store_kv(p0 + j)) {
-          uint16_t* ko = rs.kc + ((int64_t)bg * capacity + p0 + j) * kHd + t0;
-          *reinterpret_cast<half4_t*>(ko) = lo;
-          *reinterpret_cast<half4_t*>(ko + 64) = hi;
-        }
       }
     }
     lds_barrier();
+    // the block's valid positions in this slot go to the caches from here, the
+    // values with adjacent lanes at adjacent positions
+    const int64_t lo_pos = slot0 > 0 ? slot0 : 0;
+    const int64_t end = slot0 + (int64_t)span * kChunk < rs.len_bound ? slot0 + (int64_t)span * kChunk : rs.len_bound;
+    if (p0 < end && pmax >= lo_pos) {  // uniform
+      const int sh = rps > 1 ? 32 - __builtin_clz(rps - 1) : 0;  // rps <= 2^sh
+#pragma unroll 1
+      for (int e = tid; e < rps * 16; e += kLdsThreads) {
+        const int64_t pos = p0 + (e >> 4);
+        if (pos >= lo_pos && pos < end)
+          *reinterpret_cast<u32x4*>(rs.kc + ((int64_t)bg * capacity + pos) * kHd + (e & 15) * 8) =
+              *reinterpret_cast<const u32x4*>(newkv + e * 8);
+      }
+#pragma unroll 1
+      for (int e = tid; e < kHd << sh; e += kLdsThreads) {
+        const int j = e & ((1 << sh) - 1), d = e >> sh;
+        const int64_t pos = p0 + j;
+        if (j < rps && pos >= lo_pos && pos < end)
+          rs.vc[((int64_t)bg * kHd + d) * capacity + pos] =
+              __builtin_bit_cast(uint16_t, newkv[(rps + j) * kHd + d]);
+      }
+    }
     if (owner) {
       const half8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
       const int qi = 16 * wave + li;
@@ -676,24 +785,7 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
     lds_barrier();
     const half_t* b = lbuf + (t & 1) * kLdsChunk;
     if (owner) {
-      const bool tail = key0 + kChunk - 1 > pmax;  // values of keys after pmax are zeroed (stale entries)
-      auto kfrag = [&](int kt, int s4) {
-        return *reinterpret_cast<const half8_t*>(b + (16 * kt + li) * kLdsKeyStride + 32 * lg + 8 * s4);
-      };
-      auto vfrag = [&](int t2, int dt) {
-        const int ka = 32 * t2 + 4 * lg, kb = ka + 16;
-        const half_t* vr = b + 64 * kLdsKeyStride + (16 * dt + li) * kLdsValStride;
-        const half4_t va = *reinterpret_cast<const half4_t*>(vr + ka);
-        const half4_t vb = *reinterpret_cast<const half4_t*>(vr + kb);
-        half8_t f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          f[e] = (!tail || key0 + ka + e <= pmax) ? va[e] : (half_t)0;
-          f[4 + e] = (!tail || key0 + kb + e <= pmax) ? vb[e] : (half_t)0;
-        }
-        return f;
-      };
-      attn_update_src(a, p0, wave, li, lg, qf, kfrag, vfrag, key0, m, l, o);
+      attn_update_lds(a, p0, p0, pmax, wave, li, lg, qf, b, key0, m, l, o);
     }
     // buffer (t + 1) % 2 was last read before this chunk's barrier
     if (t + 1 < nt) {
@@ -702,12 +794,14 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
     }
   }
   if (!owner) return;
+  l = quad_sum(l);
   float* po = part_o + ((int64_t)bg * nslots + slot) * nq_pad * kHd;
   float2* pml = part_ml + ((int64_t)bg * nslots + slot) * nq_pad;
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) po[(int64_t)(16 * wave + 4 * lg + i) * kHd + 16 * dt + li] = o[dt][i];
+    for (int i = 0; i < 4; ++i)
+      if (16 * wave + 4 * lg + i < a.nq) po[(16 * wave + 4 * lg + i) * kHd + 16 * dt + li] = o[dt][i];
   if (lg == 0) pml[16 * wave + li] = make_float2(m, l);
 }
 
@@ -797,7 +891,7 @@ constexpr int kRopeRows = 16;
 __global__ __launch_bounds__(256) void prefill_rope_kernel(const float* __restrict__ qkv,
                                                            const uint16_t* __restrict__ bias, int hq, int hkv, int rps,
                                                            const int32_t* __restrict__ pos_base, int pos_offset,
-                                                           int64_t len_bound, int64_t capacity, double theta,
+                                                           int64_t len_bound, int64_t capacity, RopeBase base,
                                                            uint16_t* __restrict__ q_out, uint16_t* __restrict__ kc,
                                                            uint16_t* __restrict__ vc, int32_t* __restrict__ status) {
   __shared__ float2 tab[kRopeRows][64];
@@ -805,7 +899,7 @@ __global__ __launch_bounds__(256) void prefill_rope_kernel(const float* __restri
   const int nr = rps - j0 < kRopeRows ? rps - j0 : kRopeRows;
   const int t = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t p0 = (int64_t)pos_base[bi] + pos_offset + j0;
-  const double freq = rope_freq(t, theta);
+  const double freq = rope_freq(t, base);
   for (int r = wave; r < nr; r += 4) tab[r][t] = rope_cos_sin(p0 + r, freq);
   __syncthreads();
   const int nh = hq + 2 * hkv, share = blockIdx.z, shares = gridDim.z;
@@ -939,29 +1033,13 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(2))
     lds_barrier();
     const half_t* b = lbuf + (t & 1) * kLdsChunk;
     if (owner && key0 <= p0 + 16 * qt + 15) {  // uniform: the tile's last row reaches the chunk
-      const bool tail = key0 + kChunk - 1 > pmax;  // values of keys after pmax are zeroed (stale entries)
-      auto kfrag = [&](int kt, int s4) {
-        return *reinterpret_cast<const half8_t*>(b + (16 * kt + li) * kLdsKeyStride + 32 * lg + 8 * s4);
-      };
-      auto vfrag = [&](int t2, int dt) {
-        const int ka = 32 * t2 + 4 * lg, kb = ka + 16;
-        const half_t* vr = b + 64 * kLdsKeyStride + (16 * dt + li) * kLdsValStride;
-        const half4_t va = *reinterpret_cast<const half4_t*>(vr + ka);
-        const half4_t vb = *reinterpret_cast<const half4_t*>(vr + kb);
-        half8_t f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          f[e] = (!tail || key0 + ka + e <= pmax) ? va[e] : (half_t)0;
-          f[4 + e] = (!tail || key0 + kb + e <= pmax) ? vb[e] : (half_t)0;
-        }
-        return f;
-      };
-      attn_update_src(a, p0, qt, li, lg, qf, kfrag, vfrag, key0, m, l, o);
+      attn_update_lds(a, p0, p0 + 16 * qt, pmax, qt, li, lg, qf, b, key0, m, l, o);
     }
     // buffer (t + 1) % 2 was last read before this chunk's barrier
     if (t + 1 < nt) store_chunk(lbuf + ((t + 1) & 1) * kLdsChunk);
   }
   if (!owner) return;
+  l = quad_sum(l);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = 16 * qt + 4 * lg + i;
@@ -1118,23 +1196,34 @@ hipError_t launch_add_rmsnorm(float* h, const float* delta, int64_t m, int hidde
   return hipGetLastError();
 }
 
+namespace {
+RopeBase rope_base(double theta) {
+  const long double ln = std::log((long double)theta);
+  const double hi = (double)ln;
+  return {hi, (double)(ln - (long double)hi)};
+}
+}  // namespace
+
 hipError_t launch_rope_kv(const float* qkv, const uint16_t* bias, int m, int hq, int hkv, int rps,
                           const int32_t* pos_base, int pos_offset, int64_t len_bound, int64_t capacity, double theta,
                           uint16_t* q_out, uint16_t* kc, uint16_t* vc, int32_t* status, hipStream_t stream) {
   hipLaunchKernelGGL(rope_kv_kernel, dim3((unsigned)m, (unsigned)(hq + 2 * hkv)), dim3(64), 0, stream, qkv, bias, hq,
-                     hkv, rps, pos_base, pos_offset, len_bound, capacity, theta, q_out, kc, vc, status);
+                     hkv, rps, pos_base, pos_offset, len_bound, capacity, rope_base(theta), q_out, kc, vc, status);
   return hipGetLastError();
 }
 
 namespace {
-// Chunks per wavefront: about 512 wavefronts in all (two per CU) once the
-// cache is long enough, at most 16 chunks each; a single chunk when the
-// block has more than 4 query tiles.
+// Chunks per workgroup, at most 16: enough for one workgroup per CU, or two
+// where the block has one query tile (whose partial sums are small); a single
+// chunk when it has more than 4 tiles.  More slots cost more than they overlap:
+// every one writes its rows' fp32 sums for the merge to read (5 rows x 28 heads,
+// 8192 positions, 256 / 512 workgroups: 18.8 / 27.1 us; 4 x 9 rows 28.9 / 30.5; 8
+// sequences x 1 row, 4096 positions: 23.7 / 22.6).
 int attention_span(int b, int hq, int hkv, int rps, int64_t len_bound) {
   const int64_t nch = (len_bound + kChunk - 1) / kChunk;
   const int nqt = (rps * (hq / hkv) + 15) / 16;
   if (nqt > 4) return 1;
-  int64_t span = nch * b * hkv / 512;
+  int64_t span = nch * b * hkv / (nqt > 1 ? 256 : 512);
   span = span < 1 ? 1 : (span > 16 ? 16 : span);
   return (int)span;
 }
@@ -1189,7 +1278,7 @@ hipError_t launch_rope_attention(const float* qkv, const uint16_t* bias, int b, 
   float* part_o = static_cast<float*>(ws);
   float2* part_ml = reinterpret_cast<float2*>(part_o + (size_t)b * hkv * nslots * nq_pad * kHd);
   const size_t lds = ((size_t)2 * kLdsChunk + (size_t)2 * rps * kHd) * sizeof(uint16_t);
-  const RopeSrc rs{qkv, bias, theta, len_bound, kc, vc, status};
+  const RopeSrc rs{qkv, bias, rope_base(theta), len_bound, kc, vc, status};
   hipLaunchKernelGGL(attn_chunk_lds_kernel<true>, dim3((unsigned)nslots, (unsigned)(b * hkv)), dim3(kLdsThreads), lds,
                      stream, nullptr, kc, vc, hq, hkv, rps, capacity, pos_base, pos_offset, nslots, span, nq_pad,
                      part_o, part_ml, rs);
@@ -1206,7 +1295,7 @@ hipError_t launch_prefill_rope_kv(const float* qkv, const uint16_t* bias, int b,
   // shares of the heads: about four workgroups per CU
   int64_t shares = (int64_t)cu_count() * 4 / ((int64_t)blocks * b);
   shares = shares < 1 ? 1 : (shares > 8 ? 8 : shares);
-  hipLaunchKernelGGL(prefill_rope_kernel, dim3((unsigned)blocks, (unsigned)b, (unsigned)shares), dim3(256), 0, stream, qkv, bias, hq, hkv, rps, pos_base, pos_offset, len_bound, capacity, theta, q_out, kc,
+  hipLaunchKernelGGL(prefill_rope_kernel, dim3((unsigned)blocks, (unsigned)b, (unsigned)shares), dim3(256), 0, stream, qkv, bias, hq, hkv, rps, pos_base, pos_offset, len_bound, capacity, rope_base(theta), q_out, kc,
                      vc, status);
   return hipGetLastError();
 }
