@@ -163,7 +163,7 @@ def gemv_trace(path, variant, calls=None):
 
 # the FP16 verification kernels (linear_kernel<2, ...> is the FP16 instance; the
 # INT4 / FP8 instances serve draft projections)
-VERIFY_KERNELS = ("sq::linear_kernel<2,", "sq::gemm_rows_kernel", "sq::gemm_f16_kernel")
+VERIFY_KERNELS = ("sq::linear_kernel<2,", "sq::gemm_rows_kernel", "sq::tile_kernel<2,")
 REDUCE_KERNEL = "sq::slice_reduce_kernel"
 
 
