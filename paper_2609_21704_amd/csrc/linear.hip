@@ -219,18 +219,21 @@ struct XStage {
 
 __device__ __forceinline__ half8_t as_h8(u32x4 v) { return __builtin_bit_cast(half8_t, v); }
 
-// (several activation tiles hold more registers; a CU runs one workgroup of 8
-// wavefronts, two per SIMD)
 // Workgroup meeting slots of one-slice launches at few rows (256 workgroups, m <= 8), empty between launches:
 // such calls need no workspace, also as a first call inside a stream capture.
 constexpr size_t kMeetSlots = 256 * 8 * 16;
 static __device__ unsigned long long meet_slots[kMeetSlots];
 
-template <int KIND, int NW, int MT>
+// (several activation tiles hold more registers; a CU runs one workgroup of 8
+// wavefronts, two per SIMD)
+// ACC: y is added to.  An instance of its own, because a branch that may read
+// y makes the compiler wait for all loads where the branches meet, the next
+// unit's weights among them (11264 x 2048 FP8 at m = 36: 19.9 -> 19.4 us).
+template <int KIND, int NW, int MT, bool ACC>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : 2)))
 void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t kslice, const uint8_t* __restrict__ w,
                    const uint16_t* __restrict__ scales16, const uint16_t* __restrict__ zeros16,
-                   const float* __restrict__ scales32, int64_t n, void* __restrict__ y, int out_mode,
+                   const float* __restrict__ scales32, int64_t n, void* __restrict__ y, int f16_out,
                    float* __restrict__ split_out, int64_t nwg_max, int chunk_units, unsigned long long* xchg,
                    unsigned long long* slice_xchg, int direct) {
   extern __shared__ __align__(16) char smem[];
@@ -301,9 +304,9 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
     if constexpr (KIND == kW8) val *= scales32[row];
     if (split_out)
       split_out[((int64_t)split * M + m) * n + row] = val;
-    else if (out_mode == kOutF16)
+    else if (f16_out)
       reinterpret_cast<uint16_t*>(y)[(int64_t)m * n + row] = f32_to_f16_bits(val);
-    else if (out_mode == kOutAcc)
+    else if (ACC)
       reinterpret_cast<float*>(y)[(int64_t)m * n + row] += val;
     else
       reinterpret_cast<float*>(y)[(int64_t)m * n + row] = val;
@@ -318,7 +321,7 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
     // sum's full size (3584 k, relative to 64 bits, before / after: FP8 1.63e-7 / 0.82e-7,
     // FP16 1.55e-7 / 1.20e-7, INT4 0.78e-7 / 0.68e-7)
     // (from three row tiles on the registers are worth more: 37888 x 3584 INT4 at m = 36
-    // 40.6 us, with two sums 41.4; four tiles would spill)
+    // 40.6 us, with two sums 41.4)
     constexpr bool kTwo = MT < 3;
     float4_t acc[MT], acc2[MT];
 #pragma unroll
@@ -430,7 +433,7 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
           if (kTwo) acc[mt] += acc2[mt];
         if (MT > 1 && direct) {
           // the chunk is a whole task of this workgroup: its values are finished
-          // here (meeting the other K slice's in a 64-bit slot when there are two)
+          // here, or this K slice's partial outputs are
           const int64_t row = t * 16 + col;
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt)
@@ -438,16 +441,7 @@ void linear_kernel(const uint16_t* __restrict__ x, int M, int64_t k, int64_t ksl
             for (int r = 0; r < 4; ++r) {
               const int m = mt * 16 + 4 * q + r;
               if (m >= M || row >= n) continue;
-              float val = acc[mt][r];
-              if (slice_xchg) {
-                unsigned long long* sl = slice_xchg + (size_t)m * n + row;
-                const unsigned long long oth = atomicExch(sl, (1ull << 32) | __builtin_bit_cast(uint32_t, val));
-                if (oth == 0ull) continue;  // the other slice finishes this value
-                const float o = __builtin_bit_cast(float, (uint32_t)(oth & 0xFFFFFFFFull));
-                val = split == 0 ? val + o : o + val;
-                atomicExch(sl, 0ull);  // empty for the next launch
-              }
-              store_y(row, m, val);
+              store_y(row, m, acc[mt][r]);
             }
         } else {  // its partial sum goes to the chunk's slot
 #pragma unroll
@@ -599,9 +593,10 @@ hipError_t slice_reduce(const float* partial, int splits, int64_t mn, void* y, i
 }
 
 constexpr int64_t kChunkMinUnits = 4;  // units per chunk (measured on large matrices: 4 beats 1 and 2)
-// One workgroup per CU. Up to 16 rows the chunk partial sums may take 40 KB (151936 rows at m = 16 need 38:
-// 381 -> 197 us in FP16, whole tasks per wavefront have no epilogue there); above, 32 KB and else whole tasks,
-// whose two K slices meet in registers (17920 x 1536 at m = 64 in FP16: 26 us, with 40 KB in chunks 46 us).
+// One workgroup per CU. Up to 16 rows, where whole tasks per wavefront (direct) have no instance, the chunk
+// partial sums may take 40 KB, 640 KB / m row blocks per CU (about 163000 rows at m = 16: 151936 rows in FP16
+// 381 -> 197 us). Above, 32 KB, and else the direct mode, whose activations get the rest of the LDS
+// (17920 x 1536 at m = 64 in FP16: 26 us in one K slice, with 40 KB in chunks 46 us).
 template <int MT>
 constexpr size_t kLdsTotal = MT == 1 ? 158 * 1024 : 150 * 1024;
 template <int MT>
@@ -612,6 +607,8 @@ hipError_t linear_launch(const uint16_t* x, int m, int64_t k, const uint8_t* w, 
                          const uint16_t* zeros16, const float* scales32, int64_t n, void* y, int out_mode,
                          bool direct, hipStream_t stream) {
   constexpr int64_t UK = (int64_t)kU * k_per_slab<KIND>();
+  constexpr bool kAccForm = KIND == kW4 && MT <= 2;  // only the INT4 draft's few rows are added to
+  if (out_mode == kOutAcc && !kAccForm) return hipErrorNotSupported;
   // K slices of whole units whose activations fit (2 bytes per k and row, plus a pad cell per row);
   // the direct mode keeps no chunk partial sums in LDS
   int64_t kmax = (int64_t)((kLdsTotal<MT> - (direct ? 0 : kPieceBudget<MT>)) / ((size_t)m * 2)) - 8;
@@ -631,13 +628,13 @@ hipError_t linear_launch(const uint16_t* x, int m, int64_t k, const uint8_t* w, 
   if (nwg_max < 1) nwg_max = 1;
   // chunks of kChunkMinUnits units, or of fewer where those would leave wavefronts
   // without one (a row block of 2048 x 1536 is three INT4 units: as one chunk, seven
-  // of eight wavefronts idled, 7.3 -> 6.0 us at m = 3; not with three or more row
-  // tiles, 11264 x 2048 FP8 at m = 36 19.4 -> 22.3), and longer ones where the
-  // partial sums ([chunks per workgroup][m][16] floats) exceed the budget;
+  // of eight wavefronts idled, 7.3 -> 6.0 us at m = 3; not with two or more row
+  // tiles, whose partial sums cost more: 11264 x 2048 FP8 at m = 32 16.6 us, with finer
+  // chunks 19.6, at m = 36 19.4 and 22.3), and longer ones where the partial sums ([chunks per workgroup][m][16] floats) exceed the budget;
   // direct: one chunk per task, no partial sums
   int64_t cmin = (ntask * S + nwg_max * NW - 1) / (nwg_max * NW);
   if (cmin > kChunkMinUnits) cmin = kChunkMinUnits;
-  int64_t C = direct ? S : (MT <= 2 ? cmin : kChunkMinUnits), nch_max = 0;
+  int64_t C = direct ? S : (MT == 1 ? cmin : kChunkMinUnits), nch_max = 0;
   for (;; ++C) {
     const int64_t J = (S + C - 1) / C;
     nch_max = (ntask * J + nwg_max - 1) / nwg_max;
@@ -670,9 +667,19 @@ hipError_t linear_launch(const uint16_t* x, int m, int64_t k, const uint8_t* w, 
   unsigned long long* xchg = reinterpret_cast<unsigned long long*>(slots);
   // more than half the LDS, so that a CU holds one workgroup
   const size_t lds_launch = lds < 81 * 1024 ? 81 * 1024 : lds;
-  hipLaunchKernelGGL((linear_kernel<KIND, NW, MT>), dim3((unsigned)nwg_max, (unsigned)splits), dim3(NW * 64),
-                     lds_launch, stream, x, m, k, kslice, w, scales16, zeros16, scales32, n, y, out_mode,
-                     split_out, nwg_max, (int)C, xchg, slice_meet ? xchg + wg_slots : nullptr, (int)direct);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nwg_max, (unsigned)splits), dim3(NW * 64), lds_launch, stream, x, m, k,
+                       kslice, w, scales16, zeros16, scales32, n, y, (int)(out_mode == kOutF16), split_out, nwg_max,
+                       (int)C, xchg, slice_meet ? xchg + wg_slots : nullptr, (int)direct);
+  };
+  if constexpr (kAccForm) {
+    if (out_mode == kOutAcc)
+      launch(linear_kernel<KIND, NW, MT, true>);
+    else
+      launch(linear_kernel<KIND, NW, MT, false>);
+  } else {
+    launch(linear_kernel<KIND, NW, MT, false>);
+  }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || splits == 1 || slice_meet) return err;
   return slice_reduce(split_out, splits, (int64_t)m * n, y, out_mode, stream);
