@@ -81,9 +81,15 @@ inline bool tile_takes(int64_t n, int64_t k) {
 inline bool tile_takes_long(int64_t n, int64_t k, int m, int lo, int hi) {
   return (n + 15) / 16 <= cu_count() && k <= 6144 && m >= lo && m <= hi;
 }
+// FP8: also short rows of more row blocks, from four activation rows (m = 3, GEMV / tile: 5504 x 2048 5.6 / 6.0,
+// 17920 x 1536 9.7 / 10.2) to sixteen, or ten of the largest (m = 16, tile / linear_kernel: 11264 x 2048 11.4 /
+// 11.5, 17920 x 1536 13.9 / 12.9), and long rows at five and six (1536 x 8960, m = 5: 11.1 / 13.6, m = 8: 13.6 /
+// 10.8).
 inline bool tile_takes_w8(int64_t n, int64_t k, int m) {
+  const int64_t cells = (n + 15) / 16 * k;
   return tile_takes(n, k) || tile_takes_long(n, k, m, 5, 16) ||
-         (m <= 16 && k <= 2048 && (n + 15) / 16 * k <= 1800000);
+         (m >= 4 && k <= 2048 && cells <= 1800000 && m <= (cells <= 1500000 ? 16 : 10)) ||
+         (m >= 5 && m <= 6 && (n + 15) / 16 <= cu_count() && k <= 9216);
 }
 
 // Verification over row blocks on the vector ALUs, 1 <= m <= 8; returns
