@@ -24,13 +24,15 @@
 // q_out / p_out.  A -inf logit is a masked token (probability 0).  A row
 // holding a NaN or +inf logit, or no finite logit, has no distribution: its
 // sequence gets n_accepted = next_token = -1 (and NaN rows in q_out / p_out).
-// Greedy reduces every row to its argmax in one kernel, whose last workgroup
-// per sequence takes the decisions.
+// Greedy reduces every row to the argmax of its chunks, and a second kernel
+// merges them and takes the decisions.
 //
 // Last workgroups are found by counting arrivals.  A workgroup publishes its
 // part with an agent-scope store, waits for that store and then adds to the
 // counter, so the one that completes the count sees every part; nobody waits
-// for another workgroup.  The counters are zero between launches: that workgroup resets its.
+// for another workgroup.  The counters lie in the call's scratch and the
+// statistics kernel clears them, so that a call depends on nothing that an
+// earlier one left behind.
 #include <math.h>
 
 #include <mutex>
@@ -225,23 +227,14 @@ __device__ __forceinline__ int64_t published(const int64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Arrival counters, zero between launches: set 0 for the calls on the
-// library's workspace, set 1 for the allocation-free call (the two may run on
-// different streams).  A launch covers at most kSlots rows or sequences.
-constexpr int kSlots = 65536;
-static __device__ int32_t arrivals[2][2][kSlots];
-
 // One thread's arrival, after its parts are published: true for the last of n
-// (every part is visible to it; the counter is reset).  The parts are written
-// through to the level all XCDs share, so the wait for their stores is all
-// the release needs (a release fence would also write back the whole L2,
-// measured at about 2 us), and they are read from there.
+// (every part is visible to it).  The parts are written through to the level
+// all XCDs share, so the wait for their stores is all the release needs (a
+// release fence would also write back the whole L2, measured at about 2 us),
+// and they are read from there.
 __device__ __forceinline__ bool arrive(int32_t* counter, int n) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if (n == 1) return true;
-  if (__hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n - 1) return false;
-  __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return true;
+  return n == 1 || __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
 }
 
 // Row r of the combined row space: target rows first ([b][kd+1] order), then
@@ -331,9 +324,12 @@ __device__ __forceinline__ void load_row_chunk(const float* __restrict__ l, int 
 template <bool kOne>
 __global__ __launch_bounds__(64) void stats_kernel(const float* __restrict__ draft, const float* __restrict__ target,
                                                    int64_t rows_t, int v, float temp, int nchunk,
-                                                   double2* __restrict__ stats) {
+                                                   double2* __restrict__ stats, int32_t* __restrict__ counters,
+                                                   int rows_s) {
   const int64_t row = blockIdx.x / nchunk;
   const int c = blockIdx.x % nchunk;
+  // the arrival counter of a sequence (rows_s target rows), for the accept kernel
+  if (counters && c == 0 && row < rows_t && row % rows_s == 0 && threadIdx.x == 0) counters[row / rows_s] = 0;
   float x[kCPer];
   load_row_chunk(row_ptr(draft, target, rows_t, row, v), c, v, x);
   const Soft<kOne> sf(temp);
@@ -382,35 +378,36 @@ __global__ __launch_bounds__(64) void probs_kernel(const float* __restrict__ dra
   }
 }
 
-// 2. per (sequence, chunk): decisions, first rejection, chunk share of the draw weights.
+// 2. per (sequence, G consecutive chunks): decisions, first rejection, the chunks' shares of the draw weights.
 // zs[(s * nchunk + c) * 2 + 0] = sum of R over the chunk for the draw row
 // (residual max(0, p_n - q_n) when n < kd, else p_kd); [.. + 1] = sum of R for
 // p_n (the fallback when the residual mass is zero).  The last workgroup of a
 // sequence draws.  A sequence with a row without a distribution gets -1.
-// blockIdx.x = (s - s0) * nchunk + c.
+// blockIdx.x = s * groups + group, groups = ceil(nchunk / G).
 // Loads that wait for nothing computed here go out together, so that their
 // round trips overlap: the draft tokens and their uniforms, the first rows of
-// chunk partials, the logits at the tokens, and this chunk of p_0 and q_0
+// chunk partials, the logits at the tokens, and the first chunk of p_0 and q_0
 // (the draw rows when the first draft token is rejected, or when kd = 0).
-// Every one of them is unconditional (indices clamped, the value ignored
-// where it does not apply).
+// Indices are clamped and a value that does not apply is ignored, so that no
+// load waits for a condition computed from another.
 template <bool kWide, bool kOne>
 __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restrict__ draft,
                                                           const float* __restrict__ target,
                                                           const int32_t* __restrict__ tokens,
                                                           const uint32_t* __restrict__ u24, int b, int kd, int v,
                                                           float temp, int nchunk, const double2* __restrict__ stats,
-                                                          int64_t* __restrict__ zs, int s0, int set,
+                                                          int64_t* __restrict__ zs, int32_t* __restrict__ counters,
+                                                          int G, int groups,
                                                           int32_t* __restrict__ n_accepted,
                                                           int32_t* __restrict__ next_token) {
   constexpr int kBatch = 3;  // rows of partials a wavefront holds at once
   __shared__ double sL[129], sS[129];
   __shared__ int sAcc[64];
-  __shared__ int64_t sh0[4], sh1[4];
+  __shared__ int64_t sh0[4], sh1[4], sz[2][2][4];
   __shared__ int sLast, sChunk;
   __shared__ int64_t sOff;
-  const int s = s0 + blockIdx.x / nchunk;
-  const int c = blockIdx.x % nchunk;
+  const int s = blockIdx.x / groups;
+  const int c0 = (int)(blockIdx.x % groups) * G, c1 = min(c0 + G, nchunk);  // this workgroup's chunks
   const int w = threadIdx.x >> 6;
   const int nrows = 2 * kd + 1;
   const int64_t rows_t = (int64_t)b * (kd + 1);
@@ -432,19 +429,19 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   auto load_batch = [&](int r0) {
 #pragma unroll
     for (int j = 0; j < kBatch; ++j)
-      load_cells(stats + row_of(min(r0 + 4 * j, nrows - 1)) * nchunk, nchunk, e[j]);
+      if (r0 + 4 * j < nrows) load_cells(stats + row_of(r0 + 4 * j) * nchunk, nchunk, e[j]);
   };
   load_batch(w);
-  // this chunk of p_0 and q_0 (of p_0 twice when kd = 0), thread t holding
+  // a chunk of p_0 and q_0 (of p_0 twice when kd = 0), thread t holding
   // logits t, t + 256, ...
   float pv[kPer], qv[kPer];
   const float* q0 = kd > 0 ? draft + (int64_t)s * v : trow;
-  auto load_chunk = [&](const float* row, float (&dst)[kPer]) {
+  auto load_chunk = [&](const float* row, int c, float (&dst)[kPer]) {
 #pragma unroll
     for (int k = 0; k < kPer; ++k) dst[k] = row[min(c * kChunk + k * kThreads + (int)threadIdx.x, v - 1)];
   };
-  load_chunk(trow, pv);
-  load_chunk(q0, qv);
+  load_chunk(trow, c0, pv);
+  load_chunk(q0, c0, qv);
   const bool tok_ok = dlane && xraw >= 0 && xraw < v;
   const int xi = tok_ok ? xraw : 0;
   const float lpt = trow[(int64_t)di * v + xi];
@@ -475,7 +472,7 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   for (int rr = threadIdx.x & 63; rr < nrows; rr += 64) invalid |= isnan(sS[rr]) ? 1 : 0;
   invalid = __any(invalid);
   if (invalid) {  // uniform across the sequence's workgroups
-    if (threadIdx.x == 0 && c == 0) {
+    if (threadIdx.x == 0 && c0 == 0) {
       n_accepted[s] = -1;
       next_token[s] = -1;
     }
@@ -503,37 +500,54 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   const double Lp = sL[n], Sp = sS[n], rSp = 1.0 / Sp;
   const bool resid = n < kd;
   const double Lq = resid ? sL[kd + 1 + n] : 0.0, Sq = resid ? sS[kd + 1 + n] : 1.0, rSq = 1.0 / Sq;
+  const float* lp = trow + (int64_t)n * v;  // the draw rows
+  const float* lq = resid ? draft + ((int64_t)n * b + s) * v : lp;
   if (n > 0) {  // uniform across the block; n = 0 uses the rows loaded ahead
-    load_chunk(trow + (int64_t)n * v, pv);
-    if (resid) load_chunk(draft + ((int64_t)n * b + s) * v, qv);
+    load_chunk(lp, c0, pv);
+    if (resid) load_chunk(lq, c0, qv);
   }
-  int64_t z0 = 0, z1 = 0;
+  for (int c = c0; c < c1; ++c) {
+    float pn[kPer] = {}, qn[kPer] = {};  // the next chunk's logits, on their way meanwhile
+    if (c + 1 < c1) {
+      load_chunk(lp, c + 1, pn);
+      if (resid) load_chunk(lq, c + 1, qn);
+    }
+    int64_t z0 = 0, z1 = 0;
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int j = c * kChunk + k * kThreads + threadIdx.x;
-    if (j >= v) break;
-    const float p = prob32(pv[k], sf, Lp, Sp, rSp);
-    if (resid) {
-      const float q = prob32(qv[k], sf, Lq, Sq, rSq);
-      const double r = (double)p - (double)q;
-      z0 += grid_weight(r > 0.0 ? r : 0.0);
-      z1 += grid_weight((double)p);
-    } else {
-      z0 += grid_weight((double)p);
+    for (int k = 0; k < kPer; ++k) {
+      const int j = c * kChunk + k * kThreads + threadIdx.x;
+      if (j >= v) break;
+      const float p = prob32(pv[k], sf, Lp, Sp, rSp);
+      if (resid) {
+        const float q = prob32(qv[k], sf, Lq, Sq, rSq);
+        const double r = (double)p - (double)q;
+        z0 += grid_weight(r > 0.0 ? r : 0.0);
+        z1 += grid_weight((double)p);
+      } else {
+        z0 += grid_weight((double)p);
+      }
+    }
+    z0 = wave_sum_i64(z0);
+    if (resid) z1 = wave_sum_i64(z1);
+    int64_t(&sw)[2][4] = sz[c & 1];  // (its last reader is two barriers back)
+    if ((threadIdx.x & 63) == 0) {
+      sw[0][w] = z0;
+      sw[1][w] = z1;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int64_t* zc = zs + ((int64_t)s * nchunk + c) * 2;
+      publish(zc, (sw[0][0] + sw[0][1]) + (sw[0][2] + sw[0][3]));
+      publish(zc + 1, (sw[1][0] + sw[1][1]) + (sw[1][2] + sw[1][3]));
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      pv[k] = pn[k];
+      qv[k] = qn[k];
     }
   }
-  z0 = wave_sum_i64(z0);
-  if (resid) z1 = wave_sum_i64(z1);
-  if ((threadIdx.x & 63) == 0) {
-    sh0[w] = z0;
-    sh1[w] = z1;
-  }
-  __syncthreads();
   if (threadIdx.x == 0) {
-    int64_t* zc = zs + ((int64_t)s * nchunk + c) * 2;
-    publish(zc, (sh0[0] + sh0[1]) + (sh0[2] + sh0[3]));
-    publish(zc + 1, (sh1[0] + sh1[1]) + (sh1[2] + sh1[3]));
-    sLast = arrive(&arrivals[set][0][s - s0], nchunk);
+    sLast = arrive(counters + s, groups);
     sChunk = -1;
   }
   __syncthreads();
@@ -607,8 +621,7 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   }
   const int64_t off = sOff;
   const bool both = resid && which == 0;
-  const float* lp = trow + (int64_t)n * v;
-  const float* lq = both ? draft + ((int64_t)n * b + s) * v : lp;
+  if (!both) lq = lp;
   int64_t R[kPer];
   int64_t local = 0;
   const int beg = chunk * kChunk + threadIdx.x * kPer;
@@ -655,11 +668,10 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
 // Greedy.  A row's argmax is the largest 64-bit key (ordered logit, inverted
 // index): the largest finite logit, its smallest index; 0 when it has no
 // finite logit, all ones when it holds a NaN or +inf.  A workgroup takes
-// kGreedyChunk logits of a row; the row's last workgroup merges the chunks'
-// keys and publishes the row's, and (kDecide) the sequence's last row takes
-// the decisions.  (Four sequences of 151936 logits, per call: 25.9 -> 8.9 us;
-// one thread per row walked the chunks in a second kernel before.)
-// blockIdx.x = (row - row0) * nchunk + c, rows_s rows per sequence.
+// kGreedyChunk logits of a row and stores their key; greedy_kernel merges a
+// sequence's rows, a wavefront each, and takes the decisions (four sequences,
+// 151936 logits: draws 6.2 us, accept calls of four drafts 6.7; with last
+// workgroups found by counting arrivals instead, twice per call, 7.5 and 14.0).
 constexpr int kGreedyPer = 16;
 constexpr int kGreedyChunk = kThreads * kGreedyPer;
 constexpr uint64_t kBadKey = ~0ull;
@@ -684,17 +696,15 @@ __device__ uint64_t block_key_max(uint64_t k, uint64_t* sh) {
   return a > b ? a : b;
 }
 
-template <bool kDecide>
-__global__ __launch_bounds__(kThreads) void argmax_kernel(const float* __restrict__ target,
-                                                          const int32_t* __restrict__ tokens, int b, int kd, int v,
-                                                          int nchunk, int64_t row0, int rows_s, int set,
-                                                          int64_t* __restrict__ keys, int64_t* __restrict__ row_keys,
+// keys[row][chunk]; blockIdx.x = (row - row0) * nchunk + chunk.  kDraw: one
+// chunk and one row per sequence (a draw), whose key is the decision.
+template <bool kDraw>
+__global__ __launch_bounds__(kThreads) void argmax_kernel(const float* __restrict__ target, int v, int nchunk,
+                                                          int64_t row0, int64_t* __restrict__ keys,
                                                           int32_t* __restrict__ n_accepted,
                                                           int32_t* __restrict__ next_token) {
   __shared__ uint64_t sh[4];
-  __shared__ int sLast;
-  const int lrow = blockIdx.x / nchunk;  // row of this launch
-  const int64_t row = row0 + lrow;
+  const int64_t row = row0 + blockIdx.x / nchunk;
   const int c = blockIdx.x % nchunk;
   const float* l = target + row * v;
   float x[kGreedyPer];
@@ -710,44 +720,49 @@ __global__ __launch_bounds__(kThreads) void argmax_kernel(const float* __restric
     key = k > key ? k : key;
   }
   key = block_key_max(key, sh);
-  if (nchunk > 1) {
-    if (threadIdx.x == 0) {
-      publish(keys + row * nchunk + c, (int64_t)key);
-      sLast = arrive(&arrivals[set][0][lrow], nchunk);
-    }
-    __syncthreads();
-    if (!sLast) return;  // uniform across the block
-    key = 0;
-    for (int i = threadIdx.x; i < nchunk; i += kThreads) {
-      const uint64_t k = (uint64_t)published(keys + row * nchunk + i);
-      key = k > key ? k : key;
-    }
-    key = block_key_max(key, sh);
+  if (threadIdx.x != 0) return;
+  if constexpr (kDraw) {
+    const int arg = key_index(key);
+    n_accepted[row] = arg < 0 ? -1 : 0;
+    next_token[row] = arg;
+  } else {
+    keys[row * nchunk + c] = (int64_t)key;
   }
-  if (!kDecide) {
-    if (threadIdx.x == 0) row_keys[row] = (int64_t)key;
-    return;
+}
+
+// A row's key from those of its chunks, by one wavefront (every lane receives it).
+__device__ __forceinline__ uint64_t row_key(const int64_t* k, int nchunk) {
+  uint64_t key = 0;
+  for (int i = threadIdx.x & 63; i < nchunk; i += 64) {
+    const uint64_t o = (uint64_t)k[i];
+    key = o > key ? o : key;
   }
-  const int64_t s = row / rows_s;  // rows_s = kd + 1
-  if (threadIdx.x == 0) {
-    publish(row_keys + row, (int64_t)key);
-    sLast = arrive(&arrivals[set][1][lrow / rows_s], rows_s);
+  return wave_all(key, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
+}
+
+constexpr int kMergeThreads = 1024;  // 16 rows at a time
+
+__global__ __launch_bounds__(kMergeThreads) void greedy_kernel(const int32_t* __restrict__ tokens, int b, int kd,
+                                                               int nchunk, const int64_t* __restrict__ keys,
+                                                               int32_t* __restrict__ n_accepted,
+                                                               int32_t* __restrict__ next_token) {
+  __shared__ int sArg[65];
+  const int s = blockIdx.x, i = threadIdx.x;
+  const int32_t xt = i < kd ? tokens[(int64_t)i * b + s] : 0;  // (kd <= 64)
+  for (int r = i >> 6; r <= kd; r += blockDim.x >> 6) {
+    const int arg = key_index(row_key(keys + ((int64_t)s * (kd + 1) + r) * nchunk, nchunk));
+    if ((i & 63) == 0) sArg[r] = arg;
   }
   __syncthreads();
-  if (!sLast || threadIdx.x >= 64) return;
-  // position i's greedy token on lane i (kd <= 64: lane 0 also takes position kd)
-  const int i = threadIdx.x;
-  const int64_t* rk = row_keys + s * rows_s;
-  const int arg = i < kd ? key_index((uint64_t)published(rk + i)) : 0;
-  const int last = key_index((uint64_t)published(rk + kd));
+  if (i >= 64) return;
+  // position i's greedy token on lane i (lane 0 also takes position kd)
+  const int arg = i < kd ? sArg[i] : 0, last = sArg[kd];
   const bool invalid = __any(arg < 0 || last < 0);
-  const int32_t xt = i < kd ? tokens[(int64_t)i * b + s] : 0;
   const uint64_t rej = __ballot(i < kd && xt != arg);  // (arg is in [0, v): so is an accepted token)
   const int n = rej ? __ffsll((unsigned long long)rej) - 1 : kd;
-  const int tok = n < kd ? __shfl(arg, n, 64) : last;
   if (i == 0) {
     n_accepted[s] = invalid ? -1 : n;
-    next_token[s] = invalid ? -1 : tok;
+    next_token[s] = invalid ? -1 : sArg[n];
   }
 }
 
@@ -1177,18 +1192,19 @@ static_assert(kChunk == kMThreads && kChunk % kThreads == 0, "the walk draws fro
 
 // Greedy (T = 0) over several chains: per sequence, the argmax of the lowest
 // alive chain's row at each depth is accepted when an alive chain drafted it.
-__global__ __launch_bounds__(kThreads) void multi_greedy_kernel(const int32_t* __restrict__ tokens, int b, int c,
-                                                                int kd, const int64_t* __restrict__ row_keys,
-                                                                int32_t* __restrict__ n_accepted,
-                                                                int32_t* __restrict__ next_token,
-                                                                int32_t* __restrict__ chain) {
+__global__ __launch_bounds__(kMergeThreads) void multi_greedy_kernel(const int32_t* __restrict__ tokens, int b, int c,
+                                                                     int kd, int nchunk,
+                                                                     const int64_t* __restrict__ keys,
+                                                                     int32_t* __restrict__ n_accepted,
+                                                                     int32_t* __restrict__ next_token,
+                                                                     int32_t* __restrict__ chain) {
   __shared__ int sArg[64 * 65];
   const int s = blockIdx.x;
   const int rows = c * (kd + 1);
   int bad = 0;
-  for (int r = threadIdx.x; r < rows; r += kThreads) {
-    const int a = key_index((uint64_t)row_keys[(int64_t)s * rows + r]);
-    sArg[r] = a;
+  for (int r = threadIdx.x >> 6; r < rows; r += kMergeThreads / 64) {
+    const int a = key_index(row_key(keys + ((int64_t)s * rows + r) * nchunk, nchunk));
+    if ((threadIdx.x & 63) == 0) sArg[r] = a;
     bad |= a < 0 ? 1 : 0;
   }
   if (__syncthreads_or(bad)) {
@@ -1225,14 +1241,14 @@ __global__ __launch_bounds__(kThreads) void multi_greedy_kernel(const int32_t* _
 
 namespace {
 
-// Scratch of one call: the greedy keys (one per chunk, one per row), or the row
-// statistics and the chunk weights (each part 256-byte aligned).  kSeqBytes
-// per sequence is held back beside them, as the size limit of the
-// allocation-free call counts it.
+// Scratch of one call: the greedy keys (one per chunk), or the row statistics,
+// the chunk weights (each part 256-byte aligned) and the arrival counters.  The
+// counters have kSeqBytes per sequence, of which they use four: what a call
+// needs, and so which calls the allocation-free form takes, stays as it was.
 constexpr size_t kSeqBytes = 40;
 struct AcceptScratch {
-  size_t st_bytes, zs_bytes, in_bytes;
-  size_t total() const { return st_bytes + zs_bytes + in_bytes; }
+  size_t st_bytes, zs_bytes, cnt_bytes;
+  size_t total() const { return st_bytes + zs_bytes + cnt_bytes; }
 };
 
 size_t pad256(size_t n) { return (n + 255) / 256 * 256; }
@@ -1242,36 +1258,25 @@ AcceptScratch accept_scratch(int b, int kd, int v, float temperature) {
   const int64_t rows_t = (int64_t)b * (kd + 1);
   AcceptScratch a;
   if (temperature == 0.0f) {
-    // (keys of kGreedyChunk logits, then the rows', fit in the keys of kChunk logits from two chunks on;
-    // a row of one chunk publishes no chunk key)
     a.st_bytes = pad256((size_t)rows_t * nchunk * sizeof(int64_t));
-    a.zs_bytes = a.in_bytes = 0;
+    a.zs_bytes = a.cnt_bytes = 0;
     return a;
   }
   const int64_t rows = rows_t + (int64_t)b * kd;
   a.st_bytes = pad256((size_t)rows * nchunk * sizeof(double2));
   a.zs_bytes = pad256((size_t)b * nchunk * 2 * sizeof(int64_t));
-  a.in_bytes = (size_t)b * kSeqBytes;
+  a.cnt_bytes = (size_t)b * kSeqBytes;
   return a;
 }
 
-// The rows' argmax keys into row_keys = ws [rows], chunk keys after them;
-// with tokens' decisions taken per sequence of kd + 1 rows (decide).
-hipError_t enqueue_argmax(const float* target, const int32_t* tokens, int b, int kd, int v, int64_t rows, bool decide,
-                          int set, int32_t* n_accepted, int32_t* next_token, char* ws, hipStream_t stream) {
+// The keys of every row's chunks of kGreedyChunk logits into keys [rows][chunks].
+hipError_t enqueue_argmax(const float* target, int v, int64_t rows, int64_t* keys, hipStream_t stream) {
   const int nchunk = (v + kGreedyChunk - 1) / kGreedyChunk;
-  int64_t* row_keys = reinterpret_cast<int64_t*>(ws);
-  int64_t* keys = row_keys + rows;
-  const int64_t slot_rows = decide ? kSlots / (kd + 1) * (kd + 1) : kSlots;  // rows per launch, whole sequences
-  for (int64_t r0 = 0; r0 < rows; r0 += slot_rows) {
-    const int64_t nr = rows - r0 < slot_rows ? rows - r0 : slot_rows;
-    const dim3 grid((unsigned)(nr * nchunk));
-    if (decide)
-      hipLaunchKernelGGL(argmax_kernel<true>, grid, dim3(kThreads), 0, stream, target, tokens, b, kd, v, nchunk, r0,
-                         kd + 1, set, keys, row_keys, n_accepted, next_token);
-    else
-      hipLaunchKernelGGL(argmax_kernel<false>, grid, dim3(kThreads), 0, stream, target, tokens, b, kd, v, nchunk, r0,
-                         1, set, keys, row_keys, n_accepted, next_token);
+  const int64_t per = (int64_t(1) << 23) / nchunk;  // rows per launch (a grid holds fewer than 2^32 threads)
+  for (int64_t r0 = 0; r0 < rows; r0 += per) {
+    const int64_t nr = rows - r0 < per ? rows - r0 : per;
+    hipLaunchKernelGGL(argmax_kernel<false>, dim3((unsigned)(nr * nchunk)), dim3(kThreads), 0, stream, target, v, nchunk,
+                       r0, keys, nullptr, nullptr);
   }
   return hipGetLastError();
 }
@@ -1279,32 +1284,42 @@ hipError_t enqueue_argmax(const float* target, const int32_t* tokens, int b, int
 // The accept kernels on the scratch `ws` (at least accept_scratch().total() bytes).
 hipError_t enqueue_accept(const float* draft, const float* target, const int32_t* tokens, const uint32_t* u24, int b,
                           int kd, int v, float temperature, int32_t* n_accepted, int32_t* next_token, float* q_out,
-                          float* p_out, char* ws, int set, hipStream_t stream) {
+                          float* p_out, char* ws, hipStream_t stream) {
   const int nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * (kd + 1);
   const AcceptScratch a = accept_scratch(b, kd, v, temperature);
-  if (temperature == 0.0f)
-    return enqueue_argmax(target, tokens, b, kd, v, rows_t, true, set, n_accepted, next_token, ws, stream);
+  if (temperature == 0.0f) {
+    if (kd == 0 && v <= kGreedyChunk) {
+      hipLaunchKernelGGL(argmax_kernel<true>, dim3((unsigned)b), dim3(kThreads), 0, stream, target, v, 1, 0, nullptr,
+                         n_accepted, next_token);
+      return hipGetLastError();
+    }
+    int64_t* keys = reinterpret_cast<int64_t*>(ws);
+    const hipError_t e = enqueue_argmax(target, v, rows_t, keys, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(greedy_kernel, dim3((unsigned)b), dim3(64 * (kd < 15 ? kd + 1 : 16)), 0, stream, tokens, b, kd,
+                       (v + kGreedyChunk - 1) / kGreedyChunk, keys, n_accepted, next_token);
+    return hipGetLastError();
+  }
   const int64_t rows = rows_t + (int64_t)b * kd;
   double2* stats = reinterpret_cast<double2*>(ws);
   int64_t* zs = reinterpret_cast<int64_t*>(ws + a.st_bytes);
+  int32_t* counters = reinterpret_cast<int32_t*>(ws + a.st_bytes + a.zs_bytes);
+  // chunks per workgroup of the accept kernel
+  const int64_t G = 1;
+  const int64_t groups = (nchunk + G - 1) / G;
   auto go = [&](auto one_tag) {
     constexpr bool One = decltype(one_tag)::value;
     hipLaunchKernelGGL(stats_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target, rows_t,
-                       v, temperature, nchunk, stats);
+                       v, temperature, nchunk, stats, counters, kd + 1);
     if (p_out || q_out)
       hipLaunchKernelGGL(probs_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target,
                          rows_t, v, temperature, nchunk, stats, q_out, p_out);
-    for (int s0 = 0; s0 < b; s0 += kSlots) {
-      const int ns = b - s0 < kSlots ? b - s0 : kSlots;
-      const dim3 grid((unsigned)((int64_t)ns * nchunk));
-      if (nchunk > 64 * kCells)
-        hipLaunchKernelGGL((accept_kernel<true, One>), grid, dim3(kThreads), 0, stream, draft, target, tokens, u24, b,
-                           kd, v, temperature, nchunk, stats, zs, s0, set, n_accepted, next_token);
-      else
-        hipLaunchKernelGGL((accept_kernel<false, One>), grid, dim3(kThreads), 0, stream, draft, target, tokens, u24, b,
-                           kd, v, temperature, nchunk, stats, zs, s0, set, n_accepted, next_token);
-    }
+    auto accept = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)(b * groups)), dim3(kThreads), 0, stream, draft, target, tokens, u24, b,
+                         kd, v, temperature, nchunk, stats, zs, counters, (int)G, (int)groups, n_accepted, next_token);
+    };
+    nchunk > 64 * kCells ? accept(accept_kernel<true, One>) : accept(accept_kernel<false, One>);
   };
   if (temperature == 1.0f)
     go(std::true_type{});
@@ -1354,7 +1369,7 @@ hipError_t launch_spec_accept(const float* draft, const float* target, const int
   const hipError_t e = workspace(accept_scratch(b, kd, v, temperature).total(), stream, &ws);
   if (e != hipSuccess) return e;
   return enqueue_accept(draft, target, tokens, u24, b, kd, v, temperature, n_accepted, next_token, q_out, p_out,
-                        static_cast<char*>(ws), 0, stream);
+                        static_cast<char*>(ws), stream);
 }
 
 hipError_t launch_spec_accept_noalloc(const float* draft, const float* target, const int32_t* tokens,
@@ -1366,14 +1381,14 @@ hipError_t launch_spec_accept_noalloc(const float* draft, const float* target, c
   const hipError_t e = noalloc_scratch(&ws);
   if (e != hipSuccess) return e;
   return enqueue_accept(draft, target, tokens, u24, b, kd, v, temperature, n_accepted, next_token, q_out, p_out, ws,
-                        1, stream);
+                        stream);
 }
 
 
 size_t spec_accept_multi_scratch_bytes(int b, int c, int kd, int v, float temperature) {
   const int64_t nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * c * (kd + 1);
-  if (temperature == 0.0f) return pad256((size_t)rows_t * (nchunk + 1) * sizeof(int64_t));
+  if (temperature == 0.0f) return pad256((size_t)rows_t * nchunk * sizeof(int64_t));
   const int64_t rows = rows_t + (int64_t)kd * b * c;
   // chunk statistics, merged statistics, chunk masses of p and of the residuals
   return pad256((size_t)rows * nchunk * sizeof(double2)) + pad256((size_t)rows * sizeof(double2)) +
@@ -1391,10 +1406,11 @@ hipError_t launch_spec_accept_multi(const float* draft, const float* target, con
   const int nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * c * (kd + 1);
   if (temperature == 0.0f) {
-    e = enqueue_argmax(target, tokens, b, kd, v, rows_t, false, 0, n_accepted, next_token, ws, stream);
+    e = enqueue_argmax(target, v, rows_t, reinterpret_cast<int64_t*>(ws), stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(multi_greedy_kernel, dim3((unsigned)b), dim3(kThreads), 0, stream, tokens, b, c, kd,
-                       reinterpret_cast<const int64_t*>(ws), n_accepted, next_token, chain);
+    hipLaunchKernelGGL(multi_greedy_kernel, dim3((unsigned)b), dim3(kMergeThreads), 0, stream, tokens, b, c, kd,
+                       (v + kGreedyChunk - 1) / kGreedyChunk, reinterpret_cast<const int64_t*>(ws), n_accepted,
+                       next_token, chain);
     return hipGetLastError();
   }
   const int64_t rows_d = (int64_t)kd * b * c, rows = rows_t + rows_d;
@@ -1413,7 +1429,7 @@ hipError_t launch_spec_accept_multi(const float* draft, const float* target, con
   auto go = [&](auto one_tag) {
     constexpr bool One = decltype(one_tag)::value;
     hipLaunchKernelGGL(stats_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target, rows_t,
-                       v, temperature, nchunk, stats);
+                       v, temperature, nchunk, stats, nullptr, 1);
     hipLaunchKernelGGL(multi_rows_kernel<One>, dim3((unsigned)(rows_t * nchunk)), dim3(64), 0, stream, a, stats, q_out,
                        p_out);
     for (int i = 1; rows_d > 0 && i < c; ++i)
