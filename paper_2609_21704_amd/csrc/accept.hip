@@ -1246,6 +1246,12 @@ namespace {
 // counters have kSeqBytes per sequence, of which they use four: what a call
 // needs, and so which calls the allocation-free form takes, stays as it was.
 constexpr size_t kSeqBytes = 40;
+
+// Workgroups of the accept kernel, about; more than one chunk each beyond that:
+// every workgroup merges its sequence's row statistics again, and its arrival
+// holds it for about 3 us (draws at 151936 logits, one chunk each / 512 / 1024
+// workgroups: 4 sequences 16.9 / 14.4 / 16.9 us, 16 38.6 / 20.9 / 23.0, 64 113 / 45.3 / 38.4).
+constexpr int64_t kAcceptBlocks = 512;
 struct AcceptScratch {
   size_t st_bytes, zs_bytes, cnt_bytes;
   size_t total() const { return st_bytes + zs_bytes + cnt_bytes; }
@@ -1306,7 +1312,7 @@ hipError_t enqueue_accept(const float* draft, const float* target, const int32_t
   int64_t* zs = reinterpret_cast<int64_t*>(ws + a.st_bytes);
   int32_t* counters = reinterpret_cast<int32_t*>(ws + a.st_bytes + a.zs_bytes);
   // chunks per workgroup of the accept kernel
-  const int64_t G = 1;
+  const int64_t G = ((int64_t)b * nchunk + kAcceptBlocks - 1) / kAcceptBlocks;
   const int64_t groups = (nchunk + G - 1) / G;
   auto go = [&](auto one_tag) {
     constexpr bool One = decltype(one_tag)::value;

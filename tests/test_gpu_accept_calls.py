@@ -26,6 +26,14 @@ def check(b, kd, v, temp, seed):
     return n
 
 
+# chunks of 1024 logits over all sequences: 512 (one per workgroup), 513 (two, the last workgroup with one), more
+# sequences than workgroups, several per workgroup with draws after acceptances
+@pytest.mark.parametrize("b,kd,v", [(1, 0, 524288), (1, 0, 524289), (171, 0, 3000), (600, 0, 1025), (130, 2, 4097),
+                                    (9, 3, 65537), (16, 1, 151936)])
+def test_spec_accept_chunks_per_workgroup(b, kd, v):
+    check(b, kd, v, 1.0, 300 + b + v)
+
+
 # one chunk of 4096 logits and one more logit, with and without drafts; more rows than wavefronts; 65 chunks of a row
 @pytest.mark.parametrize("b,kd,v", [(3, 0, 4096), (3, 0, 4097), (2, 1, 4096), (3, 15, 4097), (4, 16, 9000),
                                     (66, 64, 130), (2, 2, 262145)])
