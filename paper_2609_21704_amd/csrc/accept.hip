@@ -316,9 +316,10 @@ __device__ void wave_merge(const T& sf, const double2* st, int nchunk, double& L
 // the reductions and barriers were most of the instructions issued.
 constexpr int kCPer = kChunk / 64;  // logits per lane where a wavefront holds a chunk
 
-__device__ __forceinline__ void load_row_chunk(const float* __restrict__ l, int c, int v, float (&x)[kCPer]) {
+template <int N>
+__device__ __forceinline__ void load_row_chunk(const float* __restrict__ l, int c, int v, float (&x)[N]) {
 #pragma unroll
-  for (int e = 0; e < kCPer; ++e) x[e] = l[min(c * kChunk + e * 64 + (int)(threadIdx.x & 63), v - 1)];
+  for (int e = 0; e < N; ++e) x[e] = l[min(c * kChunk + e * (kChunk / N) + (int)threadIdx.x, v - 1)];
 }
 
 template <bool kOne>
@@ -403,7 +404,7 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   constexpr int kBatch = 3;  // rows of partials a wavefront holds at once
   __shared__ double sL[129], sS[129];
   __shared__ int sAcc[64];
-  __shared__ int64_t sh0[4], sh1[4], sz[2][2][4];
+  __shared__ int64_t sh0[4], sz[2][2][4];
   __shared__ int sLast, sChunk;
   __shared__ int64_t sOff;
   const int s = blockIdx.x / groups;
@@ -782,20 +783,24 @@ __global__ __launch_bounds__(kMergeThreads) void greedy_kernel(const int32_t* __
 // same rule applied to the fp32 distributions in any order.
 //
 // The candidates of a node (the chains sharing its prefix, in order) do not
-// depend on what is accepted elsewhere, so every node's residual masses Z can
-// be summed for all nodes and vocabulary chunks at once: multi_rows_kernel
-// gives every row's merged statistics, p's masses and the masses after a first
-// rejection, launch i = 1 .. c - 1 of multi_step_kernel the mass after the
-// rejection of a node's candidate i, which needs only the masses before it.  R
-// itself, and p and q unless they are asked for, are recomputed from the
-// logits where they are needed, never stored.  One workgroup per sequence
-// (multi_walk_kernel) then takes all decisions in parallel, walks the tree and
-// draws.  c + 1 launches over the whole chip replace a walk of up to c kd
-// passes over the vocabulary by one workgroup per sequence (two sequences,
-// four chains of four, 151936 logits, the whole call: 306 -> 75 us).
+// depend on what is accepted elsewhere, so all nodes and vocabulary chunks are
+// worked on at once: multi_rows_kernel gives every row's merged statistics,
+// p's masses, the masses after a first rejection and the first candidates'
+// tests; launch i = 1 .. c - 1 of multi_step_kernel the test of every node's
+// candidate i and, if that fails, the residual mass Z after it, which needs
+// only the masses before it.  A node that has accepted a candidate needs no
+// more: its workgroups leave at once.  R itself, and p and q unless they are
+// asked for, are recomputed from the logits where they are needed, not stored.
+// One workgroup per sequence (multi_walk_kernel) then walks the tree and draws.
+// A launch costs 2.5 us also where nothing is left to do, so that small
+// vocabularies take fewer of them, and the walk itself the candidates after
+// (walk_steps()).  Up to c + 2 launches over the whole chip replace a walk of
+// up to c kd passes over the vocabulary by one workgroup per sequence (two
+// sequences, four chains of four, 151936 logits, the whole call: 306 -> 63 us).
 constexpr int kMThreads = 1024;
 constexpr int kMWaves = kMThreads / 64;
 constexpr int kStepBlocks = 8192;  // workgroups of one step launch, about
+constexpr int kWalkLogits = 32768;  // rows whose later candidates the walk may take
 
 // q = m 2^e exactly (m < 2^24), from the bits of a finite q >= 0.
 __device__ __forceinline__ void split_f32(float q, uint64_t& m, int& e) {
@@ -860,16 +865,22 @@ __device__ __forceinline__ float prob(const Row& r, const T& sf, int y) {
 
 // Every call's rows and tables: ls [rows] merged statistics (target rows
 // first), zp [rows_t][nchunk] masses of p, zs [b][kd][c][nchunk] residual
-// masses.
+// masses after chain j's rejection, acc [b][kd][c] chain j's test.  An entry of
+// zs or acc means something only where the node's candidates before it (and
+// for zs chain j itself) have failed; of the others nothing is read into a result.
 struct MultiArgs {
   const float* draft;
   const float* target;
   const int32_t* tokens;
+  const uint32_t* u24;
   int b, c, kd, v, nchunk;
   float temp;
   double2* ls;
   int64_t* zp;
   int64_t* zs;
+  int32_t* acc;
+  int64_t* r;  // [b][v] R and q, where the walk takes candidates itself
+  float* q;
 };
 
 // A node: the chains of sequence s that share chain j's first d tokens, and
@@ -933,20 +944,23 @@ __device__ __forceinline__ int64_t wave_row_sum(const int64_t* r, int n) {
   return wave_sum_i64(t);
 }
 
-// Per (target row, chunk), one wavefront: the row's and its draft row's merged
+// Per (target row, chunk), by W wavefronts: the row's and its draft row's merged
 // statistics (by chunk 0), the chunk's mass of p and, for the rows with a
 // draft, of max(0, p - q): the mass after chain j's rejection if it is its
-// node's first candidate.  Copies of the distributions where asked for.
-template <bool kOne>
-__global__ __launch_bounds__(64) void multi_rows_kernel(MultiArgs a, const double2* __restrict__ stats,
+// node's first candidate, whose test the lane that holds its token takes.
+// Copies of the distributions where asked for.
+template <bool kOne, int W>
+__global__ __launch_bounds__(64 * W) void multi_rows_kernel(MultiArgs a, const double2* __restrict__ stats,
                                                         float* __restrict__ q_out, float* __restrict__ p_out) {
+  constexpr int N = kChunk / (64 * W);  // logits per thread
+  __shared__ int64_t sh[W];
   const int64_t row = blockIdx.x / a.nchunk;  // (s c + j) (kd + 1) + d
   const int ch = blockIdx.x % a.nchunk;
   const int d = (int)(row % (a.kd + 1));
   const int64_t sj = row / (a.kd + 1), rows_t = (int64_t)a.b * a.c * (a.kd + 1);
   const bool drafted = d < a.kd;
   const int64_t drow = drafted ? (int64_t)d * a.b * a.c + sj : 0;
-  float xp[kCPer], xq[kCPer];
+  float xp[N], xq[N];
   load_row_chunk(a.target + row * a.v, ch, a.v, xp);
   if (drafted) load_row_chunk(a.draft + drow * a.v, ch, a.v, xq);
   double Lp, Sp, Lq = 0.0, Sq = 1.0;
@@ -958,10 +972,18 @@ __global__ __launch_bounds__(64) void multi_rows_kernel(MultiArgs a, const doubl
     if (drafted) a.ls[rows_t + drow] = make_double2(Lq, Sq);
   }
   const double rSp = 1.0 / Sp, rSq = 1.0 / Sq;
+  const int64_t s = sj / a.c, j = sj - s * a.c, cell = (s * a.kd + d) * a.c + j;
+  int x = -1;
+  double u = 0.0;
+  if (drafted) {
+    x = a.tokens[drow];
+    u = ldexp((double)(a.u24[s * (a.c * a.kd + 1) + d * a.c + j] & 0xFFFFFFu), -24);
+    if (ch == 0 && threadIdx.x == 0 && (x < 0 || x >= a.v)) a.acc[cell] = 0;  // no row's token: fails
+  }
   int64_t zp = 0, zr = 0;
 #pragma unroll
-  for (int e = 0; e < kCPer; ++e) {
-    const int y = ch * kChunk + e * 64 + (int)threadIdx.x;
+  for (int e = 0; e < N; ++e) {
+    const int y = ch * kChunk + e * (64 * W) + (int)threadIdx.x;
     if (y < a.v) {
       const float p = prob32(xp[e], sf, Lp, Sp, rSp);
       zp += grid_weight((double)p);
@@ -970,24 +992,37 @@ __global__ __launch_bounds__(64) void multi_rows_kernel(MultiArgs a, const doubl
         const float q = prob32(xq[e], sf, Lq, Sq, rSq);
         const double r = (double)p - (double)q;
         zr += grid_weight(r > 0.0 ? r : 0.0);
+        if (y == x) a.acc[cell] = u * (double)q < (double)p;
         if (q_out) q_out[drow * a.v + y] = q;
       }
     }
   }
-  zp = wave_sum_i64(zp);
-  zr = wave_sum_i64(zr);
+  zp = W > 1 ? block_sum_i64<W>(zp, sh) : wave_sum_i64(zp);
+  zr = W > 1 ? block_sum_i64<W>(zr, sh) : wave_sum_i64(zr);
   if (threadIdx.x == 0) {
     a.zp[row * a.nchunk + ch] = zp;
-    const int64_t s = sj / a.c, j = sj - s * a.c;
-    if (drafted) a.zs[((s * a.kd + d) * a.c + j) * a.nchunk + ch] = zr;
+    if (drafted) a.zs[cell * a.nchunk + ch] = zr;
   }
 }
 
+// The chains that share chain j's first d tokens (c <= 64), on every lane.
+__device__ __forceinline__ uint64_t sharing(const MultiArgs& a, int s, int d, int j) {
+  const int lane = threadIdx.x & 63;
+  bool same = lane < a.c;
+#pragma unroll 4
+  for (int i = 0; i < d; ++i) {
+    const int32_t* tk = a.tokens + ((int64_t)i * a.b + s) * a.c;
+    same &= tk[lane < a.c ? lane : 0] == tk[j];
+  }
+  return __ballot(same);
+}
+
 // Step `step` = 1, 2, ..: for every (sequence, depth, chain) whose chain is its
-// node's candidate number `step` (from 0), zs[..][chunk] = the chunk's residual
-// mass after that chain's rejection.  blockIdx.x = ((s kd + d) (c - step) +
-// j - step) slices + slice (at most j candidates come before chain j); a
-// workgroup takes the chunks slice, slice + slices, ...
+// node's candidate number `step` (from 0), and no candidate before it was
+// accepted, its test and, if that fails, zs[..][chunk] = the chunk's residual
+// mass after its rejection.  blockIdx.x = ((s kd + d) (c - step) + j - step)
+// slices + slice (at most j candidates come before chain j); a workgroup takes
+// the chunks slice, slice + slices, ...; every one of them takes the test.
 template <bool kOne>
 __global__ __launch_bounds__(kThreads) void multi_step_kernel(MultiArgs a, int slices, int step) {
   __shared__ int64_t sh[4];
@@ -997,18 +1032,13 @@ __global__ __launch_bounds__(kThreads) void multi_step_kernel(MultiArgs a, int s
   const int sdj = blockIdx.x / slices, sd = sdj / nj;
   const int j = step + sdj - sd * nj, s = sd / a.kd, d = sd - s * a.kd;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  // the chains with chain j's prefix, chain `lane` looked at by its lane (c <= 64)
-  bool same = lane < a.c;
-#pragma unroll 4
-  for (int i = 0; i < d; ++i) {
-    const int32_t* tk = a.tokens + ((int64_t)i * a.b + s) * a.c;
-    same &= tk[lane < a.c ? lane : 0] == tk[j];
-  }
-  const uint64_t alive = __ballot(same);
-  if (__popcll(alive & ((1ull << j) - 1ull)) != step) return;  // uniform across the block
+  const int64_t row = (int64_t)sd * a.c;
+  const int done = a.acc[row + min(lane, a.c - 1)];
+  const uint64_t alive = sharing(a, s, d, j), before = alive & ((1ull << j) - 1ull);
+  if (__popcll(before) != step || (__ballot(done) & before)) return;  // uniform across the block
   const Node nd = node_at(a, alive, s, d);
-  int64_t* zrow = a.zs + ((int64_t)sd * a.c + j) * a.nchunk;
-  // this workgroup's first logits, and the masses of the candidates before it, a wavefront each
+  int64_t* zrow = a.zs + (row + j) * a.nchunk;
+  // this workgroup's first logits and the token's, and the masses of the candidates before it, a wavefront each
   float xp[kPer], xq[kPer];
   auto load = [&](int ch) {
 #pragma unroll
@@ -1019,10 +1049,13 @@ __global__ __launch_bounds__(kThreads) void multi_step_kernel(MultiArgs a, int s
     }
   };
   load(slice);
+  const int32_t x = a.tokens[((int64_t)d * a.b + s) * a.c + j];
+  const uint32_t u = a.u24[(int64_t)s * (a.c * a.kd + 1) + d * a.c + j];
+  const bool in = x >= 0 && x < a.v;
+  const float lpx = nd.p.l[in ? x : 0], lqx = nd.q.l[in ? x : 0];
   int r = 0;
-  for (uint64_t rest = alive; rest; rest &= rest - 1) {
+  for (uint64_t rest = before; rest; rest &= rest - 1) {
     const int i = __ffsll((unsigned long long)rest) - 1;
-    if (i >= j) break;
     if ((r++ & 3) != w) continue;
     const int64_t t = wave_row_sum(zrow + (int64_t)(i - j) * a.nchunk, a.nchunk);
     if (lane == 0) sz[i] = t;
@@ -1033,6 +1066,17 @@ __global__ __launch_bounds__(kThreads) void multi_step_kernel(MultiArgs a, int s
   }
   const Soft<kOne> sf(a.temp);
   __syncthreads();
+  auto residual = [&](float p, float q, int64_t& zc) {
+    return residual_at(before, p, q, 64, [&](int i) { return sz[i]; }, [&]() { return szp; }, zc);
+  };
+  {
+    const float p = prob32(lpx, sf, nd.p.L, nd.p.S, nd.p.rS), q = prob32(lqx, sf, nd.q.L, nd.q.S, nd.q.rS);
+    int64_t zc;
+    const int64_t w1 = residual(p, q, zc);
+    const bool acc = in && test_grid(u, q, zc, w1);  // the same on every thread of every workgroup
+    if (slice == 0 && threadIdx.x == 0) a.acc[row + j] = acc;
+    if (acc) return;
+  }
   for (int ch = slice; ch < a.nchunk; ch += slices) {
     if (ch != slice) load(ch);
     int64_t z = 0;
@@ -1041,7 +1085,7 @@ __global__ __launch_bounds__(kThreads) void multi_step_kernel(MultiArgs a, int s
       if (ch * kChunk + e * kThreads + (int)threadIdx.x >= a.v) break;
       const float p = prob32(xp[e], sf, nd.p.L, nd.p.S, nd.p.rS), q = prob32(xq[e], sf, nd.q.L, nd.q.S, nd.q.rS);
       int64_t zc;
-      const int64_t w1 = residual_at(alive, p, q, j, [&](int i) { return sz[i]; }, [&]() { return szp; }, zc);
+      const int64_t w1 = residual(p, q, zc);
       const int64_t w0 = w1 - floor_qz(q, zc);
       z += w0 > 0 ? w0 : 0;
     }
@@ -1050,21 +1094,24 @@ __global__ __launch_bounds__(kThreads) void multi_step_kernel(MultiArgs a, int s
   }
 }
 
-// One workgroup per sequence: the masses, every (depth, chain)'s test, the walk,
-// the draw.  LDS: masses [kd c] int64, tokens [kd c], test results [kd c].
+// One workgroup per sequence: the walk and the draw.  At a node it reaches, the
+// candidates up to number `steps` have their tests from the launches before;
+// the others, when all of those fail, it takes here, one pass over the row each
+// (R and q [v] of the sequence, logit y always on thread y % kMThreads), as
+// multi_step_kernel would.  LDS: tokens [kd c], test results [kd c].
 template <bool kOne>
-__global__ __launch_bounds__(kMThreads) void multi_walk_kernel(MultiArgs a, const uint32_t* __restrict__ u24,
-                                                               int32_t* __restrict__ n_accepted,
+__global__ __launch_bounds__(kMThreads) void multi_walk_kernel(MultiArgs a, int steps, int32_t* __restrict__ n_accepted,
                                                                int32_t* __restrict__ next_token,
                                                                int32_t* __restrict__ chain) {
   extern __shared__ __align__(16) char msmem[];
   __shared__ int64_t sh[kMWaves];
-  __shared__ int sN, sChunk, sTok;
-  __shared__ uint64_t sAlive;
-  __shared__ int64_t sOff;
+  __shared__ int64_t sz[64];  // a node's masses
+  __shared__ int64_t sc[kWalkLogits / kChunk][kMWaves];
+  __shared__ int sChunk, sTok;
+  __shared__ int64_t sOff, szp, sR;
+  __shared__ float sQ;
   const int c = a.c, kd = a.kd, v = a.v, nchunk = a.nchunk, np = kd * c;
-  int64_t* sz = reinterpret_cast<int64_t*>(msmem);
-  int32_t* stok = reinterpret_cast<int32_t*>(sz + np);
+  int32_t* stok = reinterpret_cast<int32_t*>(msmem);
   int32_t* sacc = stok + np;
   const int s = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int64_t rows_t = (int64_t)a.b * c * (kd + 1);
@@ -1074,87 +1121,126 @@ __global__ __launch_bounds__(kMThreads) void multi_walk_kernel(MultiArgs a, cons
     const int k2 = rr - c * (kd + 1);  // draft row d * c + j
     bad |= isnan(a.ls[k2 < 0 ? (int64_t)s * c * (kd + 1) + rr : rows_t + ((int64_t)(k2 / c) * a.b + s) * c + k2 % c].y);
   }
-  for (int i = t; i < np; i += kMThreads) stok[i] = a.tokens[((int64_t)(i / c) * a.b + s) * c + i % c];
-  for (int i = w; i < np; i += kMWaves) {
-    const int64_t z = wave_row_sum(a.zs + ((int64_t)s * np + i) * nchunk, nchunk);
-    if (lane == 0) sz[i] = z;
+  for (int i = t; i < np; i += kMThreads) {
+    stok[i] = a.tokens[((int64_t)(i / c) * a.b + s) * c + i % c];
+    sacc[i] = a.acc[(int64_t)s * np + i];
   }
+  const uint32_t* u = a.u24 + (int64_t)s * (np + 1);
+  const uint32_t ud = u[np];  // the draw's
   if (t == 0) sChunk = sTok = -1;
   if (__syncthreads_or(bad)) {
     if (t == 0) n_accepted[s] = next_token[s] = chain[s] = -1;
     return;
   }
   const Soft<kOne> sf(a.temp);
-  const uint32_t* u = u24 + (int64_t)s * (c * kd + 1);
-  auto zp_sum = [&](int64_t trow) {  // by one thread, and rarely
-    int64_t z = 0;
-    for (int i = 0; i < nchunk; ++i) z += a.zp[trow * nchunk + i];
-    return z;
+  int64_t* R = a.r + (int64_t)s * v;
+  float* Q = a.q + (int64_t)s * v;
+  // the masses after the rejections of a node's candidates (`which` of them), and of p, a wavefront each
+  auto masses = [&](const Node& nd, int d, uint64_t which) {
+    for (int j = w; j < c; j += kMWaves) {
+      if (!((which >> j) & 1ull)) continue;
+      const int64_t z = wave_row_sum(a.zs + ((int64_t)s * np + d * c + j) * nchunk, nchunk);
+      if (lane == 0) sz[j] = z;
+    }
+    if (w == kMWaves - 1) {
+      const int64_t z = wave_row_sum(a.zp + nd.trow * nchunk, nchunk);
+      if (lane == 0) szp = z;
+    }
+    __syncthreads();
   };
-  // the test of chain j at depth d, given that its first d tokens were accepted
-  for (int i = t; i < np; i += kMThreads) {
-    const int d = i / c, j = i - d * c;
-    const int32_t x = stok[i];
-    int acc = 0;
-    if (x >= 0 && x < v) {
-      uint64_t alive = 0;
-      for (int o = 0; o < c; ++o) {
-        bool same = true;
-        for (int e = 0; e < d && same; ++e) same = stok[e * c + o] == stok[e * c + j];
-        alive |= (uint64_t)same << o;
-      }
+  auto residual = [&](uint64_t which, float p, float q, int64_t& zc) {
+    return residual_at(which, p, q, 64, [&](int o) { return sz[o]; }, [&]() { return szp; }, zc);
+  };
+  // every wavefront walks, chain `lane` on its lane: all values are uniform across the block
+  uint64_t alive = c == 64 ? ~0ull : ((1ull << c) - 1ull);
+  int n = kd;
+  int64_t z = 0;  // of R, once a node's candidates past `steps` have been taken here
+  bool late = false;
+  for (int d = 0; d < kd; ++d) {
+    const bool on = lane < c && ((alive >> lane) & 1ull);
+    const bool known = __popcll(alive & ((1ull << lane) - 1ull)) <= steps;
+    const int cell = d * c + min(lane, c - 1);
+    const uint64_t acc = __ballot(on && known && sacc[cell]);
+    int32_t x = -1;
+    bool accepted = acc != 0;
+    if (accepted) {
+      x = stok[d * c + __ffsll((unsigned long long)acc) - 1];  // the lowest accepted one
+    } else if (uint64_t rest = __ballot(on && !known)) {
       const Node nd = node_at(a, alive, s, d);
-      const float p = prob(nd.p, sf, x), q = prob(nd.q, sf, x);
-      const uint32_t uj = u[i];
-      if ((alive & ((1ull << j) - 1ull)) == 0) {
-        acc = ldexp((double)(uj & 0xFFFFFFu), -24) * (double)q < (double)p;
-      } else {
-        int64_t z;
-        const int64_t r = residual_at(
-            alive, p, q, j, [&](int o) { return sz[d * c + o]; }, [&]() { return zp_sum(nd.trow); }, z);
-        acc = test_grid(uj, q, z, r);
+      const uint64_t before = alive & ~rest;
+      masses(nd, d, before);
+      for (int y = t; y < v; y += kMThreads) {
+        const float q = prob(nd.q, sf, y);
+        Q[y] = q;
+        R[y] = residual(before, prob(nd.p, sf, y), q, z);
       }
-    }
-    sacc[i] = acc;
-  }
-  __syncthreads();
-  if (w == 0) {  // the walk, chain `lane` on its lane
-    uint64_t alive = c == 64 ? ~0ull : ((1ull << c) - 1ull);
-    int n = kd;
-    for (int d = 0; d < kd; ++d) {
-      const uint64_t acc = __ballot(lane < c && ((alive >> lane) & 1ull) && sacc[d * c + min(lane, c - 1)]);
-      if (!acc) {
-        n = d;
-        break;
+      (void)residual(before, 0.f, 0.f, z);  // (the mass, on threads without a logit too)
+      for (; rest; rest &= rest - 1) {
+        const int j = __ffsll((unsigned long long)rest) - 1;
+        x = stok[d * c + j];
+        if (x >= 0 && x < v) {
+          if (t == x % kMThreads) {
+            sR = R[x];
+            sQ = Q[x];
+          }
+          __syncthreads();
+          accepted = test_grid(u[d * c + j], sQ, z, sR);
+          if (accepted) break;
+        }
+        const int64_t z0 = z;
+        z = 0;
+#pragma unroll 4
+        for (int y = t; y < v; y += kMThreads) {
+          const int64_t w0 = R[y] - floor_qz(Q[y], z0), w1 = w0 > 0 ? w0 : 0;
+          R[y] = w1;
+          z += w1;
+        }
+        z = block_sum_i64<kMWaves>(z, sh);  // (its barriers also keep the next sR from this one's readers)
+        if (z == 0) {  // no residual mass on the grid: back to p
+          for (int y = t; y < v; y += kMThreads) R[y] = grid_weight((double)prob(nd.p, sf, y));
+          z = szp;
+        }
       }
-      const int32_t x = stok[d * c + __ffsll((unsigned long long)acc) - 1];  // the lowest accepted one
-      alive &= __ballot(lane < c && stok[d * c + min(lane, c - 1)] == x);
+      late = !accepted;
     }
-    if (lane == 0) {
-      sN = n;
-      sAlive = alive;
+    if (!accepted) {
+      n = d;
+      break;
     }
+    alive &= __ballot(lane < c && stok[cell] == x);
+    __syncthreads();  // (sz, sR)
   }
-  __syncthreads();
-  const int n = sN;
-  const uint64_t alive = sAlive;
   const int jf = __ffsll((unsigned long long)alive) - 1;
   const Node nd = node_at(a, alive, s, n);
   const int jl = 63 - __clzll((unsigned long long)alive);  // the node's last candidate
-  // the draw's chunk masses: the residual's after all rejections, else p's (all
-  // accepted, or no residual mass left)
-  const bool plain = n == kd || sz[n * c + jl] == 0;
-  const int64_t* zc = plain ? a.zp + nd.trow * nchunk : a.zs + ((int64_t)s * np + n * c + jl) * nchunk;
-  int64_t part = 0;
-  for (int i = t; i < nchunk; i += kMThreads) part += zc[i];
-  const int64_t z = block_sum_i64<kMWaves>(part, sh);
+  bool plain = false;
+  const int64_t* zc = nullptr;
+  if (late) {  // the draw's chunk masses, from R
+    for (int ch = 0; ch < nchunk; ++ch) {
+      const int y = ch * kChunk + t;  // kChunk == kMThreads
+      const int64_t m = wave_sum_i64(y < v ? R[y] : 0);
+      if (lane == 0) sc[ch][w] = m;
+    }
+    __syncthreads();
+  } else {
+    // the residual's after all rejections, else p's (all accepted, or no residual mass left)
+    masses(nd, n, n < kd ? alive : 0);
+    plain = n == kd || sz[jl] == 0;
+    zc = plain ? a.zp + nd.trow * nchunk : a.zs + ((int64_t)s * np + n * c + jl) * nchunk;
+    z = plain ? szp : sz[jl];
+  }
   if (z > 0) {  // uniform across the block
-    const uint64_t uu = u[c * kd] & 0xFFFFFFu;
+    const uint64_t uu = ud & 0xFFFFFFu;
     const int64_t tt = (int64_t)((__umul64hi(uu, (uint64_t)z) << 40) | ((uu * (uint64_t)z) >> 24));
     int64_t run = 0;
     for (int i0 = 0; i0 < nchunk; i0 += kMThreads) {
       const int i = i0 + t;
-      const int64_t m = i < nchunk ? zc[i] : 0;
+      int64_t m = 0;
+      if (late) {
+        for (int k = 0; i < nchunk && k < kMWaves; ++k) m += sc[i][k];
+      } else if (i < nchunk) {
+        m = zc[i];
+      }
       int64_t tile;
       const int64_t pre = run + block_exclusive_scan_i64<kMWaves>(m, sh, tile);
       if (m > 0 && pre <= tt && tt < pre + m) {
@@ -1167,14 +1253,15 @@ __global__ __launch_bounds__(kMThreads) void multi_walk_kernel(MultiArgs a, cons
     }
     const int ch = sChunk;
     if (ch >= 0) {  // always (tt < z)
-      const int y = ch * kChunk + t;  // kChunk == kMThreads
+      const int y = ch * kChunk + t;
       int64_t r = 0, zi;
       if (y < v) {
-        const float p = prob(nd.p, sf, y);
-        r = plain ? grid_weight((double)p)
-                  : residual_at(
-                        alive, p, prob(nd.q, sf, y), 64, [&](int o) { return sz[n * c + o]; },
-                        [&]() { return zp_sum(nd.trow); }, zi);
+        if (late) {
+          r = R[y];
+        } else {
+          const float p = prob(nd.p, sf, y);
+          r = plain ? grid_weight((double)p) : residual(alive, p, prob(nd.q, sf, y), zi);
+        }
       }
       int64_t tile;
       const int64_t pre = block_exclusive_scan_i64<kMWaves>(r, sh, tile);
@@ -1391,14 +1478,29 @@ hipError_t launch_spec_accept_noalloc(const float* draft, const float* target, c
 }
 
 
+namespace {
+// Step launches of a call: of a node's candidates after the first, those that
+// the whole chip takes before the walk.  All of them for large rows, of which
+// one workgroup would take some 40 us for each candidate.  A launch of up to
+// 2.5 us with nothing left to do against a pass of one workgroup over a small
+// row, where candidates are accepted early / late (us, one sequence): 16
+// chains of 16000 logits, 15 / 7 / 3 launches 51 / 39 / 32 and 164 / 160 / 136; eight,
+// 7 / 3 launches 39 / 31 and 77 / 95; 32 of 1000, 31 / 0 launches 73 / 24 and 86 / 29.
+int walk_steps(int c, int v) {
+  if (v > kWalkLogits || c - 1 <= v / 2048) return c - 1;
+  return v / 4096;
+}
+}  // namespace
+
 size_t spec_accept_multi_scratch_bytes(int b, int c, int kd, int v, float temperature) {
   const int64_t nchunk = (v + kChunk - 1) / kChunk;
   const int64_t rows_t = (int64_t)b * c * (kd + 1);
   if (temperature == 0.0f) return pad256((size_t)rows_t * nchunk * sizeof(int64_t));
   const int64_t rows = rows_t + (int64_t)kd * b * c;
-  // chunk statistics, merged statistics, chunk masses of p and of the residuals
+  // chunk statistics, merged statistics, chunk masses of p and of the residuals, test results, the walk's R
   return pad256((size_t)rows * nchunk * sizeof(double2)) + pad256((size_t)rows * sizeof(double2)) +
-         pad256((size_t)rows * nchunk * sizeof(int64_t));
+         pad256((size_t)rows * nchunk * sizeof(int64_t)) + pad256((size_t)kd * b * c * sizeof(int32_t)) +
+         (walk_steps(c, v) < c - 1 ? (size_t)b * v * (sizeof(int64_t) + sizeof(float)) : 0);
 }
 
 hipError_t launch_spec_accept_multi(const float* draft, const float* target, const int32_t* tokens,
@@ -1422,26 +1524,36 @@ hipError_t launch_spec_accept_multi(const float* draft, const float* target, con
   const int64_t rows_d = (int64_t)kd * b * c, rows = rows_t + rows_d;
   double2* stats = reinterpret_cast<double2*>(ws);
   ws += pad256((size_t)rows * nchunk * sizeof(double2));
-  MultiArgs a{draft, target, tokens, b, c, kd, v, nchunk, temperature, reinterpret_cast<double2*>(ws), nullptr, nullptr};
+  MultiArgs a{draft, target, tokens, u24, b, c, kd, v, nchunk, temperature, reinterpret_cast<double2*>(ws),
+              nullptr, nullptr, nullptr, nullptr, nullptr};
   ws += pad256((size_t)rows * sizeof(double2));
   a.zp = reinterpret_cast<int64_t*>(ws);
   a.zs = a.zp + rows_t * nchunk;
+  ws += pad256((size_t)rows * nchunk * sizeof(int64_t));
+  a.acc = reinterpret_cast<int32_t*>(ws);
+  a.r = reinterpret_cast<int64_t*>(ws + pad256((size_t)kd * b * c * sizeof(int32_t)));
+  a.q = reinterpret_cast<float*>(a.r + (size_t)b * v);
   // step i: at most c candidates meet at a node; most (sequence, depth, chain)
   // leave a launch at once, so their number is bounded and the chunks looped
   // over when there are many
   int64_t slices = rows_d > 0 ? kStepBlocks / rows_d : 1;
   slices = slices < 1 ? 1 : (slices > nchunk ? nchunk : slices);
-  const size_t lds = (size_t)kd * c * (sizeof(int64_t) + 2 * sizeof(int32_t));  // at most 64 KB
+  const size_t lds = (size_t)kd * c * 2 * sizeof(int32_t);  // at most 32 KB
+  const int steps = walk_steps(c, v);
   auto go = [&](auto one_tag) {
     constexpr bool One = decltype(one_tag)::value;
     hipLaunchKernelGGL(stats_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target, rows_t,
                        v, temperature, nchunk, stats, nullptr, 1);
-    hipLaunchKernelGGL(multi_rows_kernel<One>, dim3((unsigned)(rows_t * nchunk)), dim3(64), 0, stream, a, stats, q_out,
-                       p_out);
-    for (int i = 1; rows_d > 0 && i < c; ++i)
+    // one wavefront per chunk issues the fewest instructions, four take less time while they do not fill the chip
+    // (two chains of four, 1000 logits, the whole call: 27 / 24 us)
+    auto rows_go = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)(rows_t * nchunk)), dim3(threads), 0, stream, a, stats, q_out, p_out);
+    };
+    rows_t * nchunk <= 1024 ? rows_go(multi_rows_kernel<One, 4>, 256) : rows_go(multi_rows_kernel<One, 1>, 64);
+    for (int i = 1; rows_d > 0 && i <= steps; ++i)
       hipLaunchKernelGGL(multi_step_kernel<One>, dim3((unsigned)(rows_d / c * (c - i) * slices)), dim3(kThreads), 0,
                          stream, a, (int)slices, i);
-    hipLaunchKernelGGL(multi_walk_kernel<One>, dim3((unsigned)b), dim3(kMThreads), lds, stream, a, u24, n_accepted,
+    hipLaunchKernelGGL(multi_walk_kernel<One>, dim3((unsigned)b), dim3(kMThreads), lds, stream, a, steps, n_accepted,
                        next_token, chain);
   };
   if (temperature == 1.0f)
