@@ -19,7 +19,6 @@ comparison) with the speedup over it.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import sys
@@ -31,9 +30,6 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 METRIC = "draft+verify tokens/s at Qwen2.5-7B shape (k=4); INT4/FP8 GEMV HBM TB/s vs peak"
-CSRC = os.path.join(ROOT, "paper_2609_21704_amd", "csrc")
-# the sources of each draft GEMV variant's kernels (a traffic profile is valid while they are unchanged)
-GEMV_SOURCES = {"int4": ["gemv.hip"], "fp8": ["gemv.hip", "linear.hip"]}
 FP8_CONFIG = 3         # the Qwen2.5-7B-shaped workload with the FP8 draft (m = 4)
 COPY_BYTES = 1 << 30   # the plain copy that calibrates the HBM byte counters
 
@@ -231,20 +227,14 @@ def per_shape(cfg, rot_bytes: int = 3 << 30, iters: int = 40):
     return rows
 
 
-def sources_sha(variant: str) -> str:
-    h = hashlib.sha256()
-    for f in GEMV_SOURCES[variant]:
-        h.update(open(os.path.join(CSRC, f), "rb").read())
-    return h.hexdigest()
-
-
 def traffic_from_profile(variant: str):
     """HBM bytes per draft-GEMV call from the committed rocprofv3 counter
-    summary, if it was taken on the current kernel sources; else None."""
+    summary, if it was taken on the current sources of the draft projections; else None."""
+    from paper_2609_21704_amd.prof import sources_sha
     path = os.path.join(ROOT, "profiles", f"gemv_{variant}_traffic.txt")
     if not os.path.exists(path):
         return None
-    sha = sources_sha(variant)
+    sha = sources_sha()
     vals = {}
     for line in open(path):
         if "=" in line and not line.startswith("#"):

@@ -8,8 +8,9 @@
         HBM bytes per draft-GEMV call from the FETCH_SIZE / WRITE_SIZE
         counters, each divided by what the same counter reads, per byte, for the
         plain copy pass over N bytes (read once, written once) that the profiled
-        command dispatches last; the draft-GEMV dispatches of the variant are
-        summed and divided by C calls (default: one call per dispatch)
+        command dispatches last; the dispatches of the variant's draft
+        projections (with the sums of their K slices) are added up and divided by
+        C calls (default: one call per dispatch)
     python -m paper_2609_21704_amd.prof gemv <rocprofv3 output dir> --variant int4|fp8 [--calls C]
         the draft-GEMV dispatches of the variant: count, total and average
         duration (per call when C is given)
@@ -38,23 +39,45 @@ import sqlite3
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2609_21704_amd", "csrc")
-# the sources of each draft GEMV variant's kernels, and its dispatches: the
-# GEMV kernels with the variant's weight kind (second template argument: fp8
-# or not), and for FP8 the matrix-core streaming instance (kind 1) that takes
-# the large matrices at m >= 3
-GEMV_SOURCES = {"int4": ["gemv.hip"], "fp8": ["gemv.hip", "linear.hip"]}
+# A draft projection's dispatches: the GEMV kernels with the variant's weight
+# kind (second template argument: FP8 or not), the matrix-core kernels that
+# take it from three rows on (their first: 0 INT4, 1 FP8, 2 FP16), and the sum
+# of the K slices' partial outputs directly after any of these; and the files
+# that hold those kernels and choose between them.
+DRAFT_KIND = {"int4": 0, "fp8": 1}
+GEMV_SOURCES = ["gemv.hip", "gemm.hip", "linear.hip", "abi.cpp", "sq_internal.hpp", "sq_device.hpp"]
+REDUCE_KERNELS = ("sq::slice_reduce_kernel", "sq::splitk_reduce_kernel")
 
 
 def is_draft_gemv(name: str, variant: str) -> bool:
     if name.startswith(("sq::gemv_kernel<", "sq::gemv_rows_kernel<")):
         fp8 = name.split(",")[1].strip() == "true"
         return fp8 == (variant == "fp8")
-    return variant == "fp8" and name.startswith("sq::linear_kernel<1,")
+    return name.startswith(tuple(f"sq::{k}<{DRAFT_KIND[variant]}," for k in ("linear_kernel", "tile_kernel")))
 
 
-def sources_sha(variant: str) -> str:
+def with_reductions(names, match):
+    """For dispatch names in order: whether each is one that match(name) takes, or the reduction directly after it."""
+    out, prev = [], False
+    for name in names:
+        reduction = name.startswith(REDUCE_KERNELS)
+        take = match(name) or (prev and reduction)
+        out.append(take)
+        prev = take and not reduction
+    return out
+
+
+def draft_values(rows, variant):
+    """The values of (short kernel name, value) rows, in dispatch order, that belong to the variant's draft
+    projections."""
+    rows = list(rows)
+    keep = with_reductions([name for name, _ in rows], lambda name: is_draft_gemv(name, variant))
+    return [value for (_, value), k in zip(rows, keep) if k]
+
+
+def sources_sha() -> str:
     h = hashlib.sha256()
-    for f in GEMV_SOURCES[variant]:
+    for f in GEMV_SOURCES:
         h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()
 
@@ -127,8 +150,8 @@ def traffic(fetch_dir, write_dir, copy_bytes, variant="int4", calls=None):
     copy_key = fetch[-1][1]
     f_scale = fetch[-1][2] * 1024.0 / copy_bytes   # counters are in KiB
     w_scale = write[-1][2] * 1024.0 / copy_bytes
-    f_g = [v * 1024.0 for _, k, v in fetch if is_draft_gemv(k, variant)]
-    w_g = [v * 1024.0 for _, k, v in write if is_draft_gemv(k, variant)]
+    f_g = [v * 1024.0 for v in draft_values(((k, v) for _, k, v in fetch), variant)]
+    w_g = [v * 1024.0 for v in draft_values(((k, v) for _, k, v in write), variant)]
     n = calls or len(f_g)
     f_mean = sum(f_g) / n / f_scale
     w_mean = sum(w_g) / n / w_scale if w_g else 0.0
@@ -145,12 +168,12 @@ def traffic(fetch_dir, write_dir, copy_bytes, variant="int4", calls=None):
         f"hbm_read_bytes_per_launch = {f_mean:.1f}",
         f"hbm_write_bytes_per_launch = {w_mean:.1f}",
         f"hbm_bytes_per_launch = {f_mean + w_mean:.1f}",
-        f"gemv_source_sha256 = {sources_sha(variant)}",
+        f"gemv_source_sha256 = {sources_sha()}",
     ])
 
 
 def gemv_trace(path, variant, calls=None):
-    d = [dur for name, _, _, _, dur in kernel_rows(path) if is_draft_gemv(short_name(name), variant)]
+    d = draft_values(((short_name(name), dur) for name, _, _, _, dur in kernel_rows(path)), variant)
     n = calls or len(d)
     return "\n".join([
         f"variant = {variant}",
@@ -161,10 +184,8 @@ def gemv_trace(path, variant, calls=None):
     ])
 
 
-# the FP16 verification kernels (linear_kernel<2, ...> is the FP16 instance; the
-# INT4 / FP8 instances serve draft projections)
+# the FP16 verification kernels (linear_kernel<2, ...> and tile_kernel<2, ...> are the FP16 instances)
 VERIFY_KERNELS = ("sq::linear_kernel<2,", "sq::gemm_rows_kernel", "sq::tile_kernel<2,")
-REDUCE_KERNEL = "sq::slice_reduce_kernel"
 
 
 def dispatch_counters(path):
@@ -189,15 +210,9 @@ def verify(mfma_dir, fetch_dir, write_dir, copy_bytes, m, layers, shapes, lm):
 
     def seq(runs):
         # verify dispatches in order, each K-slice reduction that directly follows one attached to it
-        out, prev = [], False
-        for d in sorted(runs):
-            name = runs[d][0]
-            if name.startswith(VERIFY_KERNELS) or (prev and name.startswith(REDUCE_KERNEL)):
-                out.append(runs[d])
-                prev = not name.startswith(REDUCE_KERNEL)
-            else:
-                prev = False
-        return out
+        order = [runs[d] for d in sorted(runs)]
+        keep = with_reductions([e[0] for e in order], lambda name: name.startswith(VERIFY_KERNELS))
+        return [e for e, k in zip(order, keep) if k]
 
     vm, vf, vw = seq(mf), seq(fe), seq(wr)
     labels = [name for _ in range(layers) for name, _, _ in shapes] + (["lm_head"] if lm else [])
@@ -207,7 +222,7 @@ def verify(mfma_dir, fetch_dir, write_dir, copy_bytes, m, layers, shapes, lm):
     # a projection may take two dispatches (a K-slice reduction follows); attach those to the previous one
     groups = []
     for i, e in enumerate(vm):
-        if e[0].startswith(REDUCE_KERNEL) and groups:
+        if e[0].startswith(REDUCE_KERNELS) and groups:
             groups[-1].append(i)
         else:
             groups.append([i])
