@@ -90,7 +90,7 @@ __device__ __forceinline__ void load_item(Item<KIND, MT, U>& it, const uint16_t*
     }
     if constexpr (KIND == kW4) {
       const int64_t groups = k >> 7, gi = row * groups + (step < groups ? step : groups - 1);
-      it.s[u] = scales16[gi];
+      it.s[u] = step < groups ? scales16[gi] : 0;  // (a row's last scale may be infinite)
       it.z[u] = zeros16[gi];
     }
 #pragma unroll
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(NW * 64) void tile_kernel(const uint16_t* __restric
                 cur.a[u][mt][t], bw, t == 2 ? float4_t{0.f, 0.f, 0.f, 0.f} : grp2[mt], 0, 0, 0);
         }
       }
-      if constexpr (KIND == kW4) {  // (a step past the row's end adds its scale times zero activations)
+      if constexpr (KIND == kW4) {  // (a step past the row's end adds zero)
         const float s = f16_bits_to_f32((uint16_t)cur.s[u]);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] += s * grp[mt];

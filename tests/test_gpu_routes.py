@@ -57,6 +57,22 @@ def test_projection_routes(kind, n, k):
             assert torch.equal(acc, want), m
 
 
+@pytest.mark.parametrize("k", [128, 640, 3584])
+def test_int4_infinite_scale_of_the_last_group(k):
+    """A row whose last group's scale is infinite: infinities (the group's sums are not zero) from the matrix-core
+    kernels, whose steps past the row's end add nothing, and the other rows as ever."""
+    n = 48
+    (c, s, z), _ = weights("int4", n, k)
+    s[5, -1] = float("inf")
+    q = torch.stack([c & 15, c >> 4], -1).view(n, k // 128, 128).double()
+    for m in (9, 16, 33, 64):
+        x = synth.normal_f16((m, k), 1.0, synth.stream_seed(44, m, k), torch.device(DEV))
+        last = x[:, -128:].double() @ (q - z.double()[..., None])[5, -1]
+        y = sq.sq_qgemv_w4a16(x, c, s, z)
+        assert bool(last.abs().min() > 0) and torch.equal(y[:, 5].double(), last * float("inf")), m
+        assert bool(torch.isfinite(y[:, [i for i in range(n) if i != 5]]).all()), m
+
+
 CHILD = """
 import sys
 sys.path.insert(0, sys.argv[1])
