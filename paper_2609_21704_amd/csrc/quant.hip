@@ -312,8 +312,6 @@ hipError_t launch_quantize_fp8(const uint16_t* w, int64_t n, int64_t k, uint8_t*
       go(quantize_fp8_kernel<2, 1>, by_wave);
     else if (k <= 512 * 4)
       go(quantize_fp8_kernel<4, 1>, by_wave);
-    else if (k <= 512 * 7)
-      go(quantize_fp8_kernel<7, 1>, by_wave);
     else if (k <= 512 * 8)
       go(quantize_fp8_kernel<8, 1>, by_wave);
     else if (k <= 2048 * 4)
