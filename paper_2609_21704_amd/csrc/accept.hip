@@ -59,8 +59,8 @@ __device__ __forceinline__ double quotient(double a, double b, double rb) {
 // are bound by fp64 instructions (one per four cycles) where there are many
 // rows, so the two expensive operations have forms of their own:
 //   z = l / T and p = exp / S: an estimate by the reciprocal plus one
-//     exact-remainder correction, the correctly rounded quotient for three
-//     operations instead of a dozen; kOne: T == 1, z = l;
+//     exact-remainder correction (Markstein 1990, on the IBM RISC System/6000),
+//     the correctly rounded quotient for three operations instead of a dozen; kOne: T == 1, z = l;
 //   exp of x <= 0: n = rint(x / ln 2) (Cody and Waite's two-part reduction),
 //     then the minimax polynomial of degree 11 on |r| <= ln(2) / 2 (Remez
 //     exchange, relative error 3.1e-18, below the rounding of its evaluation)

@@ -17,6 +17,10 @@ namespace {
 
 typedef uint16_t ushort2_t __attribute__((ext_vector_type(2)));
 
+// Division by a reciprocal estimate, one Newton step on it and one correction
+// of the quotient by its exact fused remainder: Markstein, Computation of
+// elementary functions on the IBM RISC System/6000 processor, 1990.
+//
 // 1 / s correctly rounded or within one ulp of it, for s > 0 whose reciprocal
 // is a normal float.
 __device__ __forceinline__ float recip(float s) {
