@@ -5,10 +5,10 @@
 // tokens read every weight 32 times through them; here a weight tile meets
 // 128 or 256 rows and the matrix cores bound the time.
 //
-// A workgroup of 8 wavefronts (two per SIMD) forms a tile of BM rows x 256
-// outputs, each wavefront BM / 2 x 64 of it, in steps of 64 k staged in two
-// LDS buffers: a step's loads are issued before the previous step's products
-// and awaited after them.  Activations, and FP16 weights, go from memory to
+// A workgroup of 8 wavefronts (two per SIMD) forms a tile of BM = 128, 192 or
+// 256 rows x 256 outputs, each wavefront BM / 2 x 64 of it, in steps of 64 k
+// staged in two LDS buffers: a step's loads are issued before the previous
+// step's products and awaited after them.  Activations, and FP16 weights, go from memory to
 // LDS directly (16 bytes a lane); quantized weights pass through registers,
 // where they become halves exactly: INT4 q - z by the mantissa trick of the
 // streaming kernels, a byte permute setting a pair in k order; FP8 by
@@ -24,17 +24,36 @@
 // and one rounding of each scaled group sum, as in the streaming kernels.
 // FP8: the row scale multiplies the total.
 //
+// Sums: one running fp32 sum over thousands of k rounds at its full size with
+// every product; the matrix core's own additions cost the more, as they do not
+// round to nearest.  So the sums have levels, and their errors against 64 bits
+// stay at those of the streaming kernels (3584 k, these / streaming / one
+// running sum: FP16 1.4e-7 / 1.5e-7 / 3.8e-7, FP8 1.1e-7 / 1.4e-7 / 3.4e-7, INT4
+// 0.69e-7 / 0.69e-7 / 0.98e-7; 18944 k: 1.8e-7 / 2.3e-7 / 6.2e-7, 1.6e-7 / 1.8e-7 /
+// 5.9e-7, 0.98e-7 / 1.0e-7 / 2.2e-7):
+//   BM = 128, 192: a block of fold_steps steps in registers of its own (FP16
+//     and FP8: the accumulators; INT4: the scaled group sums), added to the
+//     total at its end.  INT4 has registers for 128 rows only;
+//   BM = 256, where the total leaves no room for that: the two products of a
+//     step accumulate by themselves and are added to the total by vector
+//     operations, beside the next products, up to kShortSteps steps.
+//
 // Where the tiles do not fill the CUs, K is cut into S parts (blockIdx
 // beyond the tiles) whose fp32 partial tiles a second kernel adds in order.
 // BM and S are the pair with the least estimated time (choose()).
-// 2000 rows by the 37888 x 3584 gate|up matrix: FP16 0.87, FP8 1.0, INT4 0.62
-// PFLOP/s: the fragment reads keep LDS as busy as the matrix cores, and INT4
-// adds its conversions; placing these between the products instead of after
-// them delays the fragment reads behind their LDS writes (877 -> 944 us).
+// 2000 rows by the 37888 x 3584 gate|up matrix: FP16 0.95, FP8 0.90, INT4 0.68
+// PFLOP/s (with one running sum 1.02, 1.04 and 0.71).  By the counters the matrix
+// cores are busy in 51, 44 and 31 % of the busy cycles and no LDS access meets a
+// bank conflict; a step waits for its fragments, as the registers hold one
+// step's, and quantized weights add their conversions.  Placing INT4's between
+// the products instead of after them delays the fragment reads behind their LDS
+// writes (877 -> 944 us).
 // Prompts in 64-row blocks through the streaming kernels ran at 0.13.
 // Tiles go to the XCDs in contiguous runs, all row tiles of an output tile
 // next to each other, so that the workgroups of an XCD share weight and
 // activation panels in its L2.
+#include <type_traits>
+
 #include "sq_device.hpp"
 #include "sq_internal.hpp"
 
@@ -46,6 +65,9 @@ constexpr int kThreads = 512;
 constexpr int kBN = 256;  // outputs per tile
 constexpr int kBK = 64;   // k per step
 constexpr int kRowBytes = kBK * 2;
+constexpr int kShortSteps = 88;  // steps of a K part at BM = 256, at most
+// K parts' partial outputs in the workspace (which is never given back), at most; 512 MB was no faster.
+constexpr double kPartBytes = 128e6;
 
 typedef __attribute__((address_space(1))) const uint32_t gword;
 typedef __attribute__((address_space(3))) uint32_t lword;
@@ -78,7 +100,8 @@ template <int KIND, int BM, bool SILU>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_gemm_kernel(
     const uint16_t* __restrict__ x, int64_t m, int64_t k, const uint8_t* __restrict__ w,
     const uint16_t* __restrict__ scales16, const uint16_t* __restrict__ zeros16, const float* __restrict__ scales32,
-    int64_t n, void* __restrict__ y, int out, float* __restrict__ partial, int mtiles, int ntiles, int part_steps) {
+    int64_t n, void* __restrict__ y, int out, float* __restrict__ partial, int mtiles, int ntiles, int part_steps,
+    int fold_steps) {
   extern __shared__ __align__(16) char smem[];
   constexpr int MT = BM / 32, NT = 4;         // 16-row tiles per wavefront
   constexpr int kABytes = BM * kRowBytes, kBBytes = kBN * kRowBytes;
@@ -183,45 +206,110 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
   };
 
-  float4_t acc[MT][NT], grp[KIND == kW4 ? MT : 1][KIND == kW4 ? NT : 1];
+  // the total, the block's sums (kShort: none) and (INT4) the group's products
+  constexpr bool kShort = BM == 256;
+  float4_t tot[MT][NT], acc[kShort ? 1 : MT][kShort ? 1 : NT], grp[KIND == kW4 ? MT : 1][KIND == kW4 ? NT : 1];
 #pragma unroll
   for (int a = 0; a < MT; ++a)
 #pragma unroll
-    for (int b = 0; b < NT; ++b) acc[a][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < NT; ++b) {
+      tot[a][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+      if constexpr (!kShort) acc[a][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+    }
+  auto fold = [&]() {
+    if constexpr (!kShort) {
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+          tot[a][b] += acc[a][b];
+          acc[a][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
 
   // fragment of 16 rows from row r0: lane l holds row r0 + l % 16, memory cells 4 kk + l / 16
   const int fr = (lane & 15) * kRowBytes, fc0 = 16 * ((lane >> 4) ^ (lane & 7)), fc1 = 16 * ((4 + (lane >> 4)) ^ (lane & 7));
   auto compute = [&](int s, int buf) {
     const char* ab = abuf + buf * kABytes + wm * (BM / 2) * kRowBytes + fr;
     const char* bb = bbuf + buf * kBBytes + wn * 64 * kRowBytes + fr;
+    auto frag = [&](const char* base, int t, int kk) {
+      return *reinterpret_cast<const half8_t*>(base + t * 16 * kRowBytes + (kk ? fc1 : fc0));
+    };
+    const float4_t zero4 = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (!kShort) {
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int fc = kk ? fc1 : fc0;
-      half8_t wf[NT], xf[MT];
+      for (int kk = 0; kk < 2; ++kk) {
+        // INT4: activations one row tile ahead (all at once they would not fit its registers)
+        constexpr int XF = KIND == kW4 ? 2 : MT;
+        half8_t wf[NT], xf[XF];
 #pragma unroll
-      for (int b = 0; b < NT; ++b) wf[b] = *reinterpret_cast<const half8_t*>(bb + b * 16 * kRowBytes + fc);
+        for (int b = 0; b < NT; ++b) wf[b] = frag(bb, b, kk);
 #pragma unroll
-      for (int a = 0; a < MT; ++a) xf[a] = *reinterpret_cast<const half8_t*>(ab + a * 16 * kRowBytes + fc);
+        for (int a = 0; a < XF - (KIND == kW4); ++a) xf[a] = frag(ab, a, kk);
 #pragma unroll
-      for (int a = 0; a < MT; ++a)
+        for (int a = 0; a < MT; ++a) {
+          if (KIND == kW4 && a + 1 < MT) xf[(a + 1) % XF] = frag(ab, a + 1, kk);
 #pragma unroll
-        for (int b = 0; b < NT; ++b) {
-          if constexpr (KIND == kW4) {
-            const float4_t c0 = (s & 1) == 0 && kk == 0 ? float4_t{0.f, 0.f, 0.f, 0.f} : grp[a][b];
-            grp[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[b], xf[a], c0, 0, 0, 0);
-          } else {
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[b], xf[a], acc[a][b], 0, 0, 0);
+          for (int b = 0; b < NT; ++b) {
+            if constexpr (KIND == kW4)
+              grp[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                  wf[b], xf[a % XF], (s & 1) == 0 && kk == 0 ? zero4 : grp[a][b], 0, 0, 0);
+            else
+              acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[b], xf[a % XF], acc[a][b], 0, 0, 0);
           }
         }
-    }
-    if constexpr (KIND == kW4) {
-      if (s & 1) {  // the group's last step (K slices start at whole groups)
+      }
+      if constexpr (KIND == kW4) {
+        if (s & 1) {  // the group's last step (K slices start at whole groups)
 #pragma unroll
-        for (int b = 0; b < NT; ++b) {
-          const float4_t sc =
-              *reinterpret_cast<const float4_t*>(sbuf + ((s >> 1) & 1) * kBN + wn * 64 + b * 16 + 4 * (lane >> 4));
+          for (int b = 0; b < NT; ++b) {
+            const float4_t sc =
+                *reinterpret_cast<const float4_t*>(sbuf + ((s >> 1) & 1) * kBN + wn * 64 + b * 16 + 4 * (lane >> 4));
 #pragma unroll
-          for (int a = 0; a < MT; ++a) acc[a][b] += sc * grp[a][b];
+            for (int a = 0; a < MT; ++a) acc[a][b] += sc * grp[a][b];
+          }
+        }
+      }
+    } else {
+      half8_t wf[2][NT];
+#pragma unroll
+      for (int b = 0; b < NT; ++b) {
+        wf[0][b] = frag(bb, b, 0);
+        wf[1][b] = frag(bb, b, 1);
+      }
+      auto products = [&](half8_t x0, half8_t x1, float4_t (&d)[NT]) {
+#pragma unroll
+        for (int b = 0; b < NT; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[0][b], x0, zero4, 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < NT; ++b) d[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[1][b], x1, d[b], 0, 0, 0);
+      };
+      if constexpr (KIND == kF16) {
+#pragma unroll
+        for (int a = 0; a < MT; ++a) {
+          float4_t d[NT];
+          products(frag(ab, a, 0), frag(ab, a, 1), d);
+#pragma unroll
+          for (int b = 0; b < NT; ++b) tot[a][b] += d[b];
+        }
+      } else {
+        // a row tile's vector adds beside the next one's products, no more of them at once (the registers)
+        float4_t d[2][NT];
+        half8_t xf[2][2];
+        xf[0][0] = frag(ab, 0, 0);
+        xf[0][1] = frag(ab, 0, 1);
+#pragma unroll
+        for (int a = 0; a <= MT; ++a) {
+          if (a + 1 < MT) {
+            xf[(a + 1) & 1][0] = frag(ab, a + 1, 0);
+            xf[(a + 1) & 1][1] = frag(ab, a + 1, 1);
+          }
+          if (a < MT) products(xf[a & 1][0], xf[a & 1][1], d[a & 1]);
+          if (a > 0) {
+#pragma unroll
+            for (int b = 0; b < NT; ++b) tot[a - 1][b] += d[(a - 1) & 1][b];
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
@@ -237,14 +325,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   auto step = [&](int s, int buf) {
     if (s + 1 < s1) issue(s + 1, buf ^ 1);
     compute(s, buf);
-    if (s + 1 < s1) convert(s + 1, buf ^ 1);
+    // (FP8 at 256 rows: after the last step the old codes go into the buffer that nobody reads any more; a branch
+    // there makes the compiler keep totals in memory)
+    if ((KIND == kW8 && BM == 256) || s + 1 < s1) convert(s + 1, buf ^ 1);
     sync();
   };
   // (two steps a turn: the buffers and the halves of an INT4 group alternate; s0 is even for INT4)
+  int left = fold_steps;  // an even number
   for (int s = s0; s < s1; s += 2) {
     step(s, 0);
     if (s + 1 < s1) step(s + 1, 1);
+    left -= 2;
+    if (left == 0) {
+      fold();
+      left = fold_steps;
+    }
   }
+  fold();
 
   // outputs: lane l holds outputs 4 (l / 16) .. +4 of a 16-output tile for row l % 16 of a row tile
   const int q4 = 4 * (lane >> 4);
@@ -255,7 +352,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int r = 0; r < 4; ++r) {
         const float sc = scales32[weight_row<SILU>(n0, wn * 64 + b * 16 + q4 + r, n)];
 #pragma unroll
-        for (int a = 0; a < MT; ++a) acc[a][b][r] *= sc;
+        for (int a = 0; a < MT; ++a) tot[a][b][r] *= sc;
       }
   }
   const bool vec = (n & 3) == 0;
@@ -271,7 +368,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int64_t col = n0 + wn * 32 + b * 16 + q4;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (col + r < half) t[col + r] = silu_gate_bits(acc[a][b][r], acc[a][b + 2][r]);
+          if (col + r < half) t[col + r] = silu_gate_bits(tot[a][b][r], tot[a][b + 2][r]);
       }
       continue;
     }
@@ -284,13 +381,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                  (SILU && b >= 2 ? n >> 1 : 0);
       const bool add = !partial && out == 1;
       if (vec && (!SILU || (n & 7) == 0) && col + 3 < end) {
-        float4_t v = acc[a][b];
+        float4_t v = tot[a][b];
         if (add) v = *reinterpret_cast<const float4_t*>(o) + v;
         *reinterpret_cast<float4_t*>(o) = v;
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (col + r < end) o[r] = (add ? o[r] : 0.f) + acc[a][b][r];
+          if (col + r < end) o[r] = (add ? o[r] : 0.f) + tot[a][b][r];
       }
     }
   }
@@ -324,22 +421,31 @@ struct Plan {
 };
 
 // The pair (rows per tile, K parts) of least estimated time: rounds of tiles
-// over the CUs, times steps, times a step's time (1.3 us at BM = 256, 0.8 us at
-// 128, from the measured rates with all CUs busy; INT4 has no registers for 256), plus
-// the partial outputs' way to memory and back.
-Plan choose(int64_t m, int64_t n, int64_t k, bool w4) {
+// over the CUs, times steps, times a step's time, 4 us around each round, and
+// the partial outputs' way to memory and back.  A step's time in us, from 4608
+// .. 37888 x 3584 and 3584 x 18944 at 300 .. 4000 rows: in a single round, where
+// all tiles go along k together and share their panels in the caches, and in
+// more, where FP16 tiles of 128 rows, whose weights take the most bytes per
+// product, are slower still along rows that the caches do not hold (4000 rows by
+// 3584 x 18944: 807 us, with 192 rows a tile 735).
+Plan choose(int64_t m, int64_t n, int64_t k, int kind) {
+  constexpr double kOne[3][3] = {{0.8, 0, 0}, {0.95, 1.45, 2.1}, {0.95, 1.45, 1.9}};  // [kind][BM / 64 - 2]
+  constexpr double kMore[3][3] = {{0.8, 0, 0}, {1.1, 1.48, 2.15}, {1.2, 1.5, 1.95}};
   const int64_t cus = cu_count(), nt = (n + kBN - 1) / kBN, steps = k / kBK;
   Plan best{128, 1, (int)steps};
   double tbest = 1e30;
-  for (int bm = 128; bm <= (w4 ? 128 : 256); bm += 128) {
+  for (int bm = 128; bm <= (kind == kW4 ? 128 : 256); bm += 64) {
     const int64_t tiles = (m + bm - 1) / bm * nt;
-    const double tstep = bm == 256 ? 1.3 : 0.8;
     for (int parts = 1; parts <= 16; ++parts) {
       int64_t ps = (steps + parts - 1) / parts;
       ps += ps & 1;  // whole INT4 groups
       if (parts > 1 && (ps < 4 || (int64_t)(parts - 1) * ps >= steps)) break;
-      if (parts > 1 && (double)parts * m * n * 4 > 512e6) break;
-      double t = (double)((tiles * parts + cus - 1) / cus) * ((double)ps * tstep + 4.0);
+      if (parts > 1 && (double)parts * m * n * 4 > kPartBytes) break;
+      if (bm == 256 && ps > kShortSteps) continue;
+      const int64_t rounds = (tiles * parts + cus - 1) / cus;
+      double tstep = (rounds == 1 ? kOne : kMore)[kind][bm / 64 - 2];
+      if (kind == kF16 && bm == 128 && rounds > 1 && k >= 16384) tstep = 1.6;
+      double t = (double)rounds * ((double)ps * tstep + 4.0);
       if (parts > 1) t += 4.0 + (double)parts * m * n * 8 / 4e6;
       if (t < tbest) {
         tbest = t;
@@ -350,6 +456,13 @@ Plan choose(int64_t m, int64_t n, int64_t k, bool w4) {
   return best;
 }
 
+// Steps per block of the sums: about where the roundings inside blocks and
+// between them are as many (those inside count more in the accumulators).
+int block_steps(int part_steps, int kind) {
+  if (kind == kW4) return part_steps <= 128 ? 8 : 24;
+  return part_steps <= 24 ? 4 : (part_steps <= 128 ? 6 : 8);
+}
+
 template <int KIND>
 hipError_t prefill_launch(const uint16_t* x, int64_t m, int64_t k, const uint8_t* w, const uint16_t* scales16,
                           const uint16_t* zeros16, const float* scales32, int64_t n, void* y, int out,
@@ -357,7 +470,7 @@ hipError_t prefill_launch(const uint16_t* x, int64_t m, int64_t k, const uint8_t
   if (k % (KIND == kW4 ? 128 : kBK) != 0 || m < 1 || m > (int64_t(1) << 20)) return hipErrorNotSupported;
   // 32-bit offsets inside a weight matrix and a row tile
   if ((double)n * (double)k * 2 >= 4294967296.0 || (double)k * 2 * 256 >= 4294967296.0) return hipErrorNotSupported;
-  const Plan p = choose(m, n, k, KIND == kW4);
+  const Plan p = choose(m, n, k, KIND);
   const int64_t mt = (m + p.bm - 1) / p.bm;
   const int64_t nt = out == 2 ? (n / 2 + kBN / 2 - 1) / (kBN / 2) : (n + kBN - 1) / kBN;
   const int64_t tiles = mt * nt * p.parts;
@@ -372,17 +485,17 @@ hipError_t prefill_launch(const uint16_t* x, int64_t m, int64_t k, const uint8_t
   auto go = [&](auto kernel, int bm) {
     const size_t lds = (size_t)2 * (bm + kBN) * kRowBytes + (KIND == kW4 ? 2 * kBN * sizeof(float) : 0);
     hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(kThreads), lds, stream, x, m, k, w, scales16, zeros16,
-                       scales32, n, y, out, partial, (int)mt, (int)nt, p.part_steps);
+                       scales32, n, y, out, partial, (int)mt, (int)nt, p.part_steps, block_steps(p.part_steps, KIND));
   };
-  if constexpr (KIND == kW4) {
-    out == 2 ? go(prefill_gemm_kernel<KIND, 128, true>, 128) : go(prefill_gemm_kernel<KIND, 128, false>, 128);
-  } else {
-    if (p.bm == 256)
-      out == 2 ? go(prefill_gemm_kernel<KIND, 256, true>, 256) : go(prefill_gemm_kernel<KIND, 256, false>, 256);
-    else
-      out == 2 ? go(prefill_gemm_kernel<KIND, 128, true>, 128) : go(prefill_gemm_kernel<KIND, 128, false>, 128);
-  }
-  hipError_t err = hipGetLastError();
+  auto form = [&](auto bm) {
+    constexpr int BM = decltype(bm)::value;
+    out == 2 ? go(prefill_gemm_kernel<KIND, BM, true>, BM) : go(prefill_gemm_kernel<KIND, BM, false>, BM);
+  };
+  if (KIND == kW4 || p.bm == 128)
+    form(std::integral_constant<int, 128>{});
+  else if constexpr (KIND != kW4)
+    p.bm == 192 ? form(std::integral_constant<int, 192>{}) : form(std::integral_constant<int, 256>{});
+  const hipError_t err = hipGetLastError();
   if (err != hipSuccess || p.parts == 1) return err;
   const int64_t total = out == 2 ? m * (n / 2) : m * n;
   int64_t blocks = (total + 255) / 256;

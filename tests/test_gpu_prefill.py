@@ -48,11 +48,14 @@ def test_prefill_linear(kind, m, n, k):
     y = torch.full((m, n), float("nan"), device=DEV)
     assert CALL[kind](x, *args, y)
     assert bool(((y.double() - ref).abs() <= bound).all())
+    # and over all of them at fp32's own error (these sums: 1.5e-7 at most); 16 bits anywhere give 1e-4 and more
+    assert float((y.double() - ref).norm() / ref.norm()) <= 3e-7
     base = synth.normal_f32((m, n), 1.0, synth.stream_seed(33, m, n), torch.device(DEV))
     acc = base.clone()
     assert CALL[kind](x, *args, acc, lib.PREFILL_ADD)
     # the same product, added: one more fp32 rounding (K parts add it to the base in the same order)
     assert bool(((acc.double() - base.double() - ref).abs() <= bound + 2.0 ** -23 * (base.double() + ref).abs()).all())
+    assert torch.equal(acc, base + y)
     if n % 2 == 0:
         t = torch.full((m, n // 2), float("nan"), dtype=torch.float16, device=DEV)
         assert CALL[kind](x, *args, t, lib.PREFILL_SILU)
@@ -60,6 +63,27 @@ def test_prefill_linear(kind, m, n, k):
         want = g * torch.sigmoid(g) * u
         tol = 2.0 ** -10 * want.abs() + 4 * (bound[:, :n // 2] * (u.abs() + 1) + bound[:, n // 2:] * (g.abs() + 1)) + 1e-7
         assert bool(((t.double() - want).abs() <= tol).all())
+
+
+# Relative errors (2-norm, in 1e-7) of sums in blocks and of the blocks, as the streaming kernel for 64 rows forms them:
+# 0.51 .. 2.29 for these kinds and row lengths, and a tenth more.  One running sum gives 1.3 to 3 times as much from
+# 1536 k on.
+ROUNDINGS = {"f16": {896: 1.21, 1536: 1.53, 3584: 1.61, 18944: 2.52}, "fp8": {896: 1.2, 1536: 1.56, 3584: 1.57, 18944: 2.01},
+             "int4": {896: 0.6, 1536: 0.63, 3584: 0.76, 18944: 1.11}}
+
+
+# one tile per CU and K parts, more rounds of the larger tiles, long rows
+@pytest.mark.parametrize("kind", ["f16", "fp8", "int4"])
+@pytest.mark.parametrize("m,n,k", [(300, 1000, 896), (2000, 2048, 1536), (2000, 4608, 3584), (2000, 3584, 3584),
+                                   (2000, 3584, 18944), (4000, 3584, 18944)])
+def test_prefill_linear_rounds_as_sums_in_blocks(kind, m, n, k):
+    args, ref_w = weights(kind, n, k, 34)
+    x = synth.normal_f16((m, k), 1.0, synth.stream_seed(35, m, k), torch.device(DEV))
+    ref = x.double() @ ref_w.t()
+    y = torch.empty((m, n), device=DEV)
+    assert CALL[kind](x, *args, y)
+    error = float((y.double() - ref).norm() / ref.norm())
+    assert error <= 1e-7 * ROUNDINGS[kind][k], error
 
 
 @pytest.mark.parametrize("b,rows,hq,hkv,offset", [(1, 130, 7, 1, 0), (2, 80, 4, 2, 64), (3, 65, 6, 3, 5)])
