@@ -127,7 +127,7 @@ def test_fused_norm_unsupported_shapes_enqueue_nothing():
 
 
 @pytest.mark.parametrize("n,k,m", [(3584, 3584, 1), (3584, 18944, 1), (3584, 18944, 2), (1536, 8960, 1),
-                                   (37888, 3584, 1), (4608, 3584, 4)])
+                                   (37888, 3584, 1), (4608, 3584, 4), (340000, 256, 8), (530000, 256, 5)])
 def test_qgemv_w4a16_acc_equals_gemv_then_add(n, k, m):
     codes, scales, zeros = int4_weights(n, k, n * 3 + k)
     x = torch.randn((m, k), generator=gen(k)).half().to(DEV)
