@@ -76,7 +76,7 @@
 extern "C" {
 #endif
 
-#define SQ_ABI_VERSION 7
+#define SQ_ABI_VERSION 7 /* of this header; the calls of specquant_prefill.h came without a change of it */
 
 typedef enum sq_status {
   SQ_OK = 0,
@@ -128,9 +128,8 @@ sq_status sq_quantize_fp8_e4m3(const uint16_t* w16, int64_t n, int64_t k, uint8_
 /* Draft projection with the INT4 parent (draft generation, SS III-D.2):
  *   y[i][r] = sum_c x[i][c] * (q[r][c] - z[r][c/128]) * s[r][c/128]
  * dequantized in registers; fp32 accumulation; y rounded once to y_dtype.
- * x [m][k] fp16, 1 <= m <= 64 (m <= 8: the draft GEMV; above, the matrix
- * cores, for passes over many rows such as a prompt's); k % 128 == 0,
- * 128 <= k <= 2^20
+ * x [m][k] fp16, 1 <= m <= 64 (one or two rows: the vector ALUs; from three
+ * or four on mostly the matrix cores); k % 128 == 0, 128 <= k <= 2^20
  * codes/scales/zeros as produced by sq_quantize_int4_g128 for an [n][k] matrix
  * y [m][n] of y_dtype (SQ_F16 or SQ_F32), 1 <= n <= 2^31 - 1. */
 sq_status sq_qgemv_w4a16(const uint16_t* x, int64_t m, int64_t k, const uint8_t* codes,
@@ -417,8 +416,11 @@ sq_status sq_spec_commit(const int32_t* n_accepted, const int32_t* next_token, c
  * q_out [kd][b][c][v], p_out [b][c][kd+1][v]: optional fp32 copies, T > 0 only.
  * Limits: 1 <= b <= 65535, 1 <= c <= 64, 0 <= kd <= 64, 1 <= v <= 2^26,
  *   b c (2 kd + 1) ceil(v / 1024) < 2^24; T finite and >= 0.  Uses the library
- *   workspace (row statistics, the fp32 rows unless q_out / p_out are given,
- *   and one int64 row per sequence). */
+ *   workspace: with C = ceil(v / 1024) and R = b c (2 kd + 1) rows 24 R C + 16 R
+ *   bytes of row statistics and residual masses, 4 kd b c of test results and,
+ *   for many chains of short rows (v <= 32768, c - 1 > v / 2048), 12 b v for one
+ *   node's residual and draft distribution; at T = 0 8 C bytes a parent row (each
+ *   term rounded up to 256). */
 sq_status sq_spec_accept_multi(const float* draft_logits, const float* target_logits, const int32_t* draft_tokens,
                                const uint32_t* u24, int32_t b, int32_t c, int32_t kd, int32_t v, float temperature,
                                int32_t* n_accepted, int32_t* next_token, int32_t* chain, float* q_out, float* p_out,

@@ -33,6 +33,9 @@ typedef enum sq_prefill_out {
  *   64 <= k <= 2^20 (n even with SQ_PREFILL_SILU), y 16-byte aligned.
  * SQ_ERR_UNSUPPORTED (nothing enqueued): an output form or shape without a
  * kernel (an output of more than 2^22 tiles of 128 x 256).
+ * Where the output has fewer tiles than the GPU has CUs, K parts' fp32 partial
+ * outputs take up to 128 MB (4 m n bytes a part) of the library workspace, which
+ * is not given back.
  */
 sq_status sq_prefill_linear_f16(const uint16_t* x, int64_t m, int64_t k, const uint16_t* w16, int64_t n, void* y,
                                 sq_prefill_out out, hipStream_t stream);

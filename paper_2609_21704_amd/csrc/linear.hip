@@ -630,8 +630,9 @@ hipError_t linear_launch(const uint16_t* x, int m, int64_t k, const uint8_t* w, 
   // without one (a row block of 2048 x 1536 is three INT4 units: as one chunk, seven
   // of eight wavefronts idled, 7.3 -> 6.0 us at m = 3; not with two or more row
   // tiles, whose partial sums cost more: 11264 x 2048 FP8 at m = 32 16.6 us, with finer
-  // chunks 19.6, at m = 36 19.4 and 22.3), and longer ones where the partial sums ([chunks per workgroup][m][16] floats) exceed the budget;
-  // direct: one chunk per task, no partial sums
+  // chunks 19.6, at m = 36 19.4 and 22.3), and longer ones where the partial sums
+  // ([chunks per workgroup][m][16] floats) exceed the budget; direct: one chunk per
+  // task, no partial sums
   int64_t cmin = (ntask * S + nwg_max * NW - 1) / (nwg_max * NW);
   if (cmin > kChunkMinUnits) cmin = kChunkMinUnits;
   int64_t C = direct ? S : (MT == 1 ? cmin : kChunkMinUnits), nch_max = 0;
