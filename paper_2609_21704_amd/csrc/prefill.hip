@@ -421,20 +421,25 @@ struct Plan {
 };
 
 // The pair (rows per tile, K parts) of least estimated time: rounds of tiles
-// over the CUs, times steps, times a step's time, 4 us around each round, and
-// the partial outputs' way to memory and back.  A step's time in us, from 4608
-// .. 37888 x 3584 and 3584 x 18944 at 300 .. 4000 rows: in a single round, where
-// all tiles go along k together and share their panels in the caches, and in
-// more, where FP16 tiles of 128 rows, whose weights take the most bytes per
-// product, are slower still along rows that the caches do not hold (4000 rows by
-// 3584 x 18944: 807 us, with 192 rows a tile 735).
+// over the CUs, each of its steps and a start, and the partial outputs' way to
+// memory and back.  A step takes longer the more CUs stream (the share of them
+// that a last round uses), as its operands come from memory.  Constants in us,
+// fitted to 210 shapes a kind (15 matrices from 1152 x 896 to 37888 x 3584 at 100 ..
+// 4000 rows, in several copies, so that no operand lies in a cache) with every
+// tile and up to 12 K parts: the plans it takes are within 1.2 % (FP16) and 0.4 %
+// (FP8, INT4) of the fastest on average, at worst 21 % (9728 x 896, 100 rows).
 Plan choose(int64_t m, int64_t n, int64_t k, int kind) {
-  constexpr double kOne[3][3] = {{0.8, 0, 0}, {0.95, 1.45, 2.1}, {0.95, 1.45, 1.9}};  // [kind][BM / 64 - 2]
-  constexpr double kMore[3][3] = {{0.8, 0, 0}, {1.1, 1.48, 2.15}, {1.2, 1.5, 1.95}};
+  struct Cost {
+    double step, full, start;  // a step alone, what a full chip adds to it, a round
+  };
+  constexpr Cost kCost[3][3] = {{{1.19, 0.24, 6.5}, {}, {}},  // [kind][BM / 64 - 2]
+                                {{0.97, 0.22, 6.5}, {1.24, 0.25, 9.5}, {1.73, 0.50, 10}},
+                                {{0.87, 0.51, 6}, {1.10, 0.48, 8.5}, {1.38, 0.58, 10}}};
   const int64_t cus = cu_count(), nt = (n + kBN - 1) / kBN, steps = k / kBK;
   Plan best{128, 1, (int)steps};
   double tbest = 1e30;
   for (int bm = 128; bm <= (kind == kW4 ? 128 : 256); bm += 64) {
+    const Cost c = kCost[kind][bm / 64 - 2];
     const int64_t tiles = (m + bm - 1) / bm * nt;
     for (int parts = 1; parts <= 16; ++parts) {
       int64_t ps = (steps + parts - 1) / parts;
@@ -442,11 +447,10 @@ Plan choose(int64_t m, int64_t n, int64_t k, int kind) {
       if (parts > 1 && (ps < 4 || (int64_t)(parts - 1) * ps >= steps)) break;
       if (parts > 1 && (double)parts * m * n * 4 > kPartBytes) break;
       if (bm == 256 && ps > kShortSteps) continue;
-      const int64_t rounds = (tiles * parts + cus - 1) / cus;
-      double tstep = (rounds == 1 ? kOne : kMore)[kind][bm / 64 - 2];
-      if (kind == kF16 && bm == 128 && rounds > 1 && k >= 16384) tstep = 1.6;
-      double t = (double)rounds * ((double)ps * tstep + 4.0);
-      if (parts > 1) t += 4.0 + (double)parts * m * n * 8 / 4e6;
+      const int64_t whole = tiles * parts / cus, rest = tiles * parts % cus;
+      double t = (double)whole * ((double)ps * (c.step + c.full) + c.start);
+      if (rest > 0) t += (double)ps * (c.step + c.full * (double)rest / (double)cus) + c.start;
+      if (parts > 1) t += 6.0 + (double)parts * m * n * 8 * 0.09e-6;
       if (t < tbest) {
         tbest = t;
         best = Plan{bm, parts, (int)ps};

@@ -471,7 +471,7 @@ def test_spec_accept_greedy(b, kd, v):
 
 @pytest.mark.parametrize("temp,kd,v", [(0.0, 0, 1), (0.0, 2, 4097), (1.0, 0, 1025)])
 def test_spec_accept_more_sequences_than_arrival_slots(temp, kd, v):
-    """Sequences past the slots of one launch (65536 rows or sequences) get what they get in a call of their own."""
+    """Sequences past the first 65536 rows (or sequences) of a call get what they get in a call of their own."""
     b, tail = 65536 // (kd + 1) + 40, 60
     g = torch.Generator(device=DEV).manual_seed(v)
     target = torch.randn((b, kd + 1, v), generator=g, device=DEV)
