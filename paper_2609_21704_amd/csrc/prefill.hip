@@ -65,7 +65,9 @@ constexpr int kThreads = 512;
 constexpr int kBN = 256;  // outputs per tile
 constexpr int kBK = 64;   // k per step
 constexpr int kRowBytes = kBK * 2;
-constexpr int kShortSteps = 88;  // steps of a K part at BM = 256, at most
+// Steps of a K part at BM = 256, at most: the error grows with their root.  FP16, whose streaming sums round the
+// most, may take up to 148 where the row is at least twice as long (18944 k: 2.3e-7 each, 4000 rows 735 -> 604 us).
+constexpr int kShortSteps = 88, kShortStepsF16 = 148;
 // K parts' partial outputs in the workspace (which is never given back), at most; 512 MB was no faster.
 constexpr double kPartBytes = 128e6;
 
@@ -424,7 +426,7 @@ struct Plan {
 // over the CUs, each of its steps and a start, and the partial outputs' way to
 // memory and back.  A step takes longer the more CUs stream (the share of them
 // that a last round uses), as its operands come from memory.  Constants in us,
-// fitted to 210 shapes a kind (15 matrices from 1152 x 896 to 37888 x 3584 at 100 ..
+// fitted to 210 shapes a kind (14 matrices from 1152 x 896 to 37888 x 3584 at 100 ..
 // 4000 rows, in several copies, so that no operand lies in a cache) with every
 // tile and up to 12 K parts: the plans it takes are within 1.2 % (FP16) and 0.4 %
 // (FP8, INT4) of the fastest on average, at worst 21 % (9728 x 896, 100 rows).
@@ -446,7 +448,7 @@ Plan choose(int64_t m, int64_t n, int64_t k, int kind) {
       ps += ps & 1;  // whole INT4 groups
       if (parts > 1 && (ps < 4 || (int64_t)(parts - 1) * ps >= steps)) break;
       if (parts > 1 && (double)parts * m * n * 4 > kPartBytes) break;
-      if (bm == 256 && ps > kShortSteps) continue;
+      if (bm == 256 && ps > kShortSteps && !(kind == kF16 && parts > 1 && ps <= kShortStepsF16)) continue;
       const int64_t whole = tiles * parts / cus, rest = tiles * parts % cus;
       double t = (double)whole * ((double)ps * (c.step + c.full) + c.start);
       if (rest > 0) t += (double)ps * (c.step + c.full * (double)rest / (double)cus) + c.start;
