@@ -796,7 +796,7 @@ __global__ __launch_bounds__(kMergeThreads) void greedy_kernel(const int32_t* __
 // vocabularies take fewer of them, and the walk itself the candidates after
 // (walk_steps()).  Up to c + 2 launches over the whole chip replace a walk of
 // up to c kd passes over the vocabulary by one workgroup per sequence (two
-// sequences, four chains of four, 151936 logits, the whole call: 306 -> 63 us).
+// sequences, four chains of four, 151936 logits, the whole call: 306 -> 71 us).
 constexpr int kMThreads = 1024;
 constexpr int kMWaves = kMThreads / 64;
 constexpr int kStepBlocks = 8192;  // workgroups of one step launch, about

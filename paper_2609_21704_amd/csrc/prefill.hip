@@ -3,7 +3,7 @@
 // thousands of activation rows, with the FP16 parent or the INT4 / FP8 draft
 // copy.  The streaming kernels take at most 64 rows, so a prompt of a thousand
 // tokens read every weight 32 times through them; here a weight tile meets
-// 128 or 256 rows and the matrix cores bound the time.
+// 128 to 256 rows.
 //
 // A workgroup of 8 wavefronts (two per SIMD) forms a tile of BM = 128, 192 or
 // 256 rows x 256 outputs, each wavefront BM / 2 x 64 of it, in steps of 64 k
@@ -68,7 +68,7 @@ constexpr int kRowBytes = kBK * 2;
 // Steps of a K part at BM = 256, at most: the error grows with their root.  FP16, whose streaming sums round the
 // most, may take up to 148 where the row is at least twice as long (18944 k: 2.3e-7 each, 4000 rows 735 -> 604 us).
 constexpr int kShortSteps = 88, kShortStepsF16 = 148;
-// K parts' partial outputs in the workspace (which is never given back), at most; 512 MB was no faster.
+// K parts' partial outputs in the workspace, which is never given back, at most.
 constexpr double kPartBytes = 128e6;
 
 typedef __attribute__((address_space(1))) const uint32_t gword;
