@@ -33,10 +33,14 @@ CALL = {"f16": lib.sq_prefill_linear_f16, "int4": lib.sq_prefill_linear_w4, "fp8
 # edges of the 128- and 256-row tiles and of the 256 (SiLU: 128) outputs, one step of k and more, odd outputs, K parts
 SHAPES = [(1, 64, 128), (65, 77, 640), (128, 256, 256), (129, 258, 384), (257, 514, 384), (100, 4608, 1024),
           (300, 1000, 3584), (511, 2050, 2048), (2000, 512, 1152)]
+# tiles of 192 and 256 rows (FP16 and FP8 over 256 CUs), whole rows of even and odd steps, and K parts, ragged in rows
+# and outputs
+TALL = [(1547, 5042, 320), (1547, 5041, 128), (1993, 5978, 320), (1995, 5982, 128), (161, 5574, 2688), (152, 5430, 4032),
+        (387, 5674, 2432), (398, 5526, 4480)]
 
 
 @pytest.mark.parametrize("kind", ["f16", "fp8", "int4"])
-@pytest.mark.parametrize("m,n,k", SHAPES + [(130, 96, 64), (70, 300, 192)])
+@pytest.mark.parametrize("m,n,k", SHAPES + TALL + [(130, 96, 64), (70, 300, 192)])
 def test_prefill_linear(kind, m, n, k):
     if kind == "int4" and k % 128:
         return
