@@ -324,13 +324,12 @@ __device__ __forceinline__ void load_row_chunk(const float* __restrict__ l, int 
 
 template <bool kOne>
 __global__ __launch_bounds__(64) void stats_kernel(const float* __restrict__ draft, const float* __restrict__ target,
-                                                   int64_t rows_t, int v, float temp, int nchunk,
-                                                   double2* __restrict__ stats, int32_t* __restrict__ counters,
-                                                   int rows_s) {
+                                                   int64_t rows_t, int v, float temp, int nchunk, int nseq,
+                                                   double2* __restrict__ stats, int32_t* __restrict__ counters) {
   const int64_t row = blockIdx.x / nchunk;
   const int c = blockIdx.x % nchunk;
-  // the arrival counter of a sequence (rows_s target rows), for the accept kernel
-  if (counters && c == 0 && row < rows_t && row % rows_s == 0 && threadIdx.x == 0) counters[row / rows_s] = 0;
+  // the arrival counters of nseq sequences, for the accept kernel (there are at least as many rows)
+  if (c == 0 && row < nseq && threadIdx.x == 0) counters[row] = 0;
   float x[kCPer];
   load_row_chunk(row_ptr(draft, target, rows_t, row, v), c, v, x);
   const Soft<kOne> sf(temp);
@@ -391,14 +390,16 @@ __global__ __launch_bounds__(64) void probs_kernel(const float* __restrict__ dra
 // (the draw rows when the first draft token is rejected, or when kd = 0).
 // Indices are clamped and a value that does not apply is ignored, so that no
 // load waits for a condition computed from another.
-template <bool kWide, bool kOne>
+// kMany: G chunks per workgroup instead of one (groups workgroups per sequence); a form of its own, as the single
+// chunk's takes its sequence from an argument that arrives in a register.
+template <bool kWide, bool kOne, bool kMany>
 __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restrict__ draft,
                                                           const float* __restrict__ target,
                                                           const int32_t* __restrict__ tokens,
                                                           const uint32_t* __restrict__ u24, int b, int kd, int v,
                                                           float temp, int nchunk, const double2* __restrict__ stats,
                                                           int64_t* __restrict__ zs, int32_t* __restrict__ counters,
-                                                          int G, int groups,
+                                                          int G, int ngroups,
                                                           int32_t* __restrict__ n_accepted,
                                                           int32_t* __restrict__ next_token) {
   constexpr int kBatch = 3;  // rows of partials a wavefront holds at once
@@ -407,8 +408,10 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   __shared__ int64_t sh0[4], sz[2][2][4];
   __shared__ int sLast, sChunk;
   __shared__ int64_t sOff;
+  const int groups = kMany ? ngroups : nchunk;
   const int s = blockIdx.x / groups;
-  const int c0 = (int)(blockIdx.x % groups) * G, c1 = min(c0 + G, nchunk);  // this workgroup's chunks
+  const int c0 = (int)(blockIdx.x % groups) * (kMany ? G : 1);  // this workgroup's chunks
+  const int c1 = kMany ? min(c0 + G, nchunk) : c0 + 1;
   const int w = threadIdx.x >> 6;
   const int nrows = 2 * kd + 1;
   const int64_t rows_t = (int64_t)b * (kd + 1);
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   auto load_batch = [&](int r0) {
 #pragma unroll
     for (int j = 0; j < kBatch; ++j)
-      if (r0 + 4 * j < nrows) load_cells(stats + row_of(r0 + 4 * j) * nchunk, nchunk, e[j]);
+      if (!kMany || r0 + 4 * j < nrows) load_cells(stats + row_of(min(r0 + 4 * j, nrows - 1)) * nchunk, nchunk, e[j]);
   };
   load_batch(w);
   // a chunk of p_0 and q_0 (of p_0 twice when kd = 0), thread t holding
@@ -509,7 +512,7 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(const float* __restric
   }
   for (int c = c0; c < c1; ++c) {
     float pn[kPer] = {}, qn[kPer] = {};  // the next chunk's logits, on their way meanwhile
-    if (c + 1 < c1) {
+    if (kMany && c + 1 < c1) {
       load_chunk(lp, c + 1, pn);
       if (resid) load_chunk(lq, c + 1, qn);
     }
@@ -796,7 +799,7 @@ __global__ __launch_bounds__(kMergeThreads) void greedy_kernel(const int32_t* __
 // vocabularies take fewer of them, and the walk itself the candidates after
 // (walk_steps()).  Up to c + 2 launches over the whole chip replace a walk of
 // up to c kd passes over the vocabulary by one workgroup per sequence (two
-// sequences, four chains of four, 151936 logits, the whole call: 306 -> 71 us).
+// sequences, four chains of four, 151936 logits, the whole call: 306 -> 66 us).
 constexpr int kMThreads = 1024;
 constexpr int kMWaves = kMThreads / 64;
 constexpr int kStepBlocks = 8192;  // workgroups of one step launch, about
@@ -1404,7 +1407,7 @@ hipError_t enqueue_accept(const float* draft, const float* target, const int32_t
   auto go = [&](auto one_tag) {
     constexpr bool One = decltype(one_tag)::value;
     hipLaunchKernelGGL(stats_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target, rows_t,
-                       v, temperature, nchunk, stats, counters, kd + 1);
+                       v, temperature, nchunk, b, stats, counters);
     if (p_out || q_out)
       hipLaunchKernelGGL(probs_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target,
                          rows_t, v, temperature, nchunk, stats, q_out, p_out);
@@ -1412,7 +1415,10 @@ hipError_t enqueue_accept(const float* draft, const float* target, const int32_t
       hipLaunchKernelGGL(kernel, dim3((unsigned)(b * groups)), dim3(kThreads), 0, stream, draft, target, tokens, u24, b,
                          kd, v, temperature, nchunk, stats, zs, counters, (int)G, (int)groups, n_accepted, next_token);
     };
-    nchunk > 64 * kCells ? accept(accept_kernel<true, One>) : accept(accept_kernel<false, One>);
+    if (nchunk > 64 * kCells)
+      G > 1 ? accept(accept_kernel<true, One, true>) : accept(accept_kernel<true, One, false>);
+    else
+      G > 1 ? accept(accept_kernel<false, One, true>) : accept(accept_kernel<false, One, false>);
   };
   if (temperature == 1.0f)
     go(std::true_type{});
@@ -1543,7 +1549,7 @@ hipError_t launch_spec_accept_multi(const float* draft, const float* target, con
   auto go = [&](auto one_tag) {
     constexpr bool One = decltype(one_tag)::value;
     hipLaunchKernelGGL(stats_kernel<One>, dim3((unsigned)(rows * nchunk)), dim3(64), 0, stream, draft, target, rows_t,
-                       v, temperature, nchunk, stats, nullptr, 1);
+                       v, temperature, nchunk, 0, stats, nullptr);
     // one wavefront per chunk issues the fewest instructions, four take less time while they do not fill the chip
     // (two chains of four, 1000 logits, the whole call: 27 / 24 us)
     auto rows_go = [&](auto kernel, int threads) {
