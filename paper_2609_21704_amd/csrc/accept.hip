@@ -744,18 +744,57 @@ __device__ __forceinline__ uint64_t row_key(const int64_t* k, int nchunk) {
   return wave_all(key, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
 }
 
-constexpr int kMergeThreads = 1024;  // 16 rows at a time
+// The key of logits j0 .. j1 of a row, by one wavefront.
+__device__ __forceinline__ uint64_t part_key(const float* l, int j0, int j1) {
+  uint64_t key = 0;
+  for (int j = j0 + (threadIdx.x & 63); j < j1; j += 64 * kGreedyPer) {
+    float x[kGreedyPer];
+#pragma unroll
+    for (int e = 0; e < kGreedyPer; ++e) x[e] = l[min(j + 64 * e, j1 - 1)];
+#pragma unroll
+    for (int e = 0; e < kGreedyPer; ++e) {
+      const uint64_t k = logit_key(x[e], min(j + 64 * e, j1 - 1));
+      key = k > key ? k : key;
+    }
+  }
+  return wave_all(key, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
+}
 
+constexpr int kMergeThreads = 1024;  // 16 wavefronts
+constexpr int kGreedyStep = 64 * kGreedyPer;  // logits of a wavefront's loads at once
+constexpr int kGreedySteps = 18;              // such loads of all wavefronts, at most
+
+// A sequence's decisions from its rows' keys.  kLogits: from the rows themselves, `split` wavefronts a row (more than
+// one where all rows go at once), and no launch before this one; else from the keys of their chunks.  One workgroup's
+// steps against a launch (one sequence, both launches / this one): 5 steps 5.9 / 4.2 us, 10 5.9 / 4.7, 18 6.4 / 6.0, 30
+// 5.9 / 7.0.
+template <bool kLogits>
 __global__ __launch_bounds__(kMergeThreads) void greedy_kernel(const int32_t* __restrict__ tokens, int b, int kd,
+                                                               const float* __restrict__ target, int v, int split,
                                                                int nchunk, const int64_t* __restrict__ keys,
                                                                int32_t* __restrict__ n_accepted,
                                                                int32_t* __restrict__ next_token) {
+  __shared__ uint64_t sKey[65];  // [row][part]: several parts of up to 16 wavefronts, or one of up to 65 rows
   __shared__ int sArg[65];
   const int s = blockIdx.x, i = threadIdx.x;
   const int32_t xt = i < kd ? tokens[(int64_t)i * b + s] : 0;  // (kd <= 64)
-  for (int r = i >> 6; r <= kd; r += blockDim.x >> 6) {
-    const int arg = key_index(row_key(keys + ((int64_t)s * (kd + 1) + r) * nchunk, nchunk));
-    if ((i & 63) == 0) sArg[r] = arg;
+  const int parts = kLogits ? split : 1, len = (v + parts - 1) / parts;
+  if (!kLogits && nchunk == 1) {
+    if (i <= kd) sKey[i] = (uint64_t)keys[(int64_t)s * (kd + 1) + i];
+  } else {
+    for (int w = i >> 6; w < (kd + 1) * parts; w += blockDim.x >> 6) {
+      const int64_t row = (int64_t)s * (kd + 1) + w / parts;
+      const int j0 = w % parts * len;
+      const uint64_t key =
+          kLogits ? part_key(target + row * v, j0, min(j0 + len, v)) : row_key(keys + row * nchunk, nchunk);
+      if ((i & 63) == 0) sKey[w] = key;
+    }
+  }
+  __syncthreads();
+  if (i <= kd) {
+    uint64_t key = sKey[i * parts];
+    for (int q = 1; q < parts; ++q) key = max(key, sKey[i * parts + q]);
+    sArg[i] = key_index(key);
   }
   __syncthreads();
   if (i >= 64) return;
@@ -1391,11 +1430,21 @@ hipError_t enqueue_accept(const float* draft, const float* target, const int32_t
       return hipGetLastError();
     }
     int64_t* keys = reinterpret_cast<int64_t*>(ws);
+    // wavefronts a row and steps of a wavefront, where the rows are read by the deciding kernel
+    int split = kd < 15 ? 16 / (kd + 1) : 1;
+    const int all = (v + kGreedyStep - 1) / kGreedyStep;
+    split = split < all ? split : all;
+    const int steps = ((v + split - 1) / split + kGreedyStep - 1) / kGreedyStep;
+    const bool direct = v <= kGreedyChunk && (kd + 1) * split * steps <= kGreedySteps;
+    const int waves = direct ? (kd + 1) * split : kd + 1;
+    auto decide = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)b), dim3(64 * (waves < 16 ? waves : 16)), 0, stream, tokens, b, kd,
+                         target, v, split, (v + kGreedyChunk - 1) / kGreedyChunk, keys, n_accepted, next_token);
+      return hipGetLastError();
+    };
+    if (direct) return decide(greedy_kernel<true>);
     const hipError_t e = enqueue_argmax(target, v, rows_t, keys, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(greedy_kernel, dim3((unsigned)b), dim3(64 * (kd < 15 ? kd + 1 : 16)), 0, stream, tokens, b, kd,
-                       (v + kGreedyChunk - 1) / kGreedyChunk, keys, n_accepted, next_token);
-    return hipGetLastError();
+    return e != hipSuccess ? e : decide(greedy_kernel<false>);
   }
   const int64_t rows = rows_t + (int64_t)b * kd;
   double2* stats = reinterpret_cast<double2*>(ws);

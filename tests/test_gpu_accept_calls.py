@@ -43,6 +43,32 @@ def test_spec_accept_greedy_rows(b, kd, v):
         assert sorted(set(n.tolist())) == list(range(kd + 1))
 
 
+# rows of one chunk, read by the deciding kernel: one to four wavefronts a row, one or two steps of 1024 logits, rows
+# in two passes; the first sizes past these
+@pytest.mark.parametrize("b,kd,v", [(3, 1, 1), (3, 4, 1024), (6, 4, 1025), (6, 4, 3072), (6, 4, 3073), (5, 3, 4096),
+                                    (9, 7, 2048), (9, 7, 2049), (10, 8, 2047), (3, 8, 2049), (17, 15, 1000),
+                                    (20, 16, 1024), (20, 16, 1025), (20, 17, 777), (33, 18, 777)])
+def test_spec_accept_greedy_short_rows(b, kd, v):
+    n = check(b, kd, v, 0.0, 600 + b + v)
+    if b > kd:
+        assert sorted(set(n.tolist())) == (list(range(kd + 1)) if v > 1 else [kd])
+
+
+def test_spec_accept_greedy_short_rows_ties_and_invalid():
+    """The largest logit twice, in different wavefronts' parts: the smaller index; NaN, +inf and all -inf in any part."""
+    b, kd, v = 8, 3, 4096
+    target = torch.randn((b, kd + 1, v), generator=torch.Generator().manual_seed(9))
+    target[:, :, 700] = target[:, :, 3900] = 9.0
+    target[1, 2, 4095] = float("nan")
+    target[2, 3, 1500] = float("inf")
+    target[3, 0] = float("-inf")
+    target[4, 1, 1024:] = float("-inf")
+    tok = torch.full((kd, b), 700, dtype=torch.int32)
+    tok[1, 5] = 3900
+    n, t, _, _ = _run_accept(torch.zeros((kd, b, v)), target, tok, torch.zeros((b, kd + 1), dtype=torch.int32), 0.0)
+    assert np.array_equal(n, [3, -1, -1, -1, 3, 1, 3, 3]) and np.array_equal(t, [700, -1, -1, -1, 700, 700, 700, 700])
+
+
 @pytest.mark.parametrize("temp", [1.0, 0.0])
 @pytest.mark.parametrize("b,kd,v", [(1, 0, 1000), (2, 4, 9000), (40, 1, 20000)])
 def test_spec_accept_after_other_calls_scratch(b, kd, v, temp):
