@@ -215,9 +215,10 @@ def test_qgemv_w4a16_short_rows(m, n, k):
 # So many row tiles per workgroup that up to 16 rows' chunk partial sums,
 # 64 m bytes a tile, exceed their 40 KB of LDS even in one chunk a tile (over 256
 # CUs 163840 weight rows at m = 16, 327680 at m = 8): the parent's projections
-# take another kernel, the drafts' the padded two-tile form.
-def test_verify_gemm_many_tiles_m16():
-    m, n, k = 16, 170000, 256
+# take another kernel, the drafts' the padded two-tile form.  The smaller sizes fit.
+@pytest.mark.parametrize("n,k", [(140000, 128), (170000, 256)])
+def test_verify_gemm_many_tiles_m16(n, k):
+    m = 16
     w = synth.normal_f16((n, k), 0.02, 51)
     x = synth.normal_f16((m, k), 1.0, 52)
     y_ref, d_ref = oracle.gemm_f16(bits16(x), bits16(w))
@@ -225,8 +226,9 @@ def test_verify_gemm_many_tiles_m16():
     assert oracle.normalised_error(y.cpu().numpy(), y_ref, d_ref) <= GEMV_TOL
 
 
-def test_qgemv_w8a16_many_tiles_m8():
-    m, n, k = 8, 340000, 256
+@pytest.mark.parametrize("n", [300000, 340000])
+def test_qgemv_w8a16_many_tiles_m8(n):
+    m, k = 8, 256
     rng = np.random.default_rng(53)
     codes = rng.integers(0, 256, size=(n, k), dtype=np.uint8)
     codes[(codes & 0x7F) == 0x7F] = 0  # no NaN codes
@@ -610,7 +612,7 @@ def test_qgemv_w8a16_large_parity(m, n, k):
 # partial sums at m = 16 (163840 rows and more over 256 CUs), which takes whole
 # tasks per wavefront instead.
 MANY_ROWS = [(9, 37, 384), (16, 896, 896), (17, 4864, 896), (33, 896, 4864), (48, 257, 3584), (64, 130, 3584),
-             (64, 1024, 18944), (16, 170000, 256), (12, 4608, 3584)]
+             (64, 1024, 18944), (16, 140000, 256), (16, 170000, 256), (12, 4608, 3584)]
 
 
 @pytest.mark.parametrize("m,n,k", MANY_ROWS)
